@@ -43,12 +43,40 @@ def _check_m0(src: str) -> None:
     listings = [p for p in OBJ.glob(f"{stem}-hip-amdgcn-amd-amdhsa-gfx950*.s")]
     if not listings:
         raise RuntimeError(f"no device assembly listing found for {src} in {OBJ}")
-    ours = re.compile(r"^\s*s_mov_b32\s+m0,\s*(s\d+|vcc_lo|vcc_hi)\s*$")
+    ours = re.compile(r"^\s*s_add_u32\s+m0,\s*(s\d+|vcc_lo|vcc_hi),\s*\w+\s*$")
     for listing in listings:
         for n, line in enumerate(listing.read_text().splitlines(), 1):
             code = line.split(";", 1)[0]
             if re.search(r"\bm0\b", code) and not ours.match(code):
                 raise RuntimeError(f"{listing.name}:{n}: M0 is used outside the direct-load sequence: {line.strip()}")
+
+
+def _check_accumulators(src: str) -> None:
+    """The MFMAs of the product kernels sit in inline assembly, so the compiler does not know when their results may be
+    read: an accumulation register that it copied or spilled by itself right behind an MFMA would give a wrong sum. In the
+    generated assembly, whatever touches an accumulation register has to stand at least twelve wait states behind the last
+    MFMA (seven are asked for), and whatever writes one at least three ahead of the next (two are asked for)."""
+    import re
+
+    acc = re.compile(r"\ba(\d+|\[\d+:\d+\])")
+    for listing in OBJ.glob(f"{src.rsplit('.', 1)[0]}-hip-amdgcn-amd-amdhsa-gfx950*.s"):
+        since_mfma, since_touch = 1000, 1000
+        for n, line in enumerate(listing.read_text().splitlines(), 1):
+            code = line.split(";", 1)[0].strip()
+            if not code or code.startswith(".") or code.endswith(":"):
+                continue
+            states = int(code.split()[1], 0) + 1 if code.startswith("s_nop") else 1
+            if code.startswith("v_mfma"):
+                if since_touch < 3:
+                    raise RuntimeError(f"{listing.name}:{n}: an accumulation register is written just ahead of an MFMA")
+                since_mfma = 0
+            elif acc.search(code):
+                if since_mfma < 12:
+                    raise RuntimeError(f"{listing.name}:{n}: an accumulation register is touched behind an MFMA: {code}")
+                since_touch = 0
+            else:
+                since_touch += states
+            since_mfma += states if not code.startswith("v_mfma") else 0
 
 
 def _compile(src: str) -> Path:
@@ -68,6 +96,7 @@ def _compile(src: str) -> Path:
         sys.stderr.write(err + "\n")
     if src in USES_M0:
         _check_m0(src)
+        _check_accumulators(src)
     return obj
 
 

@@ -38,14 +38,16 @@ struct Layout {
 };
 
 // Tile shape and count (the byte offsets of a layout do not depend on them: D exists only with k-blocking,
-// which never takes the small tiles).
-void set_tiles(Layout& L, int64_t m, int64_t n, int s, bool small) {
+// which never takes the small tiles). one_launch: a complex product in one launch, whose tiles hold every complex row and
+// column twice (from the real and from the imaginary planes).
+void set_tiles(Layout& L, int64_t m, int64_t n, int s, bool small, bool one_launch) {
     int wm, wn;
     tile_waves(s, small, &wm, &wn);
     L.tile_rows = wm * kFragRows;
     L.tile_cols = wn * kFragRows;
-    L.tiles_m = (int)((m + L.tile_rows - 1) / L.tile_rows);
-    L.tiles_n = (int)((n + L.tile_cols - 1) / L.tile_cols);
+    const int rows = L.tile_rows / (one_launch ? 2 : 1), cols = L.tile_cols / (one_launch ? 2 : 1);
+    L.tiles_m = (int)((m + rows - 1) / rows);
+    L.tiles_n = (int)((n + cols - 1) / cols);
 }
 
 Layout make_layout(int64_t m, int64_t n, int64_t k, int s, bool cplx) {
@@ -54,11 +56,10 @@ Layout make_layout(int64_t m, int64_t n, int64_t k, int s, bool cplx) {
     L.n_pad = round_up(n, kRowAlign);
     L.k_pad = round_up(k, kSlab);
     L.wide = needs_wide(s, L.k_pad);
-    // a complex product walks its four real products in one launch from three steps on (on 64 x 64 tiles only where
-    // the large ones would leave compute units without a tile: measured, a short inner dimension alone does not pay
-    // there); shorter ones take four launches of the real kernel and its tile choice
-    const bool one_launch = cplx && !L.wide && L.k_pad / kSlab >= 3;
-    set_tiles(L, m, n, s, one_launch ? use_small_tiles(m, n, INT64_MAX, s, L.wide) : use_small_tiles(m, n, L.k_pad, s, L.wide));
+    // a complex product without k-blocking runs in one launch (on 64 x 64 tiles only where the large ones would leave
+    // compute units without a tile)
+    const bool one_launch = cplx && !L.wide;
+    set_tiles(L, m, n, s, one_launch ? use_small_tiles(2 * m, 2 * n, INT64_MAX, s, L.wide) : use_small_tiles(m, n, L.k_pad, s, L.wide), one_launch);
     L.sa_bytes = (size_t)s * L.m_pad * L.k_pad;
     L.sb_bytes = (size_t)s * L.n_pad * L.k_pad;
     const int planes = cplx ? 2 : 1;
@@ -79,6 +80,45 @@ Layout make_layout(int64_t m, int64_t n, int64_t k, int s, bool cplx) {
     off = align_up(off + 2 * scan_slots_bytes(planes));
     L.total = off;
     return L;
+}
+
+// How many workgroups share a tile of C, each with a part of k. With fewer tiles than compute units most of the chip
+// idles while a tile's walk takes its time; integer sums add up exactly in any order, so the walk can be shared, at the
+// price of the parts' INT32 sums going through memory and of a kernel that adds and folds them. The line is drawn where
+// the estimate says so: a step of a walk takes what its MFMAs take (64 cycles per pair and wavefront of a SIMD at 2.1 GHz, and no
+// less than the 0.5 us its loads need), a launch more 5 us, the sums 3.5 TB/s. Measured (product and fold, one part against
+// the parts chosen): 1273 x 153 x 8000, 6 slices, 190 -> 45 us; 35 x 154 x 2251, 9 slices, 72 -> 15 us.
+struct Split {
+    int splits;
+    int slabs;      // of a part (even)
+    size_t bytes;   // of their sums
+};
+Split choose_split(const Layout& L, int s, size_t available) {
+    const int64_t tiles = (int64_t)L.tiles_m * L.tiles_n, slabs = L.k_pad / kSlab, steps = (slabs + 1) / 2;
+    const size_t part = (size_t)tiles * s * L.tile_rows * L.tile_cols * sizeof(int32_t);
+    Split best{1, (int)slabs, 0};
+    if (tiles == 0 || tiles >= kComputeUnits || steps < 8) return best;
+    const int pairs = s <= kBand ? s * (s + 1) / 2 : s * (s + 1) / 2 + s - kBand;   // (a second band costs about its slices more)
+    const double step_us = std::max(0.5, pairs * (L.tile_cols == 128 ? 128.0 : 64.0) / 2100.0);
+    const double alone = steps * step_us;
+    double best_us = 0.85 * alone;
+    for (int64_t n = 2; n <= 64 && n * 2 <= steps; ++n) {
+        const int64_t chunk = (steps + n - 1) / n, parts = (steps + chunk - 1) / chunk;
+        if (2 * chunk * kSlab * s > OZIMMU_INT32_BLOCK || part * parts > available || tiles * parts > 2 * kComputeUnits) continue;
+        const double us = chunk * step_us * (tiles * parts > kComputeUnits ? 1.5 : 1.0) + 5.0 + 2.0 * part * parts / 3.5e6;
+        if (us < best_us) {
+            best_us = us;
+            best = Split{(int)parts, (int)(2 * chunk), part * (size_t)parts};
+        }
+    }
+    return best;
+}
+// Room for those sums behind a workspace of `total` bytes. They are used where the caller's workspace has it, but are not
+// asked for: smaller ones are accepted as well, and a product that fits the built-in scratch of ozimmu_dgemm_static fits
+// it with what is reported here.
+size_t split_room(const Layout& L, int s, size_t total) {
+    const size_t limit = OZIMMU_STATIC_SCRATCH_BYTES;
+    return choose_split(L, s, total <= limit ? limit - total : SIZE_MAX).bytes;
 }
 
 ozimmu_status_t hip_status(hipError_t e) { return e == hipSuccess ? OZIMMU_OK : OZIMMU_ERR_HIP; }
@@ -119,8 +159,69 @@ hipError_t split_complex_rows(const double* Z, int64_t ld, int64_t rows, int64_t
 
 // One real Ozaki product from already split planes: G = sum over diagonals, combined into C as
 // c_mode says (C_lo != nullptr: double-double sum into C, C_lo).
+// An operand of a product as it is stored: `count` vectors along k, rows or columns of a row-major array.
+struct Stored {
+    const double* X;
+    int64_t ld, count;
+    bool by_cols, negate_im;
+};
+// Slices and exponents of both operands: `a` into the layout's A, `b` into its B. sums_a, sums_b (both or neither;
+// [planes][16], device or mapped host memory): the splitters also count for the check of s as the automatic slice count
+// (Section 4.4), and the bits the planes lose with s and with s - 1 slices arrive there.
+hipError_t split_operands(const Layout& L, bool cplx, const Stored& a, const Stored& b, int64_t k, int s, unsigned char* ws,
+                          hipStream_t st, unsigned long long* sums_a = nullptr, unsigned long long* sums_b = nullptr) {
+    const int planes = cplx ? 2 : 1;
+    unsigned long long* colmax = reinterpret_cast<unsigned long long*>(ws + L.off_colmax);
+    unsigned long long* slots[2] = {nullptr, nullptr};
+    SplitOperand x[2];
+    for (int o = 0; o < 2; ++o) {
+        const Stored& y = o ? b : a;
+        x[o] = SplitOperand{y.X, y.ld, y.count, o ? L.n_pad : L.m_pad, y.by_cols, y.negate_im, {}, {}};
+        for (int p = 0; p < planes; ++p) {
+            x[o].S[p] = reinterpret_cast<int8_t*>(ws + (o ? L.off_sb : L.off_sa)[p]);
+            x[o].E[p] = reinterpret_cast<int32_t*>(ws + (o ? L.off_eb : L.off_ea)[p]);
+        }
+    }
+    hipError_t e = hipSuccess;
+    if (sums_a) {
+        slots[0] = reinterpret_cast<unsigned long long*>(ws + L.off_scan);
+        slots[1] = slots[0] + scan_slots_bytes(planes) / sizeof(unsigned long long);
+        e = launch_fill_u64(slots[0], (int64_t)(2 * scan_slots_bytes(planes) / sizeof(unsigned long long)), 0ull, st);
+    }
+    for (int o = 0; o < 2 && e == hipSuccess; ++o) {
+        const SplitOperand& y = x[o];
+        if (cplx && y.by_cols)
+            e = launch_split_cols_complex(y.X, y.ld, k, y.count, s, y.S[0], y.S[1], y.padded, L.k_pad, y.E[0], y.E[1], colmax, st, y.negate_im, slots[o]);
+        else if (cplx)
+            e = split_complex_rows(y.X, y.ld, y.count, k, s, ws, o ? L.off_sb : L.off_sa, o ? L.off_eb : L.off_ea, y.padded, L.k_pad, st, y.negate_im, slots[o]);
+        else if (y.by_cols)
+            e = launch_split_cols(y.X, y.ld, 1, k, y.count, s, y.S[0], y.padded, L.k_pad, y.E[0], colmax, st, false, slots[o], 5);
+        else
+            e = launch_split_rows(y.X, y.ld, 1, y.count, k, s, y.S[0], y.padded, L.k_pad, y.E[0], st, false, slots[o], 5);
+    }
+    if (e == hipSuccess && sums_a) e = launch_scan_reduce(slots[0], planes, s, sums_a, sums_b, st);
+    return e;
+}
+
+// Where the INT32 sums of shared walks may go: the part of the caller's workspace beyond what the layout needs.
+struct Room {
+    unsigned char* p;
+    size_t bytes;
+};
+Room room_behind(unsigned char* ws, size_t used, size_t workspace_bytes) {
+    used = align_up(used);
+    return workspace_bytes > used ? Room{ws + used, workspace_bytes - used} : Room{nullptr, 0};
+}
+void set_split(GemmArgs& g, const Layout& L, int s, const Room& room) {
+    const Split sp = choose_split(L, s, room.bytes);
+    g.splits = sp.splits;
+    g.split_slabs = sp.slabs;
+    g.partial = reinterpret_cast<int*>(room.p);
+    if (sp.splits > 1) g.block_steps = 0;   // every part fits INT32 sums
+}
+
 hipError_t run_product(const Layout& L, int64_t m, int64_t n, int s, unsigned char* ws, int plane_a, int plane_b,
-                       double* C, int64_t ldc, int c_mode, hipStream_t st, double alpha = 1.0, double beta = 0.0,
+                       double* C, int64_t ldc, int c_mode, hipStream_t st, const Room& room, double alpha = 1.0, double beta = 0.0,
                        double* C_lo = nullptr, double* Zr = nullptr, double* Cz = nullptr, int64_t ldcz = 0) {
     GemmArgs g{};
     g.SA = reinterpret_cast<const int8_t*>(ws + L.off_sa[plane_a]);
@@ -148,22 +249,21 @@ hipError_t run_product(const Layout& L, int64_t m, int64_t n, int s, unsigned ch
     g.Zr = Zr;
     g.Cz = Cz;
     g.ldcz = ldcz;
+    set_split(g, L, s, room);
     return launch_slice_gemm(g, s, C_lo ? 1 : 0, st);
 }
 
 // The four real products of a complex one from the split planes (0 = real, 1 = imaginary):
-// Cr = G(Ar,Br) - G(Ai,Bi);  Ci = G(Ar,Bi) + G(Ai,Br). The two parts are formed in two m x n planes of
+// Cr = G(Ar,Br) - G(Ai,Bi);  Ci = G(Ar,Bi) + G(Ai,Br). One launch forms them all and writes C as (re, im) pairs. With
+// k-blocking, four launches of the real kernel: the two parts are formed in two m x n planes of
 // the workspace (contiguous FP64: every update there is a full-line access), the second product of
 // each part combined with the first by one rounded FP64 operation in the kernel's epilogue; the
 // epilogue of the last product writes C, once, as (re, im) pairs.
 hipError_t run_complex_products(const Layout& L, int64_t m, int64_t n, int s, unsigned char* ws, double* C,
-                                int64_t ldc, hipStream_t st) {
+                                int64_t ldc, hipStream_t st, const Room& room) {
     double* Pr = reinterpret_cast<double*>(ws + L.off_z);
     double* Pi = Pr + (size_t)m * n;
-    // one launch: every workgroup walks the four products of its tile one after the other (the walk runs
-    // three steps ahead of the matrix cores: shorter products and k-blocked ones take four launches;
-    // make_layout has chosen the tiles accordingly)
-    if (!L.wide && L.k_pad / kSlab >= 3) {
+    if (!L.wide) {
         GemmArgs g{};
         g.SA = reinterpret_cast<const int8_t*>(ws + L.off_sa[0]);
         g.SA2 = reinterpret_cast<const int8_t*>(ws + L.off_sa[1]);
@@ -183,18 +283,15 @@ hipError_t run_complex_products(const Layout& L, int64_t m, int64_t n, int s, un
         g.tile_cols = L.tile_cols;
         g.m = (int)m;
         g.n = (int)n;
-        g.Zr = Pr;
-        g.C = Pi;
-        g.ldc = n;
         g.Cz = C;
         g.ldcz = ldc;
-        g.alpha = 1.0;
+        set_split(g, L, s, room);
         return launch_slice_gemm(g, s, 2, st);
     }
-    hipError_t e = run_product(L, m, n, s, ws, 0, 0, Pr, n, 0, st);
-    if (e == hipSuccess) e = run_product(L, m, n, s, ws, 1, 1, Pr, n, 2, st);
-    if (e == hipSuccess) e = run_product(L, m, n, s, ws, 0, 1, Pi, n, 0, st);
-    if (e == hipSuccess) e = run_product(L, m, n, s, ws, 1, 0, Pi, n, 4, st, 1.0, 0.0, nullptr, Pr, C, ldc);
+    hipError_t e = run_product(L, m, n, s, ws, 0, 0, Pr, n, 0, st, room);
+    if (e == hipSuccess) e = run_product(L, m, n, s, ws, 1, 1, Pr, n, 2, st, room);
+    if (e == hipSuccess) e = run_product(L, m, n, s, ws, 0, 1, Pi, n, 0, st, room);
+    if (e == hipSuccess) e = run_product(L, m, n, s, ws, 1, 0, Pi, n, 4, st, room, 1.0, 0.0, nullptr, Pr, C, ldc);
     return e;
 }
 
@@ -315,36 +412,6 @@ ozimmu_status_t auto_select(const ScanOperand& a, const ScanOperand& b, int64_t 
     return OZIMMU_OK;
 }
 
-// The splits of a product that also count for the check of num_slices as the automatic slice count (Section 4.4), and
-// the two small kernels that leave the bits lost with num_slices and num_slices - 1 slices in `sums` ([planes][16],
-// device or mapped host memory; first operand's planes first). Arguments already validated.
-hipError_t counting_splits(bool cplx, const Layout& L, int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
-                           const double* B, int64_t ldb, int s, unsigned char* ws, unsigned long long* sums, hipStream_t st) {
-    const int planes = cplx ? 2 : 1;
-    unsigned long long* slots_a = reinterpret_cast<unsigned long long*>(ws + L.off_scan);
-    unsigned long long* slots_b = slots_a + scan_slots_bytes(planes) / sizeof(unsigned long long);
-    unsigned long long* colmax = reinterpret_cast<unsigned long long*>(ws + L.off_colmax);
-    hipError_t e = launch_fill_u64(slots_a, (int64_t)(2 * scan_slots_bytes(planes) / sizeof(unsigned long long)), 0ull, st);
-    if (e != hipSuccess) return e;
-    if (cplx) {
-        e = split_complex_rows(A, lda, m, k, s, ws, L.off_sa, L.off_ea, L.m_pad, L.k_pad, st, false, slots_a);
-        if (e == hipSuccess)
-            e = launch_split_cols_complex(B, ldb, k, n, s, reinterpret_cast<int8_t*>(ws + L.off_sb[0]),
-                                          reinterpret_cast<int8_t*>(ws + L.off_sb[1]), L.n_pad, L.k_pad,
-                                          reinterpret_cast<int32_t*>(ws + L.off_eb[0]), reinterpret_cast<int32_t*>(ws + L.off_eb[1]),
-                                          colmax, st, false, slots_b);
-    } else {
-        e = launch_split_rows(A, lda, 1, m, k, s, reinterpret_cast<int8_t*>(ws + L.off_sa[0]), L.m_pad, L.k_pad,
-                              reinterpret_cast<int32_t*>(ws + L.off_ea[0]), st, false, slots_a, 5);
-        if (e == hipSuccess)
-            e = launch_split_cols(B, ldb, 1, k, n, s, reinterpret_cast<int8_t*>(ws + L.off_sb[0]), L.n_pad, L.k_pad,
-                                  reinterpret_cast<int32_t*>(ws + L.off_eb[0]), colmax, st, false, slots_b, 5);
-    }
-    if (e == hipSuccess) e = launch_scan_reduce(slots_a, planes, s, sums, st);
-    if (e == hipSuccess) e = launch_scan_reduce(slots_b, planes, s, sums + planes * OZIMMU_MAX_SLICES, st);
-    return e;
-}
-
 // Slice count and product in one call (see ozimmu_dgemm_auto / ozimmu_zgemm_auto in ozimmu.h).
 ozimmu_status_t gemm_auto(bool cplx, int64_t m, int64_t n, int64_t k, const double* A, int64_t lda, const double* B,
                           int64_t ldb, double* C, int64_t ldc, double threshold, int max_slices, int guess, void* workspace,
@@ -390,9 +457,11 @@ ozimmu_status_t gemm_auto(bool cplx, int64_t m, int64_t n, int64_t k, const doub
         // sums for `guess` and `guess - 1` in the mapped buffer, and the product follows at once; one wait at the end.
         L = make_layout(m, n, k, guess, cplx);
         unsigned char* ws = static_cast<unsigned char*>(workspace);
-        hipError_t e = counting_splits(cplx, L, m, n, k, A, lda, B, ldb, guess, ws, host, st);
+        hipError_t e = split_operands(L, cplx, Stored{A, lda, m, false, false}, Stored{B, ldb, n, true, false}, k, guess, ws, st, host,
+                                      host + (cplx ? 2 : 1) * OZIMMU_MAX_SLICES);
         if (e == hipSuccess)
-            e = cplx ? run_complex_products(L, m, n, guess, ws, C, ldc, st) : run_product(L, m, n, guess, ws, 0, 0, C, ldc, 0, st);
+            e = cplx ? run_complex_products(L, m, n, guess, ws, C, ldc, st, room_behind(ws, L.total, workspace_bytes))
+                     : run_product(L, m, n, guess, ws, 0, 0, C, ldc, 0, st, room_behind(ws, L.total, workspace_bytes));
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) return OZIMMU_ERR_HIP;
         if (guess_holds(host, cplx ? 4 : 2, count_a, count_b, threshold, guess, max_slices)) {
@@ -495,6 +564,7 @@ ozimmu_status_t ozimmu_slice_gemm(int64_t m, int64_t n, int64_t k, const int8_t*
     g.tile_cols = L.tile_cols;
     g.m = (int)m;
     g.n = (int)n;
+    g.splits = 1;
     g.P = P;
     g.ldp = ldp;
     return hip_status(launch_slice_gemm(g, 1, 0, st));
@@ -505,7 +575,13 @@ ozimmu_status_t ozimmu_workspace_bytes(int64_t m, int64_t n, int64_t k, int num_
     if (!dims_ok(m, n, k)) return OZIMMU_ERR_BAD_DIM;
     if (num_slices < 1 || num_slices > OZIMMU_MAX_SLICES) return OZIMMU_ERR_BAD_SLICES;
     if (!bytes) return OZIMMU_ERR_NULL;
-    *bytes = make_layout(m, n, k, num_slices, is_complex != 0).total;
+    Layout L = make_layout(m, n, k, num_slices, is_complex != 0);
+    size_t room = split_room(L, num_slices, L.total);
+    if (!is_complex) {   // a double-double product runs on the large tiles
+        set_tiles(L, m, n, num_slices, false, false);
+        room = std::max(room, split_room(L, num_slices, L.total));
+    }
+    *bytes = L.total + room;
     return OZIMMU_OK;
 }
 
@@ -531,19 +607,23 @@ ozimmu_status_t ozimmu_dgemm_stage(int stage, int64_t m, int64_t n, int64_t k, c
                                                 reinterpret_cast<int32_t*>(ws + L.off_eb[0]),
                                                 reinterpret_cast<unsigned long long*>(ws + L.off_colmax), st));
         default:
-            return hip_status(run_product(L, m, n, num_slices, ws, 0, 0, C, ldc, 0, st));
+            return hip_status(run_product(L, m, n, num_slices, ws, 0, 0, C, ldc, 0, st, room_behind(ws, L.total, workspace_bytes)));
     }
 }
 
 ozimmu_status_t ozimmu_dgemm(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda, const double* B,
                              int64_t ldb, double* C, int64_t ldc, int num_slices, void* workspace,
                              size_t workspace_bytes, void* stream) {
-    for (int stage = 0; stage < 3; ++stage) {
-        ozimmu_status_t rc = ozimmu_dgemm_stage(stage, m, n, k, A, lda, B, ldb, C, ldc, num_slices, workspace,
-                                                workspace_bytes, stream);
-        if (rc != OZIMMU_OK) return rc;
-    }
-    return OZIMMU_OK;
+    Layout L{};
+    ozimmu_status_t rc = check_gemm_args(m, n, k, A, lda, B, ldb, C, ldc, num_slices, workspace, workspace_bytes,
+                                         false, &L);
+    if (rc != OZIMMU_OK || m == 0 || n == 0) return rc;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (k == 0) return hip_status(launch_fill_f64(C, ldc, 1, m, n, 0.0, st));
+    unsigned char* ws = static_cast<unsigned char*>(workspace);
+    hipError_t e = split_operands(L, false, Stored{A, lda, m, false, false}, Stored{B, ldb, n, true, false}, k, num_slices, ws, st);
+    if (e == hipSuccess) e = run_product(L, m, n, num_slices, ws, 0, 0, C, ldc, 0, st, room_behind(ws, L.total, workspace_bytes));
+    return hip_status(e);
 }
 
 ozimmu_status_t ozimmu_zgemm(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda, const double* B,
@@ -564,14 +644,9 @@ ozimmu_status_t ozimmu_zgemm(int64_t m, int64_t n, int64_t k, const double* A, i
     hipError_t e = hipSuccess;
     // a small B on a tall A (a gate on a state vector): one kernel that splits A on the fly and reads it once
     if (gate_product_applies(A, B, C, n, k, s)) return hip_status(launch_gate_product(A, lda, m, k, n, B, ldb, s, ws + L.off_gate, C, ldc, st));
-    // the real and imaginary planes are separated while splitting (element stride 2)
-    e = split_complex_rows(A, lda, m, k, s, ws, L.off_sa, L.off_ea, L.m_pad, L.k_pad, st, false);
-    if (e == hipSuccess)
-        e = launch_split_cols_complex(B, ldb, k, n, s, reinterpret_cast<int8_t*>(ws + L.off_sb[0]),
-                                      reinterpret_cast<int8_t*>(ws + L.off_sb[1]), L.n_pad, L.k_pad,
-                                      reinterpret_cast<int32_t*>(ws + L.off_eb[0]), reinterpret_cast<int32_t*>(ws + L.off_eb[1]),
-                                      reinterpret_cast<unsigned long long*>(ws + L.off_colmax), st);
-    if (e == hipSuccess) e = run_complex_products(L, m, n, s, ws, C, ldc, st);
+    // the real and imaginary planes are separated while splitting
+    e = split_operands(L, true, Stored{A, lda, m, false, false}, Stored{B, ldb, n, true, false}, k, s, ws, st);
+    if (e == hipSuccess) e = run_complex_products(L, m, n, s, ws, C, ldc, st, room_behind(ws, L.total, workspace_bytes));
     return hip_status(e);
 }
 
@@ -652,26 +727,10 @@ static ozimmu_status_t dgemm_blas_impl(char transa, char transb, int64_t m, int6
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) % OZIMMU_WORKSPACE_ALIGN) != 0 || workspace_bytes < L.total)
         return OZIMMU_ERR_WORKSPACE;
     unsigned char* ws = static_cast<unsigned char*>(workspace);
-    int8_t* SR = reinterpret_cast<int8_t*>(ws + L.off_sa[0]);      // slices of op(B)^T: n rows of length k
-    int8_t* SC = reinterpret_cast<int8_t*>(ws + L.off_sb[0]);      // slices of op(A): m rows of length k
-    int32_t* ER = reinterpret_cast<int32_t*>(ws + L.off_ea[0]);
-    int32_t* EC = reinterpret_cast<int32_t*>(ws + L.off_eb[0]);
-    unsigned long long* colmax = reinterpret_cast<unsigned long long*>(ws + L.off_colmax);
-    hipError_t e = hipSuccess;
-    unsigned long long* slots_a = count_sums ? reinterpret_cast<unsigned long long*>(ws + L.off_scan) : nullptr;
-    unsigned long long* slots_b = count_sums ? slots_a + scan_slots_bytes(1) / sizeof(unsigned long long) : nullptr;
-    if (count_sums) e = launch_fill_u64(slots_a, (int64_t)(2 * scan_slots_bytes(1) / sizeof(unsigned long long)), 0ull, st);
-    if (e == hipSuccess) {
-        if (!tb) e = launch_split_rows(B, ldb, 1, n, k, num_slices, SR, L.m_pad, L.k_pad, ER, st, false, slots_b, 5);   // B: k x n, column j contiguous
-        else e = launch_split_cols(B, ldb, 1, k, n, num_slices, SR, L.m_pad, L.k_pad, ER, colmax, st, false, slots_b, 5);  // B: n x k
-    }
-    if (e == hipSuccess) {
-        if (!ta) e = launch_split_cols(A, lda, 1, k, m, num_slices, SC, L.n_pad, L.k_pad, EC, colmax, st, false, slots_a, 5);  // A: m x k
-        else e = launch_split_rows(A, lda, 1, m, k, num_slices, SC, L.n_pad, L.k_pad, EC, st, false, slots_a, 5);              // A: k x m
-    }
-    if (e == hipSuccess && count_sums) e = launch_scan_reduce(slots_a, 1, num_slices, count_sums, st);
-    if (e == hipSuccess && count_sums) e = launch_scan_reduce(slots_b, 1, num_slices, count_sums + OZIMMU_MAX_SLICES, st);
-    if (e == hipSuccess) e = run_product(L, n, m, num_slices, ws, 0, 0, C, ldc, 3, st, alpha, beta);
+    // op(B)^T: n rows of length k (B stored k x n by columns, or n x k); op(A): m rows of length k (A m x k, or k x m)
+    hipError_t e = split_operands(L, false, Stored{B, ldb, n, tb, false}, Stored{A, lda, m, !ta, false}, k, num_slices, ws, st,
+                                  count_sums ? count_sums + OZIMMU_MAX_SLICES : nullptr, count_sums);
+    if (e == hipSuccess) e = run_product(L, n, m, num_slices, ws, 0, 0, C, ldc, 3, st, room_behind(ws, L.total, workspace_bytes), alpha, beta);
     return hip_status(e);
 }
 
@@ -683,14 +742,19 @@ ozimmu_status_t ozimmu_dgemm_blas(char transa, char transb, int64_t m, int64_t n
                            workspace_bytes, stream, nullptr);
 }
 
+// What a complex BLAS-style product needs: beside the slices, the product before the update if C's old values are kept.
+static size_t zgemm_blas_bytes(const Layout& L, int64_t m, int64_t n, bool beta_zero) {
+    return beta_zero ? L.total : align_up(L.total + 2 * sizeof(double) * (size_t)m * (size_t)n);
+}
+
 ozimmu_status_t ozimmu_zgemm_blas_workspace_bytes(int64_t m, int64_t n, int64_t k, int num_slices, int beta_is_zero,
                                                   size_t* bytes) {
     if (!dims_ok(m, n, k)) return OZIMMU_ERR_BAD_DIM;
     if (num_slices < 1 || num_slices > OZIMMU_MAX_SLICES) return OZIMMU_ERR_BAD_SLICES;
     if (!bytes) return OZIMMU_ERR_NULL;
-    size_t total = make_layout(n, m, k, num_slices, true).total;
-    if (!beta_is_zero) total = align_up(total + 2 * sizeof(double) * (size_t)m * (size_t)n);   // the product before the update
-    *bytes = total;
+    const Layout L = make_layout(n, m, k, num_slices, true);
+    const size_t total = zgemm_blas_bytes(L, m, n, beta_is_zero);
+    *bytes = total + split_room(L, num_slices, total);
     return OZIMMU_OK;
 }
 
@@ -716,13 +780,11 @@ static ozimmu_status_t zgemm_blas_impl(char transa, char transb, int64_t m, int6
     // C^T = op(B)^T op(A)^T (a complex product commutes element by element, so the parts are the same).
     if (k == 0 || (ar == 0.0 && ai == 0.0)) return hip_status(launch_zaxpby(nullptr, 0, C, ldc, n, m, 0.0, 0.0, br, bi, st));
     if (!A || !B) return OZIMMU_ERR_NULL;
-    size_t need = 0;
-    ozimmu_zgemm_blas_workspace_bytes(m, n, k, num_slices, beta_zero, &need);
+    const Layout L = make_layout(n, m, k, num_slices, true);
+    const size_t need = zgemm_blas_bytes(L, m, n, beta_zero);
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) % OZIMMU_WORKSPACE_ALIGN) != 0 || workspace_bytes < need)
         return OZIMMU_ERR_WORKSPACE;
-    const Layout L = make_layout(n, m, k, num_slices, true);
     unsigned char* ws = static_cast<unsigned char*>(workspace);
-    unsigned long long* colmax = reinterpret_cast<unsigned long long*>(ws + L.off_colmax);
     hipError_t e = hipSuccess;
     const bool alpha_one = ar == 1.0 && ai == 0.0;
     // The product goes straight into C when C's old values are not needed, else beside the slices.
@@ -735,29 +797,10 @@ static ozimmu_status_t zgemm_blas_impl(char transa, char transb, int64_t m, int6
         if (e == hipSuccess && !(beta_zero && alpha_one)) e = launch_zaxpby(G, ldg, C, ldc, n, m, ar, ai, br, bi, st);
         return hip_status(e);
     }
-    unsigned long long* slots_a = count_sums ? reinterpret_cast<unsigned long long*>(ws + L.off_scan) : nullptr;
-    unsigned long long* slots_b = count_sums ? slots_a + scan_slots_bytes(2) / sizeof(unsigned long long) : nullptr;
-    if (count_sums) e = launch_fill_u64(slots_a, (int64_t)(2 * scan_slots_bytes(2) / sizeof(unsigned long long)), 0ull, st);
-    // planes: real, then imaginary (negated while splitting if the operand is conjugated)
-    if (e == hipSuccess) {
-        if (!tb) e = split_complex_rows(B, ldb, n, k, num_slices, ws, L.off_sa, L.off_ea, L.m_pad, L.k_pad, st, false, slots_b);   // op(B)^T: n rows of length k
-        else
-            e = launch_split_cols_complex(B, ldb, k, n, num_slices, reinterpret_cast<int8_t*>(ws + L.off_sa[0]),
-                                          reinterpret_cast<int8_t*>(ws + L.off_sa[1]), L.m_pad, L.k_pad,
-                                          reinterpret_cast<int32_t*>(ws + L.off_ea[0]), reinterpret_cast<int32_t*>(ws + L.off_ea[1]),
-                                          colmax, st, tb == 2, slots_b);
-    }
-    if (e == hipSuccess) {
-        if (ta) e = split_complex_rows(A, lda, m, k, num_slices, ws, L.off_sb, L.off_eb, L.n_pad, L.k_pad, st, ta == 2, slots_a);   // op(A): m rows of length k
-        else
-            e = launch_split_cols_complex(A, lda, k, m, num_slices, reinterpret_cast<int8_t*>(ws + L.off_sb[0]),
-                                          reinterpret_cast<int8_t*>(ws + L.off_sb[1]), L.n_pad, L.k_pad,
-                                          reinterpret_cast<int32_t*>(ws + L.off_eb[0]), reinterpret_cast<int32_t*>(ws + L.off_eb[1]),
-                                          colmax, st, false, slots_a);
-    }
-    if (e == hipSuccess && count_sums) e = launch_scan_reduce(slots_a, 2, num_slices, count_sums, st);
-    if (e == hipSuccess && count_sums) e = launch_scan_reduce(slots_b, 2, num_slices, count_sums + 2 * OZIMMU_MAX_SLICES, st);
-    if (e == hipSuccess) e = run_complex_products(L, n, m, num_slices, ws, G, ldg, st);
+    // planes: real, then imaginary (negated while splitting if the operand is conjugated); operands as in dgemm_blas_impl
+    e = split_operands(L, true, Stored{B, ldb, n, tb != 0, tb == 2}, Stored{A, lda, m, ta == 0, ta == 2}, k, num_slices, ws, st,
+                       count_sums ? count_sums + 2 * OZIMMU_MAX_SLICES : nullptr, count_sums);
+    if (e == hipSuccess) e = run_complex_products(L, n, m, num_slices, ws, G, ldg, st, room_behind(ws, need, workspace_bytes));
     if (e == hipSuccess && !(beta_zero && alpha_one)) e = launch_zaxpby(G, ldg, C, ldc, n, m, ar, ai, br, bi, st);
     return hip_status(e);
 }
@@ -784,10 +827,8 @@ static ozimmu_status_t gemm_blas_auto(bool cplx, char transa, char transb, int64
     const bool alpha_zero = alpha[0] == 0.0 && (!cplx || alpha[1] == 0.0);
     // the workspace must serve whichever slice count comes out
     for (int s = 1; s <= max_slices; ++s) {
-        size_t need = 0;
-        const ozimmu_status_t rc = cplx ? ozimmu_zgemm_blas_workspace_bytes(m, n, k, s, beta_zero, &need)
-                                        : ozimmu_workspace_bytes(n, m, k, s, 0, &need);
-        if (rc != OZIMMU_OK) return rc;
+        const Layout L = make_layout(n, m, k, s, cplx);
+        const size_t need = cplx ? zgemm_blas_bytes(L, m, n, beta_zero) : L.total;
         if (m > 0 && n > 0 && k > 0 && !alpha_zero && workspace_bytes < need) return OZIMMU_ERR_WORKSPACE;
     }
     if (!scratch_ok(scratch, scratch_bytes, std::max(m, n))) return OZIMMU_ERR_WORKSPACE;
@@ -857,13 +898,11 @@ ozimmu_status_t ozimmu_dgemm_dd(int64_t m, int64_t n, int64_t k, const double* A
         if (e0 == hipSuccess) e0 = launch_fill_f64(C_lo, ldc, 1, m, n, 0.0, st);
         return hip_status(e0);
     }
-    for (int stage = 0; stage < 2; ++stage) {   // the two splits are those of ozimmu_dgemm
-        rc = ozimmu_dgemm_stage(stage, m, n, k, A, lda, B, ldb, C_hi, ldc, num_slices, workspace, workspace_bytes, stream);
-        if (rc != OZIMMU_OK) return rc;
-    }
     unsigned char* ws = static_cast<unsigned char*>(workspace);
-    set_tiles(L, m, n, num_slices, false);   // the double-double kernels exist for the large tiles only
-    return hip_status(run_product(L, m, n, num_slices, ws, 0, 0, C_hi, ldc, 0, st, 1.0, 0.0, C_lo));
+    const hipError_t e = split_operands(L, false, Stored{A, lda, m, false, false}, Stored{B, ldb, n, true, false}, k, num_slices, ws, st);
+    if (e != hipSuccess) return OZIMMU_ERR_HIP;
+    set_tiles(L, m, n, num_slices, false, false);   // the double-double kernels exist for the large tiles only
+    return hip_status(run_product(L, m, n, num_slices, ws, 0, 0, C_hi, ldc, 0, st, room_behind(ws, L.total, workspace_bytes), 1.0, 0.0, C_lo));
 }
 
 ozimmu_status_t ozimmu_launch_plan(int64_t m, int64_t n, int64_t k, int num_slices, ozimmu_plan_t* plan) {

@@ -68,11 +68,6 @@ __device__ __forceinline__ unsigned lost_bits(uint32_t z, uint32_t L, int s) {
     return (unsigned)((below > 0 ? below : 0) - (above > 0 ? above : 0));
 }
 
-typedef int v4acc __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ v4acc mfma16(const v4i& a, const v4i& b, const v4acc& c) {
-    return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0);
-}
-
 // ---------------------------------------------------------------------------- the gate -> T1, T2, exponents
 // One workgroup per fragment f (8 columns of B). Thread (c, w) = (tid % 8, tid / 8) owns column 8 f + c and the four
 // positions 4 w .. 4 w + 3 of k. T: tensor t at t * s * nfr * ks KiB, slice q at q * nfr * ks KiB, fragment (f, step)
@@ -356,7 +351,7 @@ void gate_kernel(const GateArgs g) {
     const int np = g.n > 8 * cg ? (g.n - 8 * cg - 1) / (8 * CGS) + 1 : 0;
     if (np == 0) return;
 
-    v4acc acc[S];
+    v4i acc[S];
     v4i a[S];
     double part[4];
     // iteration it: patch it / 2, pass it % 2 (0: Ar with T1, 1: Ai with T2)
@@ -377,7 +372,7 @@ void gate_kernel(const GateArgs g) {
                 constexpr int q = decltype(qc)::value, pmax = S - 1 - q;
                 static_for<0, pmax + 1>([&](auto ic) __attribute__((always_inline)) {
                     constexpr int p = pmax - decltype(ic)::value;
-                    if constexpr (step == 0 && q == 0) acc[p] = mfma16(a[p], b[0], v4acc{0, 0, 0, 0});
+                    if constexpr (step == 0 && q == 0) acc[p] = mfma16(a[p], b[0], v4i{0, 0, 0, 0});
                     else acc[p + q] = mfma16(a[p], b[q], acc[p + q]);
                 });
                 if constexpr (last_step) {
@@ -485,9 +480,7 @@ __global__ __launch_bounds__(1024) void gate_scan_reduce_kernel(const unsigned* 
     }
 #pragma unroll
     for (int i = 0; i < 2 * kScanCounters; ++i) {
-        unsigned long long v = mine[i];
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+        const unsigned long long v = wave_sum(mine[i]);
         if ((threadIdx.x & 63) == 0 && v) atomicAdd(&sums[i], v);
     }
     const unsigned* of_gate = partials + 2 * kScanCounters * tiles;

@@ -4,5 +4,6 @@
 namespace ozimmu {
 
 hipError_t launch_product_complex(const GemmArgs& g, int s, hipStream_t st) { return launch_product_mode<kModeComplex>(g, s, st); }
+hipError_t launch_fold_complex(const GemmArgs& g, int s, hipStream_t st) { return launch_fold_mode<kModeComplex>(g, s, st); }
 
 }  // namespace ozimmu

@@ -9,21 +9,27 @@ namespace ozimmu {
 namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
-typedef long long v2l __attribute__((ext_vector_type(2)));
 
 // Workgroup -> tile. Hardware deals workgroups round-robin over the 8 XCDs (each with its own
 // L2); give every XCD a contiguous run of tiles, ordered in column panels 8 tiles tall so that
 // the 32 workgroups resident on an XCD (8 x 4 tiles) share A and B panels through that L2.
+// (group = logical / (8 tiles_n): a float quotient, corrected; an integer division is ten times the instructions.)
 __device__ __forceinline__ void tile_of_logical(int logical, int tiles_m, int tiles_n, int& tm, int& tn) {
     constexpr int GM = 8;
     const int per_group = GM * tiles_n;
-    const int group = logical / per_group;
+    int group = __builtin_amdgcn_readfirstlane((int)((float)logical * __builtin_amdgcn_rcpf((float)per_group)));
+    while (group * per_group > logical) --group;
+    while ((group + 1) * per_group <= logical) ++group;
     const int first_m = group * GM;
     const int rows = (tiles_m - first_m) < GM ? (tiles_m - first_m) : GM;
     const int in_group = logical - group * per_group;
-    tm = first_m + in_group % rows;
-    tn = in_group / rows;
+    if (rows == GM) {
+        tm = first_m + in_group % GM;
+        tn = in_group / GM;
+    } else {
+        tm = first_m + in_group % rows;
+        tn = in_group / rows;
+    }
 }
 // XCD x owns the logical tiles [first, first + count): the total is dealt out in eight nearly equal runs.
 __device__ __forceinline__ void xcd_tile_range(int xcd, int total, int& first, int& count) {
@@ -86,32 +92,20 @@ __device__ __forceinline__ void mfma_results_ready() {
 }
 
 // One wavefront-wide direct load: lane i fetches 16 bytes from gbase + voff_i and the hardware
-// writes them to LDS at lds_addr + 16 i (M0 carries the LDS base). Issued as inline assembly so
-// that its completion is awaited only by the explicit vmcnt before the step barrier and not
-// before every LDS read in between.
+// writes them to LDS at lds_addr + IMM + 16 i (M0 carries the LDS base). Issued as inline assembly so
+// that its completion is awaited only by the explicit vmcnt before a step's barrier and not
+// before every LDS read in between. gbase and lds_addr are wave-uniform. (The wait states: one between the write of M0
+// and the load, five between a vector instruction that wrote gbase, as a reload of a spilled scalar register does, and the
+// load that reads it; the compiler does not see into the assembly.)
+template <unsigned IMM>
 __device__ __forceinline__ void dma_load16(const void* gbase, unsigned voff, unsigned lds_addr) {
-    // both are wave-uniform by construction; should the register allocator have parked one of them in a
-    // vector register, this brings it back into a scalar one (it costs nothing otherwise)
-    const unsigned long long gb = (unsigned long long)gbase;
-    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)gb);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(gb >> 32));
-    const void* gs = (const void*)(((unsigned long long)hi << 32) | lo);
-    const unsigned la = (unsigned)__builtin_amdgcn_readfirstlane((int)lds_addr);
     asm volatile(
-        "s_mov_b32 m0, %2\n\t"
-        "s_nop 0\n\t"
+        "s_add_u32 m0, %2, %3\n\t"
+        "s_nop 4\n\t"
         "global_load_lds_dwordx4 %1, %0"
         :
-        : "s"(gs), "v"(voff), "s"(la)
-        : "memory");  // M0 is written here (the compiler refuses it as a clobber: reserved register); the build
-                      // checks the generated assembly for any other use of M0 in the kernels
-}
-
-// Wait until at most N of this wave's direct loads are outstanding (they return in order, so
-// everything older has landed) and until its own LDS reads are done, then meet the other waves.
-template <int N>
-__device__ __forceinline__ void wait_loads_and_barrier() {
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(N) : "memory");
+        : "s"(gbase), "v"(voff), "s"(lds_addr), "n"(IMM)
+        : "memory", "scc");
 }
 
 // Compile-time loop: f(integral_constant<int, I>) for I = BEGIN .. END - 1.
@@ -123,22 +117,51 @@ __device__ __forceinline__ void static_for(F&& f) {
     }
 }
 
-__device__ __forceinline__ v16i mfma(const v4i& a, const v4i& b, const v16i& c) {
-    return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
+// 16 rows x 16 columns x 64 positions of k: 4 registers of sums per lane.
+__device__ __forceinline__ v4i mfma16(const v4i& a, const v4i& b, const v4i& c) {
+    return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0);
+}
+// The same added into accumulation registers in place. As a builtin the small shape leaves the compiler free to write
+// its result to other registers than the addend's, and with all accumulation registers taken that ends in copies and
+// spills inside the k-walk. The compiler does not know what the instruction in the assembly needs: its operands must not
+// have been written by vector instructions just before (valu_results_ready()), and its results are read behind
+// mfma_results_ready() only.
+__device__ __forceinline__ void mfma16_acc(const v4i& a, const v4i& b, v4i& c) {
+    asm("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+}
+// The same with a direct load (dma_load16 below) issued in the shadow of the MFMA, which with the wait states behind it
+// stands between the writes of M0 and of src and the load. Completion is awaited by an explicit vmcnt only. (M0 is written here; the compiler refuses it as a clobber. The build checks the generated assembly
+// for any other use of M0 in these kernels.)
+template <unsigned IMM>
+__device__ __forceinline__ void mfma16_acc_and_load(const v4i& a, const v4i& b, v4i& c, const void* src, unsigned voff, unsigned lds_addr) {
+    asm volatile(
+        "s_add_u32 m0, %4, %5\n\t"
+        "v_mfma_i32_16x16x64_i8 %0, %1, %2, %0\n\t"
+        "s_nop 2\n\t"
+        "global_load_lds_dwordx4 %3, %6"
+        : "+a"(c)
+        : "v"(a), "v"(b), "v"(voff), "s"(lds_addr), "n"(IMM), "s"(src)
+        : "memory", "scc");
+}
+// Wait states between vector instructions that wrote operands or sums (two are asked for) and the MFMAs that read them.
+__device__ __forceinline__ void valu_results_ready() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 3" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 // acc = RN(acc + S_e 2^(-7 (e + 2))) for the diagonals of a band, least significant first. The
 // product of an integer below 2^31 and a power of two is exact, so the fused operation rounds
 // exactly like the sum it stands for.
 template <int SB>
-__device__ __forceinline__ void fold_band(double (&sum)[16], const v16i (&acc)[kBand]) {
+__device__ __forceinline__ void fold_band(double (&sum)[16], const v4i (&acc)[kBand][4]) {
     constexpr int ND = SB < kBand ? SB : kBand, E0 = SB - ND;
     mfma_results_ready();
 #pragma unroll
     for (int e = SB - 1; e >= E0; --e) {
         const double sc = __longlong_as_double((long long)(1023 - OZIMMU_SLICE_BITS * (e + 2)) << 52);
 #pragma unroll
-        for (int u = 0; u < 16; ++u) sum[u] = fma((double)acc_read(acc[e - E0][u]), sc, sum[u]);
+        for (int u = 0; u < 16; ++u) sum[u] = fma((double)acc_read(acc[e - E0][u >> 2][u & 3]), sc, sum[u]);
         __builtin_amdgcn_sched_barrier(0);   // one diagonal's temporaries at a time
     }
 }

@@ -34,6 +34,8 @@ static inline bool use_small_tiles(int64_t m, int64_t n, int64_t k_pad, int s, b
     return k_pad <= 512 || big_tiles < 256;
 }
 
+constexpr int kComputeUnits = 256;            // MI355X
+
 // Arguments of the slice-product kernel. One launch covers every tile of C.
 struct GemmArgs {
     const int8_t* SA;        // slice tensor of A   (fragment layout, see ozimmu.h)
@@ -45,6 +47,9 @@ struct GemmArgs {
     int tiles_m, tiles_n;
     int tile_cols;           // 128, or 64 (2 x 2 wavefronts)
     int m, n;                // true extent of C
+    int splits;              // workgroups per tile, each with split_slabs slabs of the walk (1: one, the whole walk)
+    int split_slabs;         // (even)
+    int* partial;            // splits > 1: their INT32 sums, [split][slice count][tile][16][threads of a tile]
     int block_steps;         // steps after which the INT32 sums are moved into the INT64 sums in D (0: never)
     long long* D;            // INT64 diagonal sums (k-blocking only)
     int32_t* P;              // pair mode (P != nullptr): raw INT32 product of the slices SA, SB point at
@@ -102,10 +107,21 @@ hipError_t launch_gate_product(const double* Z, int64_t ldz, int64_t m, int64_t 
 // Counting while splitting (the check of s as the automatic slice count, Section 4.4): scan_slots, if not null, is a
 // zeroed array of scan_slots_bytes(planes of the operand) bytes; the splitter adds, per plane, five counters into one
 // of its slots (scan_nc counters to a slot: 5 per plane of the operand; a one-plane launcher is handed the pointer to
-// its plane's five), and launch_scan_reduce turns them into the bits lost with s and with s - 1 slices:
+// its plane's five), and launch_scan_reduce turns those of both operands (the second's slots behind the first's) into the bits lost with s and
+// with s - 1 slices:
 // out[plane * 16 + s - 1], out[plane * 16 + s - 2] (device or mapped host memory).
 size_t scan_slots_bytes(int planes);
-hipError_t launch_scan_reduce(const unsigned long long* slots, int planes, int s, unsigned long long* out, hipStream_t st);
+// One operand of a product, to be split: `count` vectors of length k, the rows of a stored row-major array or its columns
+// (leading dimension ld), complex elements interleaved (one or two planes of slices and exponents).
+struct SplitOperand {
+    const double* X;
+    int64_t ld, count, padded;   // padded: vectors of its slice tensor
+    bool by_cols, negate_im;     // negate_im: the slices of -Im (a conjugated operand)
+    int8_t* S[2];
+    int32_t* E[2];
+};
+hipError_t launch_scan_reduce(const unsigned long long* slots, int planes, int s, unsigned long long* out_first,
+                              unsigned long long* out_second, hipStream_t st);
 hipError_t launch_split_rows(const double* A, int64_t lda, int inc, int64_t m, int64_t k, int s,
                              int8_t* S, int64_t m_pad, int64_t k_pad, int32_t* E, hipStream_t st,
                              bool negate = false, unsigned long long* scan_slots = nullptr, int scan_nc = 5);

@@ -259,9 +259,12 @@ __global__ __launch_bounds__(256) void col_max_kernel(const double* __restrict__
     const int64_t l1 = l0 + band < k ? l0 + band : k;
     const unsigned long long* src = reinterpret_cast<const unsigned long long*>(B);
     unsigned long long mx = 0;
-    for (int64_t l = l0; l < l1; ++l) {
-        unsigned long long b = src[(l * ldb + j) * inc] & kAbsMask;
-        mx = b > mx ? b : mx;
+    for (int64_t l = l0; l < l1; l += 8) {   // eight loads in flight (past the end the last row again)
+        unsigned long long b[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) b[u] = src[((l + u < l1 ? l + u : l1 - 1) * ldb + j) * inc] & kAbsMask;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) mx = b[u] > mx ? b[u] : mx;
     }
     if (mx) atomicMax(&colmax[j], mx);
 }
@@ -362,26 +365,33 @@ __global__ __launch_bounds__(256) void split_cols_kernel(const double* __restric
     if constexpr (SCAN) scan_flush(cnt, scan_lds, scan);
 }
 
-// The slots of a counting splitter -> the bits each of the operand's planes loses with s and with s - 1 slices:
-// out[plane * 16 + s - 1] and out[plane * 16 + s - 2] (the layout of the slice-count sums; `out` may be mapped host
-// memory). One workgroup of 256 threads.
-__global__ __launch_bounds__(256) void scan_reduce_kernel(const unsigned long long* __restrict__ slots, int nc, int s,
-                                                          unsigned long long* __restrict__ out) {
-    __shared__ unsigned long long sums[2 * kScanCounters];
-    if (threadIdx.x < 2 * kScanCounters) sums[threadIdx.x] = 0ull;
-    __syncthreads();
-    for (int i = 0; i < nc; ++i) {
-        unsigned long long v = 0;
-        for (int t = threadIdx.x; t < kScanSlots; t += 256) v += slots[(size_t)t * nc + i];
+// The slots of the counting splitters of both operands (the second's behind the first's) -> the bits each of an operand's
+// planes loses with s and with s - 1 slices: out[plane * 16 + s - 1] and out[plane * 16 + s - 2] (the layout of the
+// slice-count sums; `out` may be mapped host memory). One workgroup, a wavefront to a counter, all its loads in flight:
+// one counter after the other took 9 us per operand.
+__global__ __launch_bounds__(1024) void scan_reduce_kernel(const unsigned long long* __restrict__ slots, int nc, int s,
+                                                           unsigned long long* __restrict__ out_first, unsigned long long* __restrict__ out_second) {
+    __shared__ unsigned long long sums[2][2 * kScanCounters];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int c = wave; c < 2 * nc; c += 16) {
+        const int o = c / nc, i = c % nc;
+        const unsigned long long* src = slots + (size_t)o * kScanSlots * nc + i;
+        unsigned long long x[kScanSlots / 64], v = 0;
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-        if ((threadIdx.x & 63) == 0 && v) atomicAdd(&sums[i], v);
+        for (int t = 0; t < kScanSlots / 64; ++t) x[t] = src[(size_t)(t * 64 + lane) * nc];
+#pragma unroll
+        for (int t = 0; t < kScanSlots / 64; ++t) v += x[t];
+        v = wave_sum(v);
+        if (lane == 0) sums[o][i] = v;
     }
     __syncthreads();
-    if ((int)threadIdx.x < nc / kScanCounters) {
-        const unsigned long long* c = sums + threadIdx.x * kScanCounters;
-        out[threadIdx.x * OZIMMU_MAX_SLICES + s - 1] = (c[0] - c[1] + c[4]) >> 1;
-        if (s > 1) out[threadIdx.x * OZIMMU_MAX_SLICES + s - 2] = (c[2] - c[3] + c[4]) >> 1;
+    const int planes = nc / kScanCounters;
+    if ((int)threadIdx.x < 2 * planes) {
+        const int o = threadIdx.x / planes, pl = threadIdx.x % planes;
+        const unsigned long long* c = sums[o] + pl * kScanCounters;
+        unsigned long long* out = (o ? out_second : out_first) + pl * OZIMMU_MAX_SLICES;
+        out[s - 1] = (c[0] - c[1] + c[4]) >> 1;
+        if (s > 1) out[s - 2] = (c[2] - c[3] + c[4]) >> 1;
     }
 }
 
@@ -807,8 +817,9 @@ static ScanTarget scan_target(unsigned long long* slots, int nc, int s) {
 
 size_t scan_slots_bytes(int planes) { return (size_t)kScanSlots * kScanCounters * planes * sizeof(unsigned long long); }
 
-hipError_t launch_scan_reduce(const unsigned long long* slots, int planes, int s, unsigned long long* out, hipStream_t st) {
-    scan_reduce_kernel<<<dim3(1), dim3(256), 0, st>>>(slots, kScanCounters * planes, s, out);
+hipError_t launch_scan_reduce(const unsigned long long* slots, int planes, int s, unsigned long long* out_first, unsigned long long* out_second,
+                              hipStream_t st) {
+    scan_reduce_kernel<<<dim3(1), dim3(1024), 0, st>>>(slots, kScanCounters * planes, s, out_first, out_second);
     return hipGetLastError();
 }
 

@@ -153,5 +153,21 @@ __device__ __forceinline__ unsigned row_sum_step(unsigned x) {
     return x + (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x120 + N, 0xf, 0xf, false);
 }
 
+// Sum over the wavefront of values below 2^50, in two 32-bit parts by rotations inside the rows of 16 lanes (a 64-bit
+// shuffle reduction is twelve trips through the LDS crossbar).
+__device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
+    unsigned part[2] = {(unsigned)v & 0xffffffu, (unsigned)(v >> 24)};
+    unsigned long long total = 0;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const unsigned r = row_sum_step<1>(row_sum_step<2>(row_sum_step<4>(row_sum_step<8>(part[i]))));
+        unsigned long long t = 0;
+#pragma unroll
+        for (int l = 0; l < 64; l += 16) t += (unsigned)__builtin_amdgcn_readlane((int)r, l);
+        total += t << (24 * i);
+    }
+    return total;
+}
+
 }  // namespace
 }  // namespace ozimmu
