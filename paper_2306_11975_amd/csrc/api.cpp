@@ -182,6 +182,8 @@ hipError_t split_operands(const Layout& L, bool cplx, const Stored& a, const Sto
             x[o].E[p] = reinterpret_cast<int32_t*>(ws + (o ? L.off_eb : L.off_ea)[p]);
         }
     }
+    if (split_pair_applies(x[0], x[1], planes, L.k_pad, sums_a != nullptr))
+        return launch_split_pair(x[0], x[1], planes, k, L.k_pad, s, st, sums_a ? reinterpret_cast<unsigned*>(ws + L.off_scan) : nullptr, sums_a, sums_b);
     hipError_t e = hipSuccess;
     if (sums_a) {
         slots[0] = reinterpret_cast<unsigned long long*>(ws + L.off_scan);
@@ -196,6 +198,8 @@ hipError_t split_operands(const Layout& L, bool cplx, const Stored& a, const Sto
             e = split_complex_rows(y.X, y.ld, y.count, k, s, ws, o ? L.off_sb : L.off_sa, o ? L.off_eb : L.off_ea, y.padded, L.k_pad, st, y.negate_im, slots[o]);
         else if (y.by_cols)
             e = launch_split_cols(y.X, y.ld, 1, k, y.count, s, y.S[0], y.padded, L.k_pad, y.E[0], colmax, st, false, slots[o], 5);
+        else if (split_rows_in_pieces(y.padded, L.k_pad))
+            e = launch_split_rows_pieces(y.X, y.ld, y.count, k, s, y.S[0], y.padded, L.k_pad, y.E[0], colmax, st, slots[o]);
         else
             e = launch_split_rows(y.X, y.ld, 1, y.count, k, s, y.S[0], y.padded, L.k_pad, y.E[0], st, false, slots[o], 5);
     }

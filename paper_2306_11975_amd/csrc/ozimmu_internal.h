@@ -120,11 +120,21 @@ struct SplitOperand {
     int8_t* S[2];
     int32_t* E[2];
 };
+// Whether one launch splits both operands (split_pair_kernel), and the launch. partials (optional; 2 scan_slots_bytes(planes)
+// bytes, need not be cleared): it also counts, and the bits the planes lose with s and with s - 1 slices arrive in sums_a
+// and sums_b ([planes][16]; device or mapped host memory).
+bool split_pair_applies(const SplitOperand& a, const SplitOperand& b, int planes, int64_t k_pad, bool counting);
+hipError_t launch_split_pair(const SplitOperand& a, const SplitOperand& b, int planes, int64_t k, int64_t k_pad, int s, hipStream_t st,
+                             unsigned* partials, unsigned long long* sums_a, unsigned long long* sums_b);
 hipError_t launch_scan_reduce(const unsigned long long* slots, int planes, int s, unsigned long long* out_first,
                               unsigned long long* out_second, hipStream_t st);
 hipError_t launch_split_rows(const double* A, int64_t lda, int inc, int64_t m, int64_t k, int s,
                              int8_t* S, int64_t m_pad, int64_t k_pad, int32_t* E, hipStream_t st,
                              bool negate = false, unsigned long long* scan_slots = nullptr, int scan_nc = 5);
+// The same for few and long rows of a real operand, where split_rows_in_pieces says so. rowmax: m_pad entries of scratch.
+bool split_rows_in_pieces(int64_t m_pad, int64_t k_pad);
+hipError_t launch_split_rows_pieces(const double* A, int64_t lda, int64_t m, int64_t k, int s, int8_t* S, int64_t m_pad, int64_t k_pad,
+                                    int32_t* E, unsigned long long* rowmax, hipStream_t st, unsigned long long* scan_slots = nullptr);
 hipError_t launch_split_cols(const double* B, int64_t ldb, int inc, int64_t k, int64_t n, int s,
                              int8_t* S, int64_t n_pad, int64_t k_pad, int32_t* E,
                              unsigned long long* colmax, hipStream_t st, bool negate = false,

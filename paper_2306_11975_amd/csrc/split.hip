@@ -141,6 +141,60 @@ __global__ __launch_bounds__(64 * kRowWavesMax) void split_rows_kernel(const dou
     if constexpr (SCAN) scan_flush(cnt, scan_lds, scan);
 }
 
+// Few and long rows (longer than the register cache, fewer row groups than fill the chip): the maxima first, by workgroups
+// that take four rows and a piece of k each, then the emission the same way; the array is read twice either way.
+// 128 x 65536 at eight slices: 141 -> 25 us.
+constexpr int kRowPiece = 2048;   // positions of k: 256 threads, a quarter of a wavefront to a row, eight words each
+template <bool VEC>
+__global__ __launch_bounds__(256) void row_max_kernel(const double* __restrict__ A, int64_t lda, int m, int64_t k, unsigned long long* __restrict__ rowmax) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int row = blockIdx.x * kRowGroup + (lane >> 4);
+    if (row >= m) return;   // (the lanes of one row leave together)
+    const unsigned long long* src = reinterpret_cast<const unsigned long long*>(A) + (int64_t)row * lda;
+    unsigned long long mx = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int64_t l0 = (int64_t)blockIdx.y * kRowPiece + ((wave + 4 * j) * 16 + (lane & 15)) * 4;
+        unsigned long long b[4] = {};
+        if (l0 < k) load_word<VEC>(src, l0, k, 1, b);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) mx = (b[u] & kAbsMask) > mx ? b[u] & kAbsMask : mx;
+    }
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) {
+        const unsigned long long o = __shfl_xor(mx, off, 64);
+        mx = o > mx ? o : mx;
+    }
+    if ((lane & 15) == 0 && mx) atomicMax(&rowmax[row], mx);
+}
+template <bool WIDE, bool VEC, bool SCAN>
+__global__ __launch_bounds__(256) void split_rows_piece_kernel(const double* __restrict__ A, int64_t lda, int m, int64_t k, int s,
+                                                               int8_t* __restrict__ S, int64_t m_pad, int64_t k_pad, int32_t* __restrict__ Eout,
+                                                               const unsigned long long* __restrict__ rowmax, ScanTarget scan) {
+    __shared__ unsigned scan_lds[SCAN ? kScanCounters : 1];
+    if (SCAN && threadIdx.x < kScanCounters) scan_lds[threadIdx.x] = 0u;
+    if (SCAN) __syncthreads();
+    ScanCount cnt = {};
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int row = blockIdx.x * kRowGroup + (lane >> 4);
+    const bool live = row < m;
+    const unsigned long long* src = reinterpret_cast<const unsigned long long*>(A) + (int64_t)(live ? row : 0) * lda;
+    const int E = live ? exponent_of_max(rowmax[row]) : 0;
+    if (live && blockIdx.y == 0 && wave == 0 && (lane & 15) == 0) Eout[row] = E;
+    const int64_t k_live = live ? k : 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int64_t l0 = (int64_t)blockIdx.y * kRowPiece + ((wave + 4 * j) * 16 + (lane & 15)) * 4;
+        if (l0 < k_pad) {
+            unsigned long long b[4];
+            load_word<VEC>(src, l0, k_live, 1, b);
+            emit_word<WIDE>(b, E, s, S + word_offset(row, l0, k_pad), m_pad * k_pad, 0ull);
+            if constexpr (SCAN) scan_count4(cnt, b, E, scan.edge_g, scan.edge_h);
+        }
+    }
+    if constexpr (SCAN) scan_flush(cnt, scan_lds, scan);
+}
+
 // Rows of an interleaved complex operand, both planes in one pass: the same mapping as above, a thread's
 // word being four consecutive complex elements (four 16-byte loads), whose real parts go to one set of
 // slices and exponents and whose imaginary parts to the other. Read once (a pass per plane with element
@@ -363,6 +417,201 @@ __global__ __launch_bounds__(256) void split_cols_kernel(const double* __restric
         __syncthreads();
     }
     if constexpr (SCAN) scan_flush(cnt, scan_lds, scan);
+}
+
+// ------------------------------------------------------------------------------ both operands in one launch
+// Operands with short vectors (k up to 2048; complex 1024): one launch splits both, whichever way each is stored, and
+// reads either once. A workgroup takes four vectors stored as rows (as in the row splitters) or sixteen stored as
+// columns (16 lanes side by side are a full line of a row of the array; a thread owns words of four consecutive positions
+// of one column); every element waits in registers between the maximum and the emission, so the columns need no pass for
+// their maxima. What bounds these sizes is the number of dependent launches: at 64 x 64 x 64 the four launches this replaces
+// (row splitter, cleared maxima, column maxima, column splitter) took 14 us one after the other, this one 4.
+constexpr int kPairColumns = 16;
+struct SplitSide {
+    const double* X;           // real plane (an imaginary one is interleaved with it)
+    int64_t ld;                // of the stored array, in elements (complex: complex elements)
+    int64_t count;             // vectors: m or n
+    int8_t* S[2];              // slices and exponents per plane
+    int32_t* E[2];
+    int64_t slice_stride;      // padded vectors times padded k
+    unsigned long long flip;   // sign bit: the slices of the conjugated operand's imaginary plane
+    int by_cols, vec;
+    unsigned blocks;           // workgroups
+};
+
+// PL planes (2: interleaved complex), J words of four positions per thread of a column, R per thread of a row.
+template <bool WIDE, bool SCAN, int PL, int J>
+__global__ __launch_bounds__(64 * kRowWavesMax) void split_pair_kernel(const SplitSide first, const SplitSide second, int k, int k_pad, int s,
+                                                                       unsigned* __restrict__ partials, uint32_t edge_g, uint32_t edge_h) {
+    constexpr int R = J > 4 ? J / 4 : 1;
+    const bool is_first = blockIdx.x < first.blocks;
+    const SplitSide& side = is_first ? first : second;
+    const int64_t block = is_first ? blockIdx.x : blockIdx.x - first.blocks;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nwaves = blockDim.x >> 6;
+    const bool by_cols = side.by_cols;
+    // the thread's vector, its index among the block's, and its first word; words of one vector are `step` apart (a column's
+    // follow each other: sixteen positions are one 16-byte store per slice)
+    const int sub = by_cols ? tid & 15 : lane >> 4;
+    const int word0 = by_cols ? (tid >> 4) * J : wave * 16 + (lane & 15), step = by_cols ? 1 : nwaves * 16;
+    const int words = by_cols ? J : R;
+    const int64_t vec = block * (by_cols ? kPairColumns : kRowGroup) + sub;
+    const bool live = vec < side.count;
+    const unsigned long long* src = reinterpret_cast<const unsigned long long*>(side.X) + PL * (live ? (by_cols ? vec : vec * side.ld) : 0);
+    const int64_t inc = PL * (by_cols ? side.ld : 1);   // from one position to the next
+
+    unsigned long long v[PL][J][4];
+    unsigned long long mx[PL] = {};
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        if (PL == 1 && side.vec) {   // rows, 16-byte aligned: two loads to a word
+            const int l0 = (word0 + step * j) * 4;
+            if (live && j < words && l0 + 4 <= k) {
+                const ulonglong2 x = *reinterpret_cast<const ulonglong2*>(src + l0), y = *reinterpret_cast<const ulonglong2*>(src + l0 + 2);
+                v[0][j][0] = x.x; v[0][j][1] = x.y; v[0][j][2] = y.x; v[0][j][3] = y.y;
+                continue;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int l = (word0 + step * j) * 4 + u;
+            const bool in = live && j < words && l < k;
+            if constexpr (PL == 2) {
+                ulonglong2 x = {0ull, 0ull};
+                if (in) x = *reinterpret_cast<const ulonglong2*>(src + l * inc);
+                v[0][j][u] = x.x;
+                v[PL - 1][j][u] = x.y;
+            } else {
+                v[0][j][u] = in ? src[l * inc] : 0ull;
+            }
+        }
+    }
+#pragma unroll
+    for (int pl = 0; pl < PL; ++pl)
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const unsigned long long a = v[pl][j][u] & kAbsMask;
+                mx[pl] = a > mx[pl] ? a : mx[pl];
+            }
+    __shared__ unsigned long long wmax[PL][kRowWavesMax][kPairColumns];
+    __shared__ unsigned counts[PL * kScanCounters][SCAN ? kRowWavesMax : 1];
+#pragma unroll
+    for (int pl = 0; pl < PL; ++pl) {
+        // lanes of one vector: the low four bits of the lane number differ (rows), or the high two (columns)
+#pragma unroll
+        for (int off = 1; off <= 32; off <<= 1) {
+            const unsigned long long o = __shfl_xor(mx[pl], off, 64);
+            if ((off >= 16) == by_cols) mx[pl] = o > mx[pl] ? o : mx[pl];
+        }
+        if (by_cols ? lane < 16 : (lane & 15) == 0) wmax[pl][wave][sub] = mx[pl];
+    }
+    __syncthreads();
+    int E[PL];
+#pragma unroll
+    for (int pl = 0; pl < PL; ++pl) {
+        unsigned long long m = wmax[pl][0][sub];
+        for (int w = 1; w < nwaves; ++w) m = wmax[pl][w][sub] > m ? wmax[pl][w][sub] : m;
+        E[pl] = exponent_of_max(m);
+        if (live && word0 == 0) side.E[pl][vec] = E[pl];
+    }
+    ScanCount cnt[PL] = {};
+    if (by_cols) {
+#pragma unroll
+        for (int pl = 0; pl < PL; ++pl)
+#pragma unroll
+            for (int j0 = 0; j0 < J; j0 += 4) {
+                const int l0 = (word0 + j0) * 4;
+                Fixed x[4][4];
+                SignMask sm[4];
+                const unsigned long long flip = pl ? side.flip : 0ull;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const unsigned long long(&w)[4] = v[pl][j0 + j];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) x[j][u] = to_fixed<WIDE>(w[u], E[pl]);
+                    sm[j] = sign_mask(w[0] ^ flip, w[1] ^ flip, w[2] ^ flip, w[3] ^ flip);
+                    if constexpr (SCAN) scan_count4(cnt[pl], w, E[pl], edge_g, edge_h);
+                }
+                if (l0 < k_pad) {
+                    int8_t* dst = side.S[pl] + word_offset(vec, l0, k_pad);
+#pragma unroll
+                    for (int p = 1; p <= (WIDE ? OZIMMU_MAX_SLICES : 9); ++p) {
+                        if (p <= s) {
+                            const uint4 y = {packed_slice<WIDE>(x[0], sm[0], p), packed_slice<WIDE>(x[1], sm[1], p),
+                                             packed_slice<WIDE>(x[2], sm[2], p), packed_slice<WIDE>(x[3], sm[3], p)};
+                            *reinterpret_cast<uint4*>(dst + (p - 1) * side.slice_stride) = y;
+                        }
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);   // one group's temporaries at a time
+            }
+    } else {
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int l0 = (word0 + step * j) * 4;
+#pragma unroll
+            for (int pl = 0; pl < PL; ++pl) {
+                if (l0 < k_pad) emit_word<WIDE>(v[pl][j], E[pl], s, side.S[pl] + word_offset(vec, l0, k_pad), side.slice_stride, pl ? side.flip : 0ull);
+                if constexpr (SCAN) scan_count4(cnt[pl], v[pl][j], E[pl], edge_g, edge_h);
+                __builtin_amdgcn_sched_barrier(0);   // one word's temporaries at a time
+            }
+        }
+    }
+    if constexpr (SCAN) {
+        // this workgroup's counters, [counter][workgroup]: nothing to clear, nothing to add up atomically
+#pragma unroll
+        for (int pl = 0; pl < PL; ++pl) {
+            unsigned c[kScanCounters] = {cnt[pl].sv_g, cnt[pl].sz_g, cnt[pl].sv_h, cnt[pl].sz_h, cnt[pl].bits};
+#pragma unroll
+            for (int i = 0; i < kScanCounters; ++i) {
+#pragma unroll
+                for (int off = 32; off >= 1; off >>= 1) c[i] += __shfl_xor(c[i], off, 64);
+                if (lane == 0) counts[pl * kScanCounters + i][wave] = c[i];
+            }
+        }
+        __syncthreads();
+        if (tid < PL * kScanCounters) {
+            unsigned total = 0;
+            for (int w = 0; w < nwaves; ++w) total += counts[tid][w];
+            partials[(size_t)tid * gridDim.x + blockIdx.x] = total;
+        }
+    }
+}
+
+// Those counters -> the bits each plane of an operand loses with s and with s - 1 slices: out[plane * 16 + s - 1] and
+// out[plane * 16 + s - 2] (`out` may be mapped host memory). One workgroup.
+__global__ __launch_bounds__(1024) void split_pair_reduce_kernel(const unsigned* __restrict__ partials, unsigned blocks_first, unsigned blocks,
+                                                                 int planes, int s, unsigned long long* __restrict__ out_first,
+                                                                 unsigned long long* __restrict__ out_second) {
+    __shared__ unsigned long long sums[2][2 * kScanCounters];
+    if (threadIdx.x < 4 * kScanCounters) (&sums[0][0])[threadIdx.x] = 0ull;
+    __syncthreads();
+    const int nc = planes * kScanCounters;
+    unsigned long long mine[2][2 * kScanCounters] = {};
+    for (unsigned b = threadIdx.x; b < blocks; b += 1024) {
+#pragma unroll
+        for (int i = 0; i < 2 * kScanCounters; ++i) {
+            const unsigned c = i < nc ? partials[(size_t)i * blocks + b] : 0u;
+            mine[0][i] += b < blocks_first ? c : 0u;
+            mine[1][i] += b < blocks_first ? 0u : c;
+        }
+    }
+#pragma unroll
+    for (int o = 0; o < 2; ++o)
+#pragma unroll
+        for (int i = 0; i < 2 * kScanCounters; ++i) {
+            const unsigned long long v = wave_sum(mine[o][i]);
+            if ((threadIdx.x & 63) == 0 && v) atomicAdd(&sums[o][i], v);
+        }
+    __syncthreads();
+    if ((int)threadIdx.x < 2 * planes) {
+        const int o = threadIdx.x / planes, pl = threadIdx.x % planes;
+        const unsigned long long* c = sums[o] + pl * kScanCounters;
+        unsigned long long* out = (o ? out_second : out_first) + pl * OZIMMU_MAX_SLICES;
+        out[s - 1] = (c[0] - c[1] + c[4]) >> 1;
+        if (s > 1) out[s - 2] = (c[2] - c[3] + c[4]) >> 1;
+    }
 }
 
 // The slots of the counting splitters of both operands (the second's behind the first's) -> the bits each of an operand's
@@ -820,6 +1069,79 @@ size_t scan_slots_bytes(int planes) { return (size_t)kScanSlots * kScanCounters 
 hipError_t launch_scan_reduce(const unsigned long long* slots, int planes, int s, unsigned long long* out_first, unsigned long long* out_second,
                               hipStream_t st) {
     scan_reduce_kernel<<<dim3(1), dim3(1024), 0, st>>>(slots, kScanCounters * planes, s, out_first, out_second);
+    return hipGetLastError();
+}
+
+static unsigned pair_blocks(const SplitOperand& x) { return (unsigned)(x.padded / (x.by_cols ? kPairColumns : kRowGroup)); }
+
+bool split_pair_applies(const SplitOperand& a, const SplitOperand& b, int planes, int64_t k_pad, bool counting) {
+    if (k_pad < 1 || k_pad > (planes == 2 ? 1024 : 2048)) return false;
+    if (planes == 2 && ((reinterpret_cast<uintptr_t>(a.X) | reinterpret_cast<uintptr_t>(b.X)) % 16 != 0)) return false;
+    const int64_t blocks = (int64_t)pair_blocks(a) + pair_blocks(b);
+    if (counting && (size_t)blocks * kScanCounters * planes * sizeof(unsigned) > 2 * scan_slots_bytes(planes)) return false;
+    // Operands of more than 32 MiB (real elements) stay with the kernels of their own: there the bytes count, not the launches
+    return (a.padded + b.padded) * k_pad * planes <= (int64_t)4 << 20;
+}
+
+hipError_t launch_split_pair(const SplitOperand& a, const SplitOperand& b, int planes, int64_t k, int64_t k_pad, int s, hipStream_t st,
+                             unsigned* partials, unsigned long long* sums_a, unsigned long long* sums_b) {
+    if (!split_pair_applies(a, b, planes, k_pad, partials != nullptr)) return hipErrorInvalidValue;
+    auto side = [&](const SplitOperand& x) {
+        SplitSide y{};
+        y.X = x.X;
+        y.ld = x.ld;
+        y.count = x.count;
+        for (int p = 0; p < planes; ++p) {
+            y.S[p] = x.S[p];
+            y.E[p] = x.E[p];
+        }
+        y.slice_stride = x.padded * k_pad;
+        y.flip = x.negate_im ? 1ull << 63 : 0ull;
+        y.by_cols = x.by_cols;
+        y.vec = planes == 1 && !x.by_cols && x.ld % 2 == 0 && reinterpret_cast<uintptr_t>(x.X) % 16 == 0;
+        y.blocks = pair_blocks(x);
+        return y;
+    };
+    const SplitSide sa = side(a), sb = side(b);
+    const ScanTarget scan = scan_target(nullptr, 0, s);
+    const bool eight = k_pad > 1024;
+    const dim3 grid(sa.blocks + sb.blocks), block(64 * (eight ? 16 : (unsigned)((k_pad + 63) / 64)));
+#define OZ_PAIR(W, SC, PL, J) split_pair_kernel<W, SC, PL, J><<<grid, block, 0, st>>>(sa, sb, (int)k, (int)k_pad, s, partials, scan.edge_g, scan.edge_h)
+#define OZ_PAIRS(W, SC) do { if (planes == 2) OZ_PAIR(W, SC, 2, 4); else if (eight) OZ_PAIR(W, SC, 1, 8); else OZ_PAIR(W, SC, 1, 4); } while (0)
+    if (s > 9) { if (partials) OZ_PAIRS(true, true); else OZ_PAIRS(true, false); }
+    else       { if (partials) OZ_PAIRS(false, true); else OZ_PAIRS(false, false); }
+#undef OZ_PAIRS
+#undef OZ_PAIR
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess && partials) {
+        split_pair_reduce_kernel<<<dim3(1), dim3(1024), 0, st>>>(partials, sa.blocks, grid.x, planes, s, sums_a, sums_b);
+        e = hipGetLastError();
+    }
+    return e;
+}
+
+bool split_rows_in_pieces(int64_t m_pad, int64_t k_pad) {
+    return k_pad > (int64_t)64 * kRowCacheWords * kRowWavesMax && m_pad / kRowGroup < 1024;
+}
+
+hipError_t launch_split_rows_pieces(const double* A, int64_t lda, int64_t m, int64_t k, int s, int8_t* S, int64_t m_pad, int64_t k_pad,
+                                    int32_t* E, unsigned long long* rowmax, hipStream_t st, unsigned long long* scan_slots) {
+    const ScanTarget scan = scan_target(scan_slots, kScanCounters, s);
+    fill_u64_kernel<<<dim3((unsigned)((m_pad + 255) / 256)), dim3(256), 0, st>>>(rowmax, m_pad, 0ull);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const bool vec = lda % 2 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0;
+    const dim3 grid((unsigned)(m_pad / kRowGroup), (unsigned)((k_pad + kRowPiece - 1) / kRowPiece));
+    if (vec) row_max_kernel<true><<<grid, dim3(256), 0, st>>>(A, lda, (int)m, k, rowmax);
+    else row_max_kernel<false><<<grid, dim3(256), 0, st>>>(A, lda, (int)m, k, rowmax);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+#define OZ_PIECE(W, V, SC) split_rows_piece_kernel<W, V, SC><<<grid, dim3(256), 0, st>>>(A, lda, (int)m, k, s, S, m_pad, k_pad, E, rowmax, scan)
+#define OZ_PIECES(W, V) do { if (scan.slots) OZ_PIECE(W, V, true); else OZ_PIECE(W, V, false); } while (0)
+    if (s > 9) { if (vec) OZ_PIECES(true, true); else OZ_PIECES(true, false); }
+    else       { if (vec) OZ_PIECES(false, true); else OZ_PIECES(false, false); }
+#undef OZ_PIECES
+#undef OZ_PIECE
     return hipGetLastError();
 }
 
