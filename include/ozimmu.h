@@ -122,9 +122,12 @@ ozimmu_status_t ozimmu_slice_gemm(int64_t m, int64_t n, int64_t k, const int8_t*
  * Workspace size for ozimmu_dgemm / ozimmu_zgemm: slices of A and B, exponents, column maxima, and
  * -- only when num_slices * k_padded > OZIMMU_INT32_BLOCK (k-blocking) -- num_slices INT64 sums per
  * element of C. Otherwise every integer sum stays in registers. A complex product adds two m x n FP64
- * planes in which its real and imaginary parts are formed before C is written, once, interleaved,
+ * planes in which its real and imaginary parts are formed when k-blocking makes it four launches,
  * and, with k and n small enough, room for B's slices in the form the kernel wants that splits A on
- * the fly (see ozimmu_zgemm).
+ * the fly (see ozimmu_zgemm). A product with fewer tiles than compute units and a long inner dimension adds
+ * room for the INT32 sums of the workgroups that share a tile's walk along k (in all at most
+ * OZIMMU_STATIC_SCRATCH_BYTES where the rest is below that). That room alone is used if it is there and not
+ * asked for: a call accepts a workspace without it, and gives the same result, more slowly.
  */
 ozimmu_status_t ozimmu_workspace_bytes(int64_t m, int64_t n, int64_t k, int num_slices,
                                        int is_complex, size_t* bytes);
@@ -180,12 +183,12 @@ ozimmu_status_t ozimmu_dgemm_stage(int stage, int64_t m, int64_t n, int64_t k, c
 
 /*
  * How ozimmu_dgemm runs a shape, on the host only (nothing is launched; for tests and for callers
- * who want to know): the tile of C one workgroup owns (64 x 128; 64 x 64 from fourteen slices on, and up to
+ * who want to know): the tile of C one workgroup owns, or shares with others that walk other parts of k (64 x 128; 64 x 64 from fourteen slices on, and up to
  * nine slices when k <= 512 or fewer than 256 of the larger tiles exist), the number of workgroups, the number of bands
  * the anti-diagonals are walked in (a wavefront holds the INT32 sums of at most eight diagonals at a
- * time: 2 bands beyond eight slices), and int32_block_steps = the number of steps of
- * OZIMMU_K_ALIGN positions after which the INT32 sums are moved into INT64 sums (k-blocking),
- * 0 if a whole diagonal fits one INT32 sum.
+ * time: 2 bands beyond eight slices), and int32_block_steps = the largest number of slabs of
+ * OZIMMU_K_ALIGN positions after which the INT32 sums are moved into INT64 sums (k-blocking; the walk takes
+ * two slabs at a time), 0 if a whole diagonal fits one INT32 sum.
  */
 typedef struct {
     int tile_rows, tile_cols;

@@ -43,17 +43,37 @@ constexpr int kGateStep = 64;    // positions of k per MFMA
 // (both operands alike, which is all a sum over k needs); its 16 bytes sit at byte 16 l.
 __device__ __forceinline__ int frag_offset(int row, int pos) { return ((pos >> 4) * 16 + row) * 16 + (pos & 15); }
 
-// to_fixed for a row whose maximum is a normal number (the shift is then never negative) when only the upper 56 bits
-// of the fraction are wanted (eight slices at most): a shift of 64 or more is cut to 63, which leaves nothing there.
-__device__ __forceinline__ Fixed to_fixed_upper(unsigned long long bits, int E) {
-    const unsigned e = (unsigned)(bits >> 52) & 0x7ffu;
-    const unsigned long long mant = bits & kMantMask;
-    const unsigned long long T = (e ? (mant | (1ull << 52)) : mant) << 11;
-    const unsigned z = (unsigned)(E + 1022) - (e ? e : 1u);
-    Fixed f;
-    f.hi = T >> (z < 63u ? z : 63u);
-    f.lo = 0ull;
+// |x| 2^(-E) < 1 to its upper 56 binary places as two words of 28: the scaled number's integer part, then that of the scaled
+// rest (conversion and fraction are exact, truncation is what SplitInt wants, subnormals and zeros need no cases of their own). With
+// integer instructions the same takes two 64-bit shifts and the handling of the exponent field; and FP64 instructions
+// overlap better with the MFMAs of the other wavefronts (6 qubits of 24 201.0 -> 198.8 us, 5 qubits 213 -> 206).
+struct Words28 {
+    unsigned w[2];
+};
+__device__ __forceinline__ Words28 to_words28(unsigned long long bits, int E) {
+    const double y = ldexp(__longlong_as_double((long long)(bits & kAbsMask)), 28 - E);
+    Words28 f;
+    f.w[0] = (unsigned)y;
+    f.w[1] = (unsigned)ldexp(__builtin_amdgcn_fract(y), 28);
     return f;
+}
+// 28 bits to the low seven bits of four bytes, most significant first in the top byte; bit 7 of a byte is left over.
+__device__ __forceinline__ unsigned spread28(unsigned x) {
+    const unsigned y = (x & 0x3fffu) | ((x << 2) & ~0x3fffu);
+    return (y & 0x007f007fu) | ((y << 1) & ~0x007f007fu);
+}
+// Slices 4 g + 1 .. 4 g + 4 of four elements, a slice to a word (element u in byte u), the bytes still to be cut to seven bits.
+__device__ __forceinline__ void slices_of_four(const Words28 (&x)[4], int g, unsigned (&out)[4]) {
+    unsigned e[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) e[u] = spread28(x[u].w[g]);
+    // 4 x 4 bytes transposed: pairs of elements, then pairs of pairs
+    const unsigned a_hi = __builtin_amdgcn_perm(e[1], e[0], 0x07030602u), a_lo = __builtin_amdgcn_perm(e[1], e[0], 0x05010400u);
+    const unsigned b_hi = __builtin_amdgcn_perm(e[3], e[2], 0x07030602u), b_lo = __builtin_amdgcn_perm(e[3], e[2], 0x05010400u);
+    out[0] = __builtin_amdgcn_perm(b_hi, a_hi, 0x07060302u);   // the top bytes: the first of the four slices
+    out[1] = __builtin_amdgcn_perm(b_hi, a_hi, 0x05040100u);
+    out[2] = __builtin_amdgcn_perm(b_lo, a_lo, 0x07060302u);
+    out[3] = __builtin_amdgcn_perm(b_lo, a_lo, 0x05040100u);
 }
 
 // scan_count4 with the edges of a compile-time slice count (no counters for S - 1 = 0 slices)
@@ -165,15 +185,21 @@ __global__ __launch_bounds__(512) void gate_split_kernel(const double* __restric
 // more per tile; up to 64 x 64 a lane takes two words of its row and a wavefront four patches): four such workgroups
 // then share a compute unit up to eight slices, and the latency of a tile's loads and its barrier hide behind three
 // other tiles instead of one.
-constexpr int gate_waves(int cls, int few) { return cls == 2 ? 16 : few ? 4 : 8; }
-template <int S, int CLS, bool SCAN, int FEW = 0>   // FEW: 1 = four wavefronts, k <= 32; 2 = four wavefronts, two words to a lane
+constexpr int gate_waves(int cls, int few) { return cls == 2 ? 16 : few == 3 ? 2 : few ? 4 : 8; }
+// The narrowest gates (k <= 16, n <= 8: up to three qubits) have work for two wavefronts, and a quarter of a fragment's
+// positions: their slices take a quarter of the LDS (the operand's other lanes read the same 16 positions again, and meet
+// the zeros of the gate's fragments), so that eight such workgroups share a compute unit. A tile of so few bytes is all
+// latency, and twice as many in flight take two thirds of the time (2 qubits of 24: 552 -> 360 us).
+// FEW: 1 = four wavefronts, k <= 32; 2 = four wavefronts, two words to a lane; 3 = two wavefronts, k <= 16, n <= 8
+template <int S, int CLS, bool SCAN, int FEW = 0>
 __global__ __launch_bounds__(64 * gate_waves(CLS, FEW)) __attribute__((amdgpu_waves_per_eu(S <= kBand ? 4 : 2, S <= kBand ? 4 : 2)))
 void gate_kernel(const GateArgs g) {
     static_assert(!FEW || CLS == 0, "four wavefronts: the smallest class only");
     constexpr bool WIDE = S > 9;   // the slices beyond the ninth come from the lower word of the fixed-point fraction
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     constexpr int KS = 1 << CLS, NFR = 8 << CLS, WAVES = gate_waves(CLS, FEW), NT = 64 * WAVES;
-    constexpr int SLICE = KS * 2 * kFragBytes;   // one slice of one plane of the tile's rows: [step][row fragment]
+    constexpr int FRAG = FEW == 3 ? kFragBytes / 4 : kFragBytes;
+    constexpr int SLICE = KS * 2 * FRAG;   // one slice of one plane of the tile's rows: [step][row fragment]
     constexpr int PLANE = S * SLICE;
     // behind the two planes: exponents of the tile's rows, [plane][32], then those of the gate's fragments, [tensor][NFR][16]
     int* ex = reinterpret_cast<int*>(lds + 2 * PLANE);
@@ -185,10 +211,10 @@ void gate_kernel(const GateArgs g) {
 
     // ---- this wavefront's patches: rows 16 rf .. + 15 of the tile, complex columns 8 f .. 8 f + 7 for f = cg, cg + WAVES / 2, ...
     const int rf = wave & 1, cg = wave >> 1;
-    const unsigned char* a_rd = lds + rf * kFragBytes + 16 * lane;
+    const unsigned char* a_rd = lds + rf * FRAG + 16 * (FEW == 3 ? lane & 15 : lane);
     constexpr int BSLICE = NFR * KS * kFragBytes, TENSOR = S * BSLICE;
     auto read_a = [&](int plane, int p, int step) __attribute__((always_inline)) -> v4i {
-        return *reinterpret_cast<const v4i*>(a_rd + plane * PLANE + p * SLICE + step * 2 * kFragBytes);
+        return *reinterpret_cast<const v4i*>(a_rd + plane * PLANE + p * SLICE + step * 2 * FRAG);
     };
     // fragments of the gate: a wave-uniform byte offset (tensor, fragment) plus the lane's 16 bytes, unsigned, so that the
     // loads take the tensor's address as their scalar base and a 32-bit register as offset
@@ -212,8 +238,8 @@ void gate_kernel(const GateArgs g) {
     // the others skip this part. The positions of a step beyond those words are never written: the gate's fragments
     // hold zeros there (gate_split_kernel), and an integer times zero is zero whatever the LDS holds.
     for (int i = tid; i < 2 * NFR * 16; i += NT) ex_gate[i] = g.E[i];
-    constexpr int LPR = FEW == 1 ? 16 : NT / kGateRows, W = KS * 16 / LPR;   // (FEW 1: k <= 32, never 16 lanes to a row)
-    const int lshift = FEW == 2 ? 3 : CLS == 0 ? (g.k <= 16 ? 2 : g.k <= 32 ? 3 : 4) : (LPR == 32 ? 5 : 4);   // log2 of the lanes per row
+    constexpr int LPR = FEW == 1 || FEW == 3 ? 16 : NT / kGateRows, W = KS * 16 / LPR;   // (FEW 1, 3: k <= 32, 16, never 16 lanes to a row)
+    const int lshift = FEW == 3 ? 2 : FEW == 2 ? 3 : CLS == 0 ? (g.k <= 16 ? 2 : g.k <= 32 ? 3 : 4) : (LPR == 32 ? 5 : 4);   // log2 of the lanes per row
     if (tid < (kGateRows << lshift)) {   // whole wavefronts
         const int lrow = tid >> lshift, cl = tid & ((1 << lshift) - 1);
         const int64_t row = row_tile + lrow;
@@ -280,20 +306,9 @@ void gate_kernel(const GateArgs g) {
             ex[kGateRows + lrow] = e_im;
         }
         ScanCount cnt_re = {}, cnt_im = {};
-        auto emit = [&](auto normal_tag) __attribute__((always_inline)) {
+        auto emit = [&]() __attribute__((always_inline)) {
 #pragma unroll
             for (int j = 0; j < W; ++j) {
-                Fixed xr[4], xi[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    if constexpr (decltype(normal_tag)::value && S <= kBand) {
-                        xr[u] = to_fixed_upper(v[j][u].x, e_re);
-                        xi[u] = to_fixed_upper(v[j][u].y, e_im);
-                    } else {
-                        xr[u] = to_fixed<WIDE>(v[j][u].x, e_re);
-                        xi[u] = to_fixed<WIDE>(v[j][u].y, e_im);
-                    }
-                }
                 const SignMask sr = sign_mask(v[j][0].x, v[j][1].x, v[j][2].x, v[j][3].x);
                 const SignMask si = sign_mask(v[j][0].y, v[j][1].y, v[j][2].y, v[j][3].y);
                 if constexpr (SCAN) {
@@ -303,17 +318,43 @@ void gate_kernel(const GateArgs g) {
                     scan_count4<S>(cnt_im, im4, e_im);
                 }
                 const int word = cl + LPR * j;   // sixteen words to a step
-                unsigned char* dst = lds + ((word >> 4) * 2 + (lrow >> 4)) * kFragBytes + frag_offset(lrow & 15, (word & 15) * 4);
-                static_for<1, S + 1>([&](auto pc) __attribute__((always_inline)) {
-                    constexpr int p = decltype(pc)::value;
-                    *reinterpret_cast<uint32_t*>(dst + (p - 1) * SLICE) = packed_slice<WIDE>(xr, sr, p);
-                    *reinterpret_cast<uint32_t*>(dst + PLANE + (p - 1) * SLICE) = packed_slice<WIDE>(xi, si, p);
-                });
+                unsigned char* dst = lds + ((word >> 4) * 2 + (lrow >> 4)) * FRAG + frag_offset(lrow & 15, (word & 15) * 4);
+                if constexpr (S <= kBand) {
+#pragma unroll
+                    for (int plane = 0; plane < 2; ++plane) {
+                        Words28 x[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) x[u] = plane ? to_words28(v[j][u].y, e_im) : to_words28(v[j][u].x, e_re);
+#pragma unroll
+                        for (int g4 = 0; g4 < 2; ++g4) {
+                            if (4 * g4 >= S) continue;
+                            unsigned c[4];
+                            slices_of_four(x, g4, c);
+#pragma unroll
+                            for (int q = 0; q < 4; ++q)
+                                if (4 * g4 + q < S)
+                                    *reinterpret_cast<uint32_t*>(dst + plane * PLANE + (4 * g4 + q) * SLICE) =
+                                        apply_sign(c[q] & 0x7f7f7f7fu, plane ? si : sr);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);   // one plane's temporaries at a time
+                    }
+                } else {
+                    Fixed xr[4], xi[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        xr[u] = to_fixed<WIDE>(v[j][u].x, e_re);
+                        xi[u] = to_fixed<WIDE>(v[j][u].y, e_im);
+                    }
+                    static_for<1, S + 1>([&](auto pc) __attribute__((always_inline)) {
+                        constexpr int p = decltype(pc)::value;
+                        *reinterpret_cast<uint32_t*>(dst + (p - 1) * SLICE) = packed_slice<WIDE>(xr, sr, p);
+                        *reinterpret_cast<uint32_t*>(dst + PLANE + (p - 1) * SLICE) = packed_slice<WIDE>(xi, si, p);
+                    });
+                }
                 __builtin_amdgcn_sched_barrier(0);   // one word's temporaries at a time
             }
         };
-        if (normal) emit(std::true_type{});
-        else emit(std::false_type{});
+        emit();
         if constexpr (SCAN) {
             // sums over the wavefront (rotations inside the rows of 16 lanes, then the four rows through scalar registers),
             // one LDS word per wavefront and counter: no atomics, which a tile of few elements would feel
@@ -499,8 +540,8 @@ __global__ __launch_bounds__(1024) void gate_scan_reduce_kernel(const unsigned* 
 
 template <int S, int CLS, bool SCAN, int FEW>
 hipError_t launch_gate(const GateArgs& g, hipStream_t st) {
-    constexpr int lds = 2 * S * (1 << CLS) * 2 * kFragBytes + (2 * kGateRows + 2 * (8 << CLS) * 16 + 16 * 2 * kScanCounters) * (int)sizeof(int);
-    static_assert(lds <= 160 * 1024 && (S > kBand || CLS == 2 || 2 * lds <= 160 * 1024) && (!FEW || S > kBand || 4 * lds <= 160 * 1024),
+    constexpr int lds = 2 * S * (1 << CLS) * 2 * (FEW == 3 ? kFragBytes / 4 : kFragBytes) + (2 * kGateRows + 2 * (8 << CLS) * 16 + 16 * 2 * kScanCounters) * (int)sizeof(int);
+    static_assert(lds <= 160 * 1024 && (S > kBand || CLS == 2 || 2 * lds <= 160 * 1024) && (!FEW || S > kBand || (FEW == 3 ? 8 : 4) * lds <= 160 * 1024),
                   "the LDS of a compute unit: two workgroups of eight wavefronts (four of four) up to eight slices, else one workgroup");
     hipError_t e = allow_dynamic_lds<&gate_kernel<S, CLS, SCAN, FEW>>(lds);
     if (e != hipSuccess) return e;
@@ -511,6 +552,10 @@ hipError_t launch_gate(const GateArgs& g, hipStream_t st) {
 template <int S, int CLS>
 hipError_t launch_gate(const GateArgs& g, hipStream_t st) {
     if constexpr (CLS == 0) {
+        // no more tiles than compute units: eight wavefronts share a tile, whose time is what the call takes (1024 x 64 x 64
+        // 14.2 -> 13.0 us per call); with more tiles four wavefronts each, four tiles to a compute unit, are faster
+        if (g.m <= (int64_t)kGateRows * kComputeUnits) return g.scan ? launch_gate<S, 0, true, 0>(g, st) : launch_gate<S, 0, false, 0>(g, st);
+        if (g.k <= 16 && g.n <= 8) return g.scan ? launch_gate<S, 0, true, 3>(g, st) : launch_gate<S, 0, false, 3>(g, st);
         if (g.k <= 32 && g.n <= 32) return g.scan ? launch_gate<S, 0, true, 1>(g, st) : launch_gate<S, 0, false, 1>(g, st);
         return g.scan ? launch_gate<S, 0, true, 2>(g, st) : launch_gate<S, 0, false, 2>(g, st);
     } else {
