@@ -87,7 +87,7 @@ Layout make_layout(int64_t m, int64_t n, int64_t k, int s, bool cplx) {
 // price of the parts' INT32 sums going through memory and of a kernel that adds and folds them. The line is drawn where
 // the estimate says so: a step of a walk takes what its MFMAs take (64 cycles per pair and wavefront of a SIMD at 2.1 GHz, and no
 // less than the 0.5 us its loads need), a launch more 5 us, the sums 3.5 TB/s. Measured (product and fold, one part against
-// the parts chosen): 1273 x 153 x 8000, 6 slices, 190 -> 45 us; 35 x 154 x 2251, 9 slices, 72 -> 15 us.
+// the parts chosen): 1273 x 153 x 8000, 6 slices, 96 -> 50 us; 35 x 154 x 2251, 9 slices, 69 -> 18 us.
 struct Split {
     int splits;
     int slabs;      // of a part (even)

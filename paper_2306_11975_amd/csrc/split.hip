@@ -143,7 +143,7 @@ __global__ __launch_bounds__(64 * kRowWavesMax) void split_rows_kernel(const dou
 
 // Few and long rows (longer than the register cache, fewer row groups than fill the chip): the maxima first, by workgroups
 // that take four rows and a piece of k each, then the emission the same way; the array is read twice either way.
-// 128 x 65536 at eight slices: 141 -> 25 us.
+// 128 x 65536 at eight slices: 141 -> 42 us (both launches and the cleared maxima).
 constexpr int kRowPiece = 2048;   // positions of k: 256 threads, a quarter of a wavefront to a row, eight words each
 template <bool VEC>
 __global__ __launch_bounds__(256) void row_max_kernel(const double* __restrict__ A, int64_t lda, int m, int64_t k, unsigned long long* __restrict__ rowmax) {
@@ -421,11 +421,14 @@ __global__ __launch_bounds__(256) void split_cols_kernel(const double* __restric
 
 // ------------------------------------------------------------------------------ both operands in one launch
 // Operands with short vectors (k up to 2048; complex 1024): one launch splits both, whichever way each is stored, and
-// reads either once. A workgroup takes four vectors stored as rows (as in the row splitters) or sixteen stored as
-// columns (16 lanes side by side are a full line of a row of the array; a thread owns words of four consecutive positions
-// of one column); every element waits in registers between the maximum and the emission, so the columns need no pass for
+// reads either once. A workgroup takes four vectors stored as rows (as in the row splitters) or sixteen or eight stored as
+// columns (16 lanes side by side are a full line of a row of the array, 8 of complex elements; a thread owns words of four consecutive
+// positions of one column); every element waits in registers between the maximum and the emission, so the columns need no pass for
 // their maxima. What bounds these sizes is the number of dependent launches: at 64 x 64 x 64 the four launches this replaces
-// (row splitter, cleared maxima, column maxima, column splitter) took 14 us one after the other, this one 4.
+// (row splitter, cleared maxima, column maxima, column splitter) took 14.3 us one after the other, this one 5.4.
+// Eight columns where sixteen would leave compute units without a workgroup (1024^3 at nine slices: the launch 19 -> 17 us, the
+// call 54.7 -> 52.6) and where sixteen would not fit the registers (k above 1024). The workgroup that holds the other half of
+// a line is dealt to the same XCD, whose L2 then serves it.
 constexpr int kPairColumns = 16;
 struct SplitSide {
     const double* X;           // real plane (an imaginary one is interleaved with it)
@@ -436,25 +439,29 @@ struct SplitSide {
     int64_t slice_stride;      // padded vectors times padded k
     unsigned long long flip;   // sign bit: the slices of the conjugated operand's imaginary plane
     int by_cols, vec;
+    int col_shift;             // columns to a workgroup, as a power of two: 3 or 4
     unsigned blocks;           // workgroups
 };
 
-// PL planes (2: interleaved complex), J words of four positions per thread of a column, R per thread of a row.
-template <bool WIDE, bool SCAN, int PL, int J>
+// PL planes (2: interleaved complex), four words of four positions per thread of a column, R per thread of a row.
+template <bool WIDE, bool SCAN, int PL, int R>
 __global__ __launch_bounds__(64 * kRowWavesMax) void split_pair_kernel(const SplitSide first, const SplitSide second, int k, int k_pad, int s,
                                                                        unsigned* __restrict__ partials, uint32_t edge_g, uint32_t edge_h) {
-    constexpr int R = J > 4 ? J / 4 : 1;
+    constexpr int J = 4;
     const bool is_first = blockIdx.x < first.blocks;
     const SplitSide& side = is_first ? first : second;
-    const int64_t block = is_first ? blockIdx.x : blockIdx.x - first.blocks;
+    int64_t block = is_first ? blockIdx.x : blockIdx.x - first.blocks;
+    const int cols = 1 << side.col_shift;
+    // consecutive workgroups go to the 8 XCDs in turn: blocks 2i and 2i + 1 change places with ones eight apart
+    if (side.by_cols && cols < kPairColumns && (block | 15) < side.blocks) block = (block & ~15) | (block & 7) << 1 | (block >> 3 & 1);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nwaves = blockDim.x >> 6;
     const bool by_cols = side.by_cols;
     // the thread's vector, its index among the block's, and its first word; words of one vector are `step` apart (a column's
     // follow each other: sixteen positions are one 16-byte store per slice)
-    const int sub = by_cols ? tid & 15 : lane >> 4;
-    const int word0 = by_cols ? (tid >> 4) * J : wave * 16 + (lane & 15), step = by_cols ? 1 : nwaves * 16;
+    const int sub = by_cols ? tid & (cols - 1) : lane >> 4;
+    const int word0 = by_cols ? (tid >> side.col_shift) * J : wave * 16 + (lane & 15), step = by_cols ? 1 : nwaves * 16;
     const int words = by_cols ? J : R;
-    const int64_t vec = block * (by_cols ? kPairColumns : kRowGroup) + sub;
+    const int64_t vec = block * (by_cols ? cols : kRowGroup) + sub;
     const bool live = vec < side.count;
     const unsigned long long* src = reinterpret_cast<const unsigned long long*>(side.X) + PL * (live ? (by_cols ? vec : vec * side.ld) : 0);
     const int64_t inc = PL * (by_cols ? side.ld : 1);   // from one position to the next
@@ -498,13 +505,13 @@ __global__ __launch_bounds__(64 * kRowWavesMax) void split_pair_kernel(const Spl
     __shared__ unsigned counts[PL * kScanCounters][SCAN ? kRowWavesMax : 1];
 #pragma unroll
     for (int pl = 0; pl < PL; ++pl) {
-        // lanes of one vector: the low four bits of the lane number differ (rows), or the high two (columns)
+        // lanes of one vector: the low four bits of the lane number differ (rows), or the high two or three (columns)
 #pragma unroll
         for (int off = 1; off <= 32; off <<= 1) {
             const unsigned long long o = __shfl_xor(mx[pl], off, 64);
-            if ((off >= 16) == by_cols) mx[pl] = o > mx[pl] ? o : mx[pl];
+            if (by_cols ? off >= cols : off < 16) mx[pl] = o > mx[pl] ? o : mx[pl];
         }
-        if (by_cols ? lane < 16 : (lane & 15) == 0) wmax[pl][wave][sub] = mx[pl];
+        if (by_cols ? lane < cols : (lane & 15) == 0) wmax[pl][wave][sub] = mx[pl];
     }
     __syncthreads();
     int E[PL];
@@ -518,34 +525,32 @@ __global__ __launch_bounds__(64 * kRowWavesMax) void split_pair_kernel(const Spl
     ScanCount cnt[PL] = {};
     if (by_cols) {
 #pragma unroll
-        for (int pl = 0; pl < PL; ++pl)
+        for (int pl = 0; pl < PL; ++pl) {
+            const int l0 = word0 * 4;
+            Fixed x[4][4];
+            SignMask sm[4];
+            const unsigned long long flip = pl ? side.flip : 0ull;
 #pragma unroll
-            for (int j0 = 0; j0 < J; j0 += 4) {
-                const int l0 = (word0 + j0) * 4;
-                Fixed x[4][4];
-                SignMask sm[4];
-                const unsigned long long flip = pl ? side.flip : 0ull;
+            for (int j = 0; j < 4; ++j) {
+                const unsigned long long(&w)[4] = v[pl][j];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const unsigned long long(&w)[4] = v[pl][j0 + j];
+                for (int u = 0; u < 4; ++u) x[j][u] = to_fixed<WIDE>(w[u], E[pl]);
+                sm[j] = sign_mask(w[0] ^ flip, w[1] ^ flip, w[2] ^ flip, w[3] ^ flip);
+                if constexpr (SCAN) scan_count4(cnt[pl], w, E[pl], edge_g, edge_h);
+            }
+            if (l0 < k_pad) {
+                int8_t* dst = side.S[pl] + word_offset(vec, l0, k_pad);
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) x[j][u] = to_fixed<WIDE>(w[u], E[pl]);
-                    sm[j] = sign_mask(w[0] ^ flip, w[1] ^ flip, w[2] ^ flip, w[3] ^ flip);
-                    if constexpr (SCAN) scan_count4(cnt[pl], w, E[pl], edge_g, edge_h);
-                }
-                if (l0 < k_pad) {
-                    int8_t* dst = side.S[pl] + word_offset(vec, l0, k_pad);
-#pragma unroll
-                    for (int p = 1; p <= (WIDE ? OZIMMU_MAX_SLICES : 9); ++p) {
-                        if (p <= s) {
-                            const uint4 y = {packed_slice<WIDE>(x[0], sm[0], p), packed_slice<WIDE>(x[1], sm[1], p),
-                                             packed_slice<WIDE>(x[2], sm[2], p), packed_slice<WIDE>(x[3], sm[3], p)};
-                            *reinterpret_cast<uint4*>(dst + (p - 1) * side.slice_stride) = y;
-                        }
+                for (int p = 1; p <= (WIDE ? OZIMMU_MAX_SLICES : 9); ++p) {
+                    if (p <= s) {
+                        const uint4 y = {packed_slice<WIDE>(x[0], sm[0], p), packed_slice<WIDE>(x[1], sm[1], p),
+                                         packed_slice<WIDE>(x[2], sm[2], p), packed_slice<WIDE>(x[3], sm[3], p)};
+                        *reinterpret_cast<uint4*>(dst + (p - 1) * side.slice_stride) = y;
                     }
                 }
-                __builtin_amdgcn_sched_barrier(0);   // one group's temporaries at a time
             }
+            __builtin_amdgcn_sched_barrier(0);   // one plane's temporaries at a time
+        }
     } else {
 #pragma unroll
         for (int j = 0; j < R; ++j) {
@@ -1072,15 +1077,20 @@ hipError_t launch_scan_reduce(const unsigned long long* slots, int planes, int s
     return hipGetLastError();
 }
 
-static unsigned pair_blocks(const SplitOperand& x) { return (unsigned)(x.padded / (x.by_cols ? kPairColumns : kRowGroup)); }
+static int pair_col_shift(const SplitOperand& x, int64_t k_pad) { return k_pad > 1024 || x.padded / kPairColumns < kComputeUnits ? 3 : 4; }
+static unsigned pair_blocks(const SplitOperand& x, int64_t k_pad) { return (unsigned)(x.by_cols ? x.padded >> pair_col_shift(x, k_pad) : x.padded / kRowGroup); }
 
 bool split_pair_applies(const SplitOperand& a, const SplitOperand& b, int planes, int64_t k_pad, bool counting) {
     if (k_pad < 1 || k_pad > (planes == 2 ? 1024 : 2048)) return false;
     if (planes == 2 && ((reinterpret_cast<uintptr_t>(a.X) | reinterpret_cast<uintptr_t>(b.X)) % 16 != 0)) return false;
-    const int64_t blocks = (int64_t)pair_blocks(a) + pair_blocks(b);
+    const int64_t blocks = (int64_t)pair_blocks(a, k_pad) + pair_blocks(b, k_pad);
     if (counting && (size_t)blocks * kScanCounters * planes * sizeof(unsigned) > 2 * scan_slots_bytes(planes)) return false;
-    // Operands of more than 32 MiB (real elements) stay with the kernels of their own: there the bytes count, not the launches
-    return (a.padded + b.padded) * k_pad * planes <= (int64_t)4 << 20;
+    // Operands of more than 64 MiB stay with the kernels of their own: there the bytes count, not the launches. Per call, own kernels
+    // against this launch: 1408^3 at nine slices (33 MiB) 127 -> 118 us, 2048^3 at twelve (64) 438 -> 428, complex 4096 x 4096 x 512 at seven
+    // (64) 752 -> 741, 64 x 16384 x 512 at eight (64.3) 70 -> 47 but 16384 x 64 x 512, the same bytes the other way round, 55.7 -> 56.6.
+    // Two operands stored as rows have no pass for maxima to save, and their own kernels keep more loads in flight: the line is at
+    // 32 MiB (transposed 3001 x 1777 x 1203 at six slices, 44 MiB: 163 us with its own kernels, 168 with this launch; 2048 x 2048 x 1024 109, 108).
+    return (a.padded + b.padded) * k_pad * planes <= (int64_t)(a.by_cols || b.by_cols ? 8 : 4) << 20;
 }
 
 hipError_t launch_split_pair(const SplitOperand& a, const SplitOperand& b, int planes, int64_t k, int64_t k_pad, int s, hipStream_t st,
@@ -1099,15 +1109,16 @@ hipError_t launch_split_pair(const SplitOperand& a, const SplitOperand& b, int p
         y.flip = x.negate_im ? 1ull << 63 : 0ull;
         y.by_cols = x.by_cols;
         y.vec = planes == 1 && !x.by_cols && x.ld % 2 == 0 && reinterpret_cast<uintptr_t>(x.X) % 16 == 0;
-        y.blocks = pair_blocks(x);
+        y.col_shift = pair_col_shift(x, k_pad);
+        y.blocks = pair_blocks(x, k_pad);
         return y;
     };
     const SplitSide sa = side(a), sb = side(b);
     const ScanTarget scan = scan_target(nullptr, 0, s);
-    const bool eight = k_pad > 1024;
-    const dim3 grid(sa.blocks + sb.blocks), block(64 * (eight ? 16 : (unsigned)((k_pad + 63) / 64)));
-#define OZ_PAIR(W, SC, PL, J) split_pair_kernel<W, SC, PL, J><<<grid, block, 0, st>>>(sa, sb, (int)k, (int)k_pad, s, partials, scan.edge_g, scan.edge_h)
-#define OZ_PAIRS(W, SC) do { if (planes == 2) OZ_PAIR(W, SC, 2, 4); else if (eight) OZ_PAIR(W, SC, 1, 8); else OZ_PAIR(W, SC, 1, 4); } while (0)
+    const bool two = k_pad > 1024;
+    const dim3 grid(sa.blocks + sb.blocks), block(64 * (two ? 16 : (unsigned)((k_pad + 63) / 64)));
+#define OZ_PAIR(W, SC, PL, R) split_pair_kernel<W, SC, PL, R><<<grid, block, 0, st>>>(sa, sb, (int)k, (int)k_pad, s, partials, scan.edge_g, scan.edge_h)
+#define OZ_PAIRS(W, SC) do { if (planes == 2) OZ_PAIR(W, SC, 2, 1); else if (two) OZ_PAIR(W, SC, 1, 2); else OZ_PAIR(W, SC, 1, 1); } while (0)
     if (s > 9) { if (partials) OZ_PAIRS(true, true); else OZ_PAIRS(true, false); }
     else       { if (partials) OZ_PAIRS(false, true); else OZ_PAIRS(false, false); }
 #undef OZ_PAIRS

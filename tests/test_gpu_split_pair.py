@@ -27,7 +27,7 @@ def stored(M, pad, odd):
 @pytest.mark.parametrize("ta", [False, True])
 @pytest.mark.parametrize("tb", [False, True])
 @pytest.mark.parametrize("m,n,k,s", [(5, 17, 1, 3), (16, 33, 64, 9), (130, 70, 65, 10), (40, 20, 1024, 8), (40, 20, 1025, 12), (20, 50, 2048, 7),
-                                     (20, 50, 2049, 7)])
+                                     (20, 50, 2049, 7), (9, 4100, 40, 6), (300, 150, 130, 5)])
 def test_real_operands_bit_exact(ta, tb, m, n, k, s):
     A, B = wl.phi_pair(m, n, k, 1.0, seed=k)
     A[0, :] = 0.0
