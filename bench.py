@@ -314,7 +314,7 @@ def main():
             "zero_operands": {"TOPs": z_tops, "shader_MHz": z_mhz},
             "random_7bit_operands": {"TOPs": r_tops, "shader_MHz": r_mhz},
             "kernel_vs_random_7bit_loop": achieved_tops / r_tops if r_tops > 0 else None,
-            # the other INT8 MFMA shape of gfx950, for the record (the kernel uses 32x32x32)
+            # the shape that the product kernel uses; the two above and the next key are of 32x32x32
             "mfma_16x16x64": {"zero_operands": {"TOPs": z16, "shader_MHz": z16_mhz},
                               "random_7bit_operands": {"TOPs": r16, "shader_MHz": r16_mhz}},
         }
