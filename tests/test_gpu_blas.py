@@ -52,7 +52,7 @@ def test_blas_transposes_and_scalars_bit_exact(ta, tb):
 
 @pytest.mark.parametrize("m,n,k,s", [(300, 270, 1300, 7), (33, 520, 2049, 5), (257, 64, 64, 13), (40, 50, 70000, 2)])
 def test_blas_shapes_across_the_kernels(m, n, k, s):
-    """Short k (sum kept in registers), long k (diagonal buffers) and INT64 k-blocking."""
+    """Short k, long k, and k beyond the INT32 block (walks shared by several workgroups)."""
     run(True, False, m, n, k, 1.25, 0.75, s, phi=2.0, seed=3, pad=(1, 0, 7))
     run(False, True, m, n, k, 1.0, 0.0, s, phi=0.5, seed=4)
 
@@ -111,7 +111,7 @@ def test_complex_blas_transposes_and_scalars_bit_exact(ta, tb):
 
 @pytest.mark.parametrize("m,n,k,s", [(300, 270, 1300, 7), (33, 520, 2049, 5), (257, 64, 64, 13), (40, 50, 70000, 2)])
 def test_complex_blas_shapes_across_the_kernels(m, n, k, s):
-    """Short k (both products of a part in one launch), long k (four launches) and INT64 k-blocking."""
+    """Short k, long k, and k beyond the INT32 block (walks shared by several workgroups, four launches)."""
     zrun("C", "N", m, n, k, 1.25 + 0.5j, 0.75j, s, seed=3, pad=(1, 0, 7))
     zrun("N", "C", m, n, k, 1.0, 0.0, s, seed=4)
 

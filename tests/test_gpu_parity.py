@@ -248,7 +248,7 @@ def test_dgemm_seeded_random_shapes_bit_exact(case):
                                      (1, 1, 140000, 16)])
 def test_dgemm_extreme_aspect_ratios_bit_exact(m, n, k, s):
     """Thousands of tiles along one dimension and a single ragged one along the other; very long k with a
-    handful of outputs (INT64 diagonal sums, two bands at 16 slices)."""
+    handful of outputs (shared walks beyond the INT32 block, two bands at 16 slices)."""
     A, B = wl.phi_pair(m, n, k, 1.0, seed=41)
     assert np.array_equal(bits(gpu_dgemm(A, B, s)), bits(oracle.dgemm(A, B, s)))
 
@@ -311,7 +311,8 @@ def test_dgemm_subnormal_and_overflowing_scale():
 
 
 def test_dgemm_k_blocking_long_diagonals():
-    """s * k_pad > 2^17 forces the INT64 path: registers are flushed every 2^17 products."""
+    """s * k_pad > 2^17: one INT32 sum cannot hold a diagonal. With the reported workspace products of so few tiles share their
+    walks, and every part fits; INT64 sums in the workspace are what test_gpu_k_blocking.py runs."""
     m, n, k, s = 40, 50, 70000, 2
     A, B = wl.phi_pair(m, n, k, 2.0, seed=7)
     assert s * ozimmu.slice_geometry(m, k)[1] > ozimmu.INT32_BLOCK
@@ -348,7 +349,7 @@ def test_two_runs_identical_and_stream_argument():
 
 # ------------------------------------------------------------------ complex
 @pytest.mark.parametrize("m,n,k,s", [(64, 64, 64, 7), (130, 70, 256, 7), (33, 300, 100, 11),
-                                     # longer k, INT32 and INT64 sums
+                                     # longer k, shared walks within and beyond the INT32 block
                                      (70, 50, 1300, 6), (300, 260, 1100, 9), (20, 30, 70000, 2)])
 def test_zgemm_bit_exact(m, n, k, s):
     A = wl.gaussian_complex(m, k, seed=1)
@@ -366,10 +367,9 @@ def test_zgemm_bit_exact(m, n, k, s):
 @pytest.mark.parametrize("s", range(1, 17))
 @pytest.mark.parametrize("k", [96, 128, 200])
 def test_zgemm_one_launch_every_slice_count(s, k):
-    """The four real products walked by one workgroup per tile, for every kernel instantiation: one
-    continuous stream of steps up to eight slices (k = 96: exactly the three steps the walk runs ahead, k = 128:
-    one more),
-    a pipeline per band beyond; two tile rows and columns with ragged edges."""
+    """The four real products as the four results of one wavefront's patch, for every kernel instantiation: one band up to
+    eight slices, two beyond; an odd number of slabs of 32 positions and even ones; two tile rows and columns with ragged
+    edges."""
     m, n = 70, 140
     A = wl.gaussian_complex(m, k, seed=10 + s)
     B = wl.unit_column_complex(k, n, seed=30 + s)
