@@ -51,32 +51,16 @@ def _check_m0(src: str) -> None:
                 raise RuntimeError(f"{listing.name}:{n}: M0 is used outside the direct-load sequence: {line.strip()}")
 
 
-def _check_accumulators(src: str) -> None:
-    """The MFMAs of the product kernels sit in inline assembly, so the compiler does not know when their results may be
-    read: an accumulation register that it copied or spilled by itself right behind an MFMA would give a wrong sum. In the
-    generated assembly, whatever touches an accumulation register has to stand at least twelve wait states behind the last
-    MFMA (seven are asked for), and whatever writes one at least three ahead of the next (two are asked for)."""
-    import re
+def _check_hazards(src: str) -> None:
+    """The MFMAs and direct loads of the product kernels sit in inline assembly, where the compiler adds no wait states: an
+    accumulation register that it copied right behind an MFMA, or an operand that it wrote right ahead of one, would give a
+    wrong sum. asm_check reads the distances off the generated assembly."""
+    from . import asm_check
 
-    acc = re.compile(r"\ba(\d+|\[\d+:\d+\])")
     for listing in OBJ.glob(f"{src.rsplit('.', 1)[0]}-hip-amdgcn-amd-amdhsa-gfx950*.s"):
-        since_mfma, since_touch = 1000, 1000
-        for n, line in enumerate(listing.read_text().splitlines(), 1):
-            code = line.split(";", 1)[0].strip()
-            if not code or code.startswith(".") or code.endswith(":"):
-                continue
-            states = int(code.split()[1], 0) + 1 if code.startswith("s_nop") else 1
-            if code.startswith("v_mfma"):
-                if since_touch < 3:
-                    raise RuntimeError(f"{listing.name}:{n}: an accumulation register is written just ahead of an MFMA")
-                since_mfma = 0
-            elif acc.search(code):
-                if since_mfma < 12:
-                    raise RuntimeError(f"{listing.name}:{n}: an accumulation register is touched behind an MFMA: {code}")
-                since_touch = 0
-            else:
-                since_touch += states
-            since_mfma += states if not code.startswith("v_mfma") else 0
+        found = asm_check.hazards(listing.read_text().splitlines())
+        if found:
+            raise RuntimeError("\n".join(f"{listing.name}:{x}" for x in found[:20]))
 
 
 def _compile(src: str) -> Path:
@@ -96,7 +80,7 @@ def _compile(src: str) -> Path:
         sys.stderr.write(err + "\n")
     if src in USES_M0:
         _check_m0(src)
-        _check_accumulators(src)
+        _check_hazards(src)
     return obj
 
 

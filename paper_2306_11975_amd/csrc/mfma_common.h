@@ -150,6 +150,14 @@ __device__ __forceinline__ void valu_results_ready() {
     __builtin_amdgcn_sched_barrier(0);
 }
 
+// At the bottom of the step loop: what the compiler puts on its exit and its back edge (it copied one sum there) comes no
+// closer to the last MFMAs than the twelve wait states that the build checks for. They pass while those MFMAs execute.
+__device__ __forceinline__ void last_mfma_issued() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 3");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // acc = RN(acc + S_e 2^(-7 (e + 2))) for the diagonals of a band, least significant first. The
 // product of an integer below 2^31 and a power of two is exact, so the fused operation rounds
 // exactly like the sum it stands for.

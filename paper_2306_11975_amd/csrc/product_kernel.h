@@ -426,6 +426,7 @@ __device__ __forceinline__ void band_walk(v4i (&acc)[kBand][4], const GemmArgs& 
                 __builtin_amdgcn_sched_barrier(0);   // keep the reads where their registers fall free
             }
         });
+        last_mfma_issued();
         if constexpr (!B::TWO && SB > 1) advance(PH2);
         if constexpr (B::TWO) advance(PH1);
         if constexpr (B::NB1 == 2) {
