@@ -182,7 +182,7 @@ hipError_t split_operands(const Layout& L, bool cplx, const Stored& a, const Sto
             x[o].E[p] = reinterpret_cast<int32_t*>(ws + (o ? L.off_eb : L.off_ea)[p]);
         }
     }
-    if (split_pair_applies(x[0], x[1], planes, L.k_pad, sums_a != nullptr))
+    if (split_pair_applies(x[0], x[1], planes, L.k_pad, s, sums_a != nullptr))
         return launch_split_pair(x[0], x[1], planes, k, L.k_pad, s, st, sums_a ? reinterpret_cast<unsigned*>(ws + L.off_scan) : nullptr, sums_a, sums_b);
     hipError_t e = hipSuccess;
     if (sums_a) {

@@ -123,7 +123,7 @@ struct SplitOperand {
 // Whether one launch splits both operands (split_pair_kernel), and the launch. partials (optional; 2 scan_slots_bytes(planes)
 // bytes, need not be cleared): it also counts, and the bits the planes lose with s and with s - 1 slices arrive in sums_a
 // and sums_b ([planes][16]; device or mapped host memory).
-bool split_pair_applies(const SplitOperand& a, const SplitOperand& b, int planes, int64_t k_pad, bool counting);
+bool split_pair_applies(const SplitOperand& a, const SplitOperand& b, int planes, int64_t k_pad, int s, bool counting);
 hipError_t launch_split_pair(const SplitOperand& a, const SplitOperand& b, int planes, int64_t k, int64_t k_pad, int s, hipStream_t st,
                              unsigned* partials, unsigned long long* sums_a, unsigned long long* sums_b);
 hipError_t launch_scan_reduce(const unsigned long long* slots, int planes, int s, unsigned long long* out_first,

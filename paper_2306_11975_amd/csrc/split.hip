@@ -440,6 +440,7 @@ struct SplitSide {
     unsigned long long flip;   // sign bit: the slices of the conjugated operand's imaginary plane
     int by_cols, vec;
     int col_shift;             // columns to a workgroup, as a power of two: 3 or 4
+    int row_shift;             // groups of four rows to a workgroup, as a power of two: 0 to 2
     unsigned blocks;           // workgroups
 };
 
@@ -458,10 +459,13 @@ __global__ __launch_bounds__(64 * kRowWavesMax) void split_pair_kernel(const Spl
     const bool by_cols = side.by_cols;
     // the thread's vector, its index among the block's, and its first word; words of one vector are `step` apart (a column's
     // follow each other: sixteen positions are one 16-byte store per slice)
+    // (rows: wavefronts side by side are on different groups of four rows)
+    const int group = by_cols ? 0 : wave & ((1 << side.row_shift) - 1), groups = by_cols ? 1 : 1 << side.row_shift;
     const int sub = by_cols ? tid & (cols - 1) : lane >> 4;
-    const int word0 = by_cols ? (tid >> side.col_shift) * J : wave * 16 + (lane & 15), step = by_cols ? 1 : nwaves * 16;
+    const int word0 = by_cols ? (tid >> side.col_shift) * J : (wave >> side.row_shift) * 16 + (lane & 15);
+    const int step = by_cols ? 1 : (nwaves >> side.row_shift) * 16;
     const int words = by_cols ? J : R;
-    const int64_t vec = block * (by_cols ? cols : kRowGroup) + sub;
+    const int64_t vec = by_cols ? block * cols + sub : (block * groups + group) * kRowGroup + sub;
     const bool live = vec < side.count;
     const unsigned long long* src = reinterpret_cast<const unsigned long long*>(side.X) + PL * (live ? (by_cols ? vec : vec * side.ld) : 0);
     const int64_t inc = PL * (by_cols ? side.ld : 1);   // from one position to the next
@@ -517,8 +521,8 @@ __global__ __launch_bounds__(64 * kRowWavesMax) void split_pair_kernel(const Spl
     int E[PL];
 #pragma unroll
     for (int pl = 0; pl < PL; ++pl) {
-        unsigned long long m = wmax[pl][0][sub];
-        for (int w = 1; w < nwaves; ++w) m = wmax[pl][w][sub] > m ? wmax[pl][w][sub] : m;
+        unsigned long long m = wmax[pl][group][sub];
+        for (int w = group + groups; w < nwaves; w += groups) m = wmax[pl][w][sub] > m ? wmax[pl][w][sub] : m;
         E[pl] = exponent_of_max(m);
         if (live && word0 == 0) side.E[pl][vec] = E[pl];
     }
@@ -1077,26 +1081,64 @@ hipError_t launch_scan_reduce(const unsigned long long* slots, int planes, int s
     return hipGetLastError();
 }
 
-static int pair_col_shift(const SplitOperand& x, int64_t k_pad) { return k_pad > 1024 || x.padded / kPairColumns < kComputeUnits ? 3 : 4; }
-static unsigned pair_blocks(const SplitOperand& x, int64_t k_pad) { return (unsigned)(x.by_cols ? x.padded >> pair_col_shift(x, k_pad) : x.padded / kRowGroup); }
+// How split_pair_kernel is launched: wavefronts to a workgroup, words of its row to a thread, and what a workgroup takes.
+struct PairShape {
+    unsigned waves;
+    int row_words;                 // 1, 2 or 4
+    int col_shift[2], row_shift;
+    unsigned blocks[2];
+};
+// The operands that are stored as rows hold enough that the loads in flight count. Per call, one word to a thread against four
+// (and own kernels): transposed 3994 x 153 x 872 at four slices 39.9 -> 28.2 us (33.6), 5289 x 46 x 629 at eight 44.9 -> 37.3 (42.7),
+// 36613 x 220 x 204 at five 84.6 -> 75.7 (73.5), rows beside columns 10254 x 34 x 764 at ten 106.6 -> 88.2 (94.1), 16785 x 353 x 580 at four
+// 115 -> 87 (87), complex 3859 x 187 x 821 at six 89 -> 80 (81). Below the line one word is up to 5 % faster: more threads have work.
+static bool long_rows(const SplitOperand& a, const SplitOperand& b, int planes, int64_t k_pad) {
+    const int64_t of_rows = ((a.by_cols ? 0 : a.padded) + (b.by_cols ? 0 : b.padded)) * k_pad * planes;
+    return planes == 2 ? k_pad >= 256 && of_rows >= (int64_t)5 << 19 : of_rows >= (int64_t)(k_pad >= 256 ? 1 : 2) << 20;
+}
+static PairShape pair_shape(const SplitOperand& a, const SplitOperand& b, int planes, int64_t k_pad) {
+    const bool two = k_pad > 1024, any_cols = a.by_cols || b.by_cols;
+    PairShape p{};
+    p.waves = two ? 16 : (unsigned)((k_pad + 63) / 64);   // sixteen positions of a column to a thread
+    p.row_words = two ? 2 : 1;
+    // Rows of some size are read four words to a thread, for four times the loads in flight: by as few wavefronts as that asks
+    // for, or, beside columns, which need the others, by workgroups of several groups of four rows.
+    if (long_rows(a, b, planes, k_pad)) {
+        const unsigned segments = (unsigned)((k_pad + 255) / 256);   // wavefronts along a row
+        p.row_words = 4;
+        p.row_shift = !any_cols ? 0 : two ? 1 : 2;
+        p.waves = !any_cols ? segments : two ? 16 : 4 * segments;
+    }
+    const SplitOperand* const x[2] = {&a, &b};
+    for (int i = 0; i < 2; ++i) {
+        p.col_shift[i] = two || x[i]->padded / kPairColumns < kComputeUnits ? 3 : 4;
+        p.blocks[i] = (unsigned)(x[i]->by_cols ? x[i]->padded >> p.col_shift[i] : x[i]->padded / (kRowGroup << p.row_shift));
+    }
+    return p;
+}
 
-bool split_pair_applies(const SplitOperand& a, const SplitOperand& b, int planes, int64_t k_pad, bool counting) {
+bool split_pair_applies(const SplitOperand& a, const SplitOperand& b, int planes, int64_t k_pad, int s, bool counting) {
     if (k_pad < 1 || k_pad > (planes == 2 ? 1024 : 2048)) return false;
     if (planes == 2 && ((reinterpret_cast<uintptr_t>(a.X) | reinterpret_cast<uintptr_t>(b.X)) % 16 != 0)) return false;
-    const int64_t blocks = (int64_t)pair_blocks(a, k_pad) + pair_blocks(b, k_pad);
+    const PairShape shape = pair_shape(a, b, planes, k_pad);
+    const int64_t blocks = (int64_t)shape.blocks[0] + shape.blocks[1];
     if (counting && (size_t)blocks * kScanCounters * planes * sizeof(unsigned) > 2 * scan_slots_bytes(planes)) return false;
-    // Operands of more than 64 MiB stay with the kernels of their own: there the bytes count, not the launches. Per call, own kernels
-    // against this launch: 1408^3 at nine slices (33 MiB) 127 -> 118 us, 2048^3 at twelve (64) 438 -> 428, complex 4096 x 4096 x 512 at seven
-    // (64) 752 -> 741, 64 x 16384 x 512 at eight (64.3) 70 -> 47 but 16384 x 64 x 512, the same bytes the other way round, 55.7 -> 56.6.
-    // Two operands stored as rows have no pass for maxima to save, and their own kernels keep more loads in flight: the line is at
-    // 32 MiB (transposed 3001 x 1777 x 1203 at six slices, 44 MiB: 163 us with its own kernels, 168 with this launch; 2048 x 2048 x 1024 109, 108).
-    return (a.padded + b.padded) * k_pad * planes <= (int64_t)(a.by_cols || b.by_cols ? 8 : 4) << 20;
+    // Complex rows of more than nine slices: four words of both planes leave no registers for the cut, one word too few loads in
+    // flight (per call, own kernels against this launch: 4045 x 196 x 664 at thirteen 185 -> 199 and 201 us).
+    if (planes == 2 && s > 9 && long_rows(a, b, planes, k_pad)) return false;
+    // Operands of more than 64 MiB (padded) stay with the kernels of their own: there the bytes count more than the launches. Per call, own
+    // kernels against this launch: 2104 x 1240 x 1431 at ten slices (38 MiB) 221 -> 208 us, 4076 columns beside 42 rows, k = 1661, at thirteen (54) 116 -> 104,
+    // 10769 x 2471 x 580 at nine (62) 604 -> 597, complex 428 x 11207 x 303 at six (58) 186 -> 164; beyond it 10634 x 435 x 1094 at seven (96) 186 -> 180,
+    // 31863 x 1144 x 706 at three (185) 272 -> 276. (Wide operands stored as columns would gain beyond it too: 64 x 16384 x 512 at eight, 64.5 MiB,
+    // 70 -> 47.)
+    return (a.padded + b.padded) * k_pad * planes <= (int64_t)8 << 20;
 }
 
 hipError_t launch_split_pair(const SplitOperand& a, const SplitOperand& b, int planes, int64_t k, int64_t k_pad, int s, hipStream_t st,
                              unsigned* partials, unsigned long long* sums_a, unsigned long long* sums_b) {
-    if (!split_pair_applies(a, b, planes, k_pad, partials != nullptr)) return hipErrorInvalidValue;
-    auto side = [&](const SplitOperand& x) {
+    if (!split_pair_applies(a, b, planes, k_pad, s, partials != nullptr)) return hipErrorInvalidValue;
+    const PairShape shape = pair_shape(a, b, planes, k_pad);
+    auto side = [&](const SplitOperand& x, int i) {
         SplitSide y{};
         y.X = x.X;
         y.ld = x.ld;
@@ -1109,16 +1151,19 @@ hipError_t launch_split_pair(const SplitOperand& a, const SplitOperand& b, int p
         y.flip = x.negate_im ? 1ull << 63 : 0ull;
         y.by_cols = x.by_cols;
         y.vec = planes == 1 && !x.by_cols && x.ld % 2 == 0 && reinterpret_cast<uintptr_t>(x.X) % 16 == 0;
-        y.col_shift = pair_col_shift(x, k_pad);
-        y.blocks = pair_blocks(x, k_pad);
+        y.col_shift = shape.col_shift[i];
+        y.row_shift = shape.row_shift;
+        y.blocks = shape.blocks[i];
         return y;
     };
-    const SplitSide sa = side(a), sb = side(b);
+    const SplitSide sa = side(a, 0), sb = side(b, 1);
     const ScanTarget scan = scan_target(nullptr, 0, s);
-    const bool two = k_pad > 1024;
-    const dim3 grid(sa.blocks + sb.blocks), block(64 * (two ? 16 : (unsigned)((k_pad + 63) / 64)));
+    const dim3 grid(sa.blocks + sb.blocks), block(64 * shape.waves);
 #define OZ_PAIR(W, SC, PL, R) split_pair_kernel<W, SC, PL, R><<<grid, block, 0, st>>>(sa, sb, (int)k, (int)k_pad, s, partials, scan.edge_g, scan.edge_h)
-#define OZ_PAIRS(W, SC) do { if (planes == 2) OZ_PAIR(W, SC, 2, 1); else if (two) OZ_PAIR(W, SC, 1, 2); else OZ_PAIR(W, SC, 1, 1); } while (0)
+#define OZ_PAIRS(W, SC) do { \
+        if (planes == 2) { if (shape.row_words == 4) OZ_PAIR(W, SC, 2, 4); else OZ_PAIR(W, SC, 2, 1); } \
+        else if (shape.row_words == 4) OZ_PAIR(W, SC, 1, 4); else if (shape.row_words == 2) OZ_PAIR(W, SC, 1, 2); else OZ_PAIR(W, SC, 1, 1); \
+    } while (0)
     if (s > 9) { if (partials) OZ_PAIRS(true, true); else OZ_PAIRS(true, false); }
     else       { if (partials) OZ_PAIRS(false, true); else OZ_PAIRS(false, false); }
 #undef OZ_PAIRS

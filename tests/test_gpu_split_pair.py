@@ -70,3 +70,47 @@ def test_guess_is_checked_from_the_counts(cplx, m, n, k):
             torch.cuda.synchronize()
             assert got == right and confirmed == (guess == right)
             assert np.array_equal(bits(C.cpu().numpy().view(np.float64)), bits(want.view(np.float64)))
+
+
+# rows of 2^20 elements and more are read four words to a thread: beside columns by workgroups of sixteen rows (k up to 1024) and of eight,
+# beside rows by one to eight wavefronts; rows aligned and not, numbers of rows that leave groups empty
+@pytest.mark.parametrize("rows_too", [False, True])
+@pytest.mark.parametrize("m,n,k,s", [(4097, 20, 257, 9), (4100, 40, 256, 3), (1300, 33, 1000, 10), (1025, 17, 1024, 4), (1030, 20, 1025, 5), (515, 50, 2047, 12)])
+def test_long_rows_bit_exact(m, n, k, s, rows_too):
+    A, B = wl.phi_pair(m, n, k, 1.0, seed=k)
+    A[m // 2, :] = 0.0
+    rows = np.r_[0:9, m // 2 - 2:m // 2 + 3, m - 9:m]
+    want = oracle.dgemm(A[rows], B, s)
+    for pad, odd in ((0, 0), (3, 1)):
+        dA, dB = stored(A, pad, odd), stored(B.T if rows_too else B, pad, odd)
+        C = torch.empty((n, m), dtype=torch.float64, device="cuda")
+        ozimmu.dgemm_blas("T", "N" if rows_too else "T", m, n, k, 1.0, dA, dA.stride(0), dB, dB.stride(0), 0.0, C, m, s, ozimmu.alloc_workspace(n, m, k, s))
+        torch.cuda.synchronize()
+        assert np.array_equal(bits(C.cpu().numpy().T[rows]), bits(want)), (pad, odd)
+
+
+# complex: four words up to nine slices, kernels of their own beyond
+@pytest.mark.parametrize("m,n,k,s", [(5130, 140, 256, 8), (2050, 150, 700, 9), (1300, 200, 1024, 3), (2050, 150, 700, 10)])
+def test_long_complex_rows_bit_exact(m, n, k, s):
+    A, B = wl.gaussian_complex(m, k, 1), wl.gaussian_complex(k, n, 2)
+    rows = np.r_[0:9, m - 9:m]
+    C = torch.empty((m, n), dtype=torch.complex128, device="cuda")
+    dA, dB = stored(A, 1, 0), stored(B, 2, 0)
+    ozimmu.zgemm(dA, dB, C, s, ozimmu.alloc_workspace(m, n, k, s, True))
+    torch.cuda.synchronize()
+    assert np.array_equal(bits(C.cpu().numpy()[rows].view(np.float64)), bits(oracle.zgemm(A[rows], B, s).view(np.float64)))
+
+
+@pytest.mark.parametrize("cplx,m,n,k", [(False, 4097, 20, 257), (False, 600, 30, 2000), (True, 1300, 150, 1024)])
+def test_guess_is_checked_from_the_counts_of_long_rows(cplx, m, n, k):
+    A, B = (wl.gaussian_complex(m, k, 5), wl.gaussian_complex(k, n, 6)) if cplx else wl.phi_pair(m, n, k, 1.0, seed=4)
+    dA, dB = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+    rows = np.r_[0:9, m - 9:m]
+    right, _ = oracle.auto_num_slices(A, B, 1.0)
+    want = (oracle.zgemm if cplx else oracle.dgemm)(A[rows], B, right)
+    for guess in (right - 1, right, right + 1, 16):
+        C = torch.empty((m, n), dtype=dA.dtype, device="cuda")
+        got, confirmed = (ozimmu.zgemm_auto if cplx else ozimmu.dgemm_auto)(dA, dB, C, 1.0, guess=guess)
+        torch.cuda.synchronize()
+        assert got == right and confirmed == (guess == right)
+        assert np.array_equal(bits(C.cpu().numpy()[rows].view(np.float64)), bits(want.view(np.float64)))
