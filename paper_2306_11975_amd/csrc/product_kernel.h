@@ -730,11 +730,7 @@ void product_kernel(const GemmArgs g) {
     // Zr (complex interleave of the four-launch form only) in one batch after it, when the fold's registers are free again.
     double old_c[MODE == kModeReal ? 16 : 1], old_zr[MODE == kModeReal ? 16 : 1];
     auto fetch_old = [&](double (&dst)[16], const double* src, bool wanted) __attribute__((always_inline)) {
-        if (!wanted) {
-#pragma unroll
-            for (int u = 0; u < 16; ++u) dst[u] = 0.0;
-            return;
-        }
+        if (!wanted) return;   // (then nothing reads them)
         const Where at = where();
         const double* c = src + (int64_t)at.row0 * g.ldc + at.col;
         if (tile_inside()) {
@@ -835,9 +831,22 @@ void product_kernel(const GemmArgs g) {
                     });
                     return;
                 }
-                if (g.c_mode != 0) {
+                // (as `combined`, with one decision for all sixteen)
+                if (g.c_mode == 1) {
 #pragma unroll
-                    for (int u = 0; u < 16; ++u) sum[u] = combined(g, old_c[u], sum[u]);
+                    for (int u = 0; u < 16; ++u) sum[u] = old_c[u] + sum[u];
+                } else if (g.c_mode == 2) {
+#pragma unroll
+                    for (int u = 0; u < 16; ++u) sum[u] = old_c[u] - sum[u];
+                } else if (g.c_mode == 3) {
+                    if (g.alpha != 1.0) {
+#pragma unroll
+                        for (int u = 0; u < 16; ++u) sum[u] = g.alpha * sum[u];
+                    }
+                    if (g.beta != 0.0) {
+#pragma unroll
+                        for (int u = 0; u < 16; ++u) sum[u] = sum[u] + g.beta * old_c[u];
+                    }
                 }
                 if (inside) {
 #pragma unroll
