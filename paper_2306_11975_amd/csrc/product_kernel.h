@@ -24,9 +24,10 @@
 // four real products of the same 16 x 16 complex elements, in the same lanes and registers: one fold, one rounded FP64
 // operation per part, and C is written once as (re, im) pairs without anything having waited in memory.
 //
-// An odd number of slabs: the last step would be half empty. Beyond nine slices a kernel of its own (HEAD) takes the last slab
-// ahead of the steps instead, with two pairs of a diagonal to an MFMA (see band_walk); up to nine, where other workgroups of the
-// compute unit fill the gap, the last step runs with zeros for A's second slab.
+// An odd number of slabs: the last step would be half empty. With nine slices and more a kernel of its own (HEAD) takes the last
+// slab ahead of the steps instead, with two pairs of a diagonal to an MFMA (see band_walk); below, where the other workgroup of the
+// compute unit fills the gap (and at nine where there is none: a call is then mostly launches), the last step runs with zeros
+// for A's second slab.
 //
 // Why the small MFMA shape: what bounds this kernel at large k is the clock that the power management grants, and with
 // signed 7-bit operands a register-only loop of 16x16x64 sustains about a fifth more operations than one of 32x32x32.
@@ -1040,21 +1041,23 @@ hipError_t launch_fold(const GemmArgs& g, int s, hipStream_t st) {
 
 template <int MODE>
 hipError_t launch_for(const GemmArgs& g, int s, hipStream_t st) {
+    // An odd number of slabs, all of them walked by one workgroup: whatever their number, the half step saved counts (per call,
+    // half-empty last step against head: 4044 x 1069 x 72 at nine slices 43 -> 39 us, 4966 x 2346 x 28 at fifteen 163 -> 113, 8192 x 2351 x 82 at eleven 192 -> 168,
+    // 5372 x 5100 x 3744 at fourteen 7450 -> 7360). A shared walk has an odd slab in its last part only.
+    const bool head = g.block_steps == 0 && g.splits == 1 && ((g.t_end - g.t_begin) & 1);
     if (g.tile_cols == 64 && s <= 9) {   // 64 x 64 tiles, two workgroups per compute unit: not for the double-double sum
         if constexpr (MODE == kModeReal || MODE == kModeComplex) {
             const bool solo = (int64_t)g.tiles_m * g.tiles_n * g.splits <= kComputeUnits;
             switch (s) {
 #define OZ_CASE(S_) case S_: return solo ? launch_one<S_, 2, 2, MODE, true>(g, st) : launch_one<S_, 2, 2, MODE>(g, st);
-                OZ_CASE(1) OZ_CASE(2) OZ_CASE(3) OZ_CASE(4) OZ_CASE(5) OZ_CASE(6) OZ_CASE(7) OZ_CASE(8) OZ_CASE(9)
+                OZ_CASE(1) OZ_CASE(2) OZ_CASE(3) OZ_CASE(4) OZ_CASE(5) OZ_CASE(6) OZ_CASE(7) OZ_CASE(8)
 #undef OZ_CASE
+                case 9:
+                    return solo ? launch_one<9, 2, 2, MODE, true>(g, st) : head ? launch_one<9, 2, 2, MODE, false, true>(g, st) : launch_one<9, 2, 2, MODE>(g, st);
             }
         }
         return hipErrorInvalidValue;
     }
-    // An odd number of slabs, all of them walked by one workgroup: whatever their number, the half step saved counts (per call,
-    // half-empty last step against head: 4966 x 2346 x 28 at fifteen slices 163 -> 113 us, 8192 x 2351 x 82 at eleven 192 -> 168,
-    // 5372 x 5100 x 3744 at fourteen 7450 -> 7360). A shared walk has an odd slab in its last part only.
-    const bool head = g.block_steps == 0 && g.splits == 1 && ((g.t_end - g.t_begin) & 1);
     switch (s) {
 #define OZ_CASE(S_, WN_) case S_: return launch_one<S_, 2, WN_, MODE>(g, st);
         OZ_CASE(1, 4) OZ_CASE(2, 4) OZ_CASE(3, 4) OZ_CASE(4, 4) OZ_CASE(5, 4) OZ_CASE(6, 4) OZ_CASE(7, 4) OZ_CASE(8, 4) OZ_CASE(9, 4)
