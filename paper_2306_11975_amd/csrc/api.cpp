@@ -85,9 +85,12 @@ Layout make_layout(int64_t m, int64_t n, int64_t k, int s, bool cplx) {
 // How many workgroups share a tile of C, each with a part of k. With fewer tiles than compute units most of the chip
 // idles while a tile's walk takes its time; integer sums add up exactly in any order, so the walk can be shared, at the
 // price of the parts' INT32 sums going through memory and of a kernel that adds and folds them. The line is drawn where
-// the estimate says so: a step of a walk takes what its MFMAs take (64 cycles per pair and wavefront of a SIMD at 2.1 GHz, and no
-// less than the 0.5 us its loads need), a launch more 5 us, the sums 3.5 TB/s. Measured (product and fold, one part against
-// the parts chosen): 1273 x 153 x 8000, 6 slices, 96 -> 50 us; 35 x 154 x 2251, 9 slices, 69 -> 18 us.
+// the estimate says so: a step of a walk takes what its MFMAs take (64 cycles per pair and wavefront of a SIMD at 2.4 GHz) and what
+// they cannot cover of its loads (with one wavefront per SIMD 66 cycles behind each, twice s of them), and no less than 0.45 us; the
+// second launch takes 4 us, the sums 4.5 TB/s; more workgroups than compute units take 1.7 times as long where two share one, else 2.1 times. The
+// constants are fitted to 500 products of 8 to 230 tiles, 12 to 120 steps and 2 to 16 slices, each timed with one to 32 parts: on
+// average the choice costs 0.6 % more than the best one. Measured (product and fold, one part against the parts chosen): 80 tiles of
+// 60 steps 41 -> 31 us at five slices, 48 of 30 at six 30 -> 25, 100 of 30 at eleven 133 -> 106; the call 1273 x 153 x 8000 at six 96 -> 50.
 struct Split {
     int splits;
     int slabs;      // of a part (even)
@@ -99,13 +102,15 @@ Split choose_split(const Layout& L, int s, size_t available) {
     Split best{1, (int)slabs, 0};
     if (tiles == 0 || tiles >= kComputeUnits || steps < 8) return best;
     const int pairs = s <= kBand ? s * (s + 1) / 2 : s * (s + 1) / 2 + s - kBand;   // (a second band costs about its slices more)
-    const double step_us = std::max(0.5, pairs * (L.tile_cols == 128 ? 128.0 : 64.0) / 2100.0);
-    const double alone = steps * step_us;
-    double best_us = 0.85 * alone;
+    const bool wide_tiles = L.tile_cols == 128;
+    const double step_us = std::max(0.45, pairs * (wide_tiles ? 128.0 : 64.0) / 2400.0 + s * (wide_tiles ? 0.0825 : 0.055));
+    const double twice = !wide_tiles && s <= 9 ? 1.7 : 2.1;
+    const double alone_us = steps * step_us + 3.0;
+    double best_us = std::min(0.95 * alone_us, alone_us - 2.0);
     for (int64_t n = 2; n <= 64 && n * 2 <= steps; ++n) {
         const int64_t chunk = (steps + n - 1) / n, parts = (steps + chunk - 1) / chunk;
         if (2 * chunk * kSlab * s > OZIMMU_INT32_BLOCK || part * parts > available || tiles * parts > 2 * kComputeUnits) continue;
-        const double us = chunk * step_us * (tiles * parts > kComputeUnits ? 1.5 : 1.0) + 5.0 + 2.0 * part * parts / 3.5e6;
+        const double us = chunk * step_us * (tiles * parts > kComputeUnits ? twice : 1.0) + 7.0 + 2.0 * part * parts / 4.5e6;
         if (us < best_us) {
             best_us = us;
             best = Split{(int)parts, (int)(2 * chunk), part * (size_t)parts};
