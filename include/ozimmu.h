@@ -182,13 +182,16 @@ ozimmu_status_t ozimmu_dgemm_stage(int stage, int64_t m, int64_t n, int64_t k, c
                                    size_t workspace_bytes, void* stream);
 
 /*
- * How ozimmu_dgemm runs a shape, on the host only (nothing is launched; for tests and for callers
- * who want to know): the tile of C one workgroup owns, or shares with others that walk other parts of k (64 x 128; 64 x 64 from fourteen slices on, and up to
- * nine slices when k <= 512 or fewer than 256 of the larger tiles exist), the number of workgroups, the number of bands
- * the anti-diagonals are walked in (a wavefront holds the INT32 sums of at most eight diagonals at a
- * time: 2 bands beyond eight slices), and int32_block_steps = the largest number of slabs of
- * OZIMMU_K_ALIGN positions after which the INT32 sums are moved into INT64 sums (k-blocking; the walk takes
- * two slabs at a time), 0 if a whole diagonal fits one INT32 sum.
+ * How ozimmu_dgemm runs a shape with a workspace of ozimmu_workspace_bytes, on the host only (nothing is launched;
+ * for tests and for callers who want to know): the tile of C one workgroup owns, or shares with others that walk other
+ * parts of k (64 x 128; 64 x 64 from fourteen slices on, and up to nine slices when k <= 512 or fewer than 256 of the
+ * larger tiles exist), the number of workgroups of the slice products (a multiple of the number of tiles where
+ * they share tiles; a second launch then adds their sums up), the number of bands the anti-diagonals are walked in (a
+ * wavefront holds the INT32 sums of at most eight diagonals at a time: 2 bands beyond eight slices), and
+ * int32_block_steps = the largest number of slabs of OZIMMU_K_ALIGN positions after which the INT32 sums are moved into
+ * INT64 sums (k-blocking; the walk takes two slabs at a time), 0 if all products of a diagonal that one workgroup adds
+ * up fit one INT32 sum. With a smaller workspace that the call still accepts, fewer workgroups share a tile, or none
+ * do, and a product with OZIMMU_INT32_BLOCK < num_slices * k_padded then runs with k-blocking.
  */
 typedef struct {
     int tile_rows, tile_cols;

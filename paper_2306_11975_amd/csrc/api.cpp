@@ -121,10 +121,11 @@ Split choose_split(const Layout& L, int s, size_t available) {
 // Room for those sums behind a workspace of `total` bytes. They are used where the caller's workspace has it, but are not
 // asked for: smaller ones are accepted as well, and a product that fits the built-in scratch of ozimmu_dgemm_static fits
 // it with what is reported here.
-size_t split_room(const Layout& L, int s, size_t total) {
+size_t split_available(size_t total) {
     const size_t limit = OZIMMU_STATIC_SCRATCH_BYTES;
-    return choose_split(L, s, total <= limit ? limit - total : SIZE_MAX).bytes;
+    return total <= limit ? limit - total : SIZE_MAX;
 }
+size_t split_room(const Layout& L, int s, size_t total) { return choose_split(L, s, split_available(total)).bytes; }
 
 ozimmu_status_t hip_status(hipError_t e) { return e == hipSuccess ? OZIMMU_OK : OZIMMU_ERR_HIP; }
 
@@ -921,9 +922,10 @@ ozimmu_status_t ozimmu_launch_plan(int64_t m, int64_t n, int64_t k, int num_slic
     const Layout L = make_layout(m, n, k, num_slices, false);
     plan->tile_rows = L.tile_rows;
     plan->tile_cols = L.tile_cols;
-    plan->workgroups = (int64_t)L.tiles_m * L.tiles_n;
+    const int parts = k > 0 ? choose_split(L, num_slices, split_available(L.total)).splits : 1;
+    plan->workgroups = (int64_t)L.tiles_m * L.tiles_n * parts;
     plan->bands = num_slices > kBand ? 2 : 1;
-    plan->int32_block_steps = L.wide ? block_steps_for(num_slices) : 0;
+    plan->int32_block_steps = L.wide && parts == 1 ? block_steps_for(num_slices) : 0;
     return OZIMMU_OK;
 }
 

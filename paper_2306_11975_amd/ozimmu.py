@@ -239,7 +239,7 @@ def zgemm(A, B, C, num_slices: int, workspace, stream=None) -> None:
 
 
 def launch_plan(m: int, n: int, k: int, num_slices: int) -> dict:
-    """How ozimmu_dgemm runs a shape (ozimmu_plan_t as a dict; see ozimmu.h)."""
+    """How ozimmu_dgemm runs a shape with a workspace of the reported size (ozimmu_plan_t as a dict; see ozimmu.h)."""
     plan = Plan()
     _check(lib().ozimmu_launch_plan(m, n, k, num_slices, ctypes.byref(plan)))
     return {name: getattr(plan, name) for name, _ in Plan._fields_}

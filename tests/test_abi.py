@@ -121,13 +121,23 @@ def test_launch_plan_host_logic():
     assert ozimmu.launch_plan(8192, 8192, 8192, 10)["bands"] == 2
     assert ozimmu.launch_plan(100, 100, 100, 16) == {"tile_rows": 64, "tile_cols": 64, "workgroups": 4,
                                                      "bands": 2, "int32_block_steps": 0}
-    # k-blocking starts where the longest diagonal (s pairs) exceeds 2^17 products: steps of 32 positions
+    # k-blocking starts where the longest diagonal (s pairs) exceeds 2^17 products: slabs of 32 positions
     assert ozimmu.launch_plan(4096, 4096, 131072, 8)["int32_block_steps"] == 512
-    assert ozimmu.launch_plan(64, 64, 16384, 8)["int32_block_steps"] == 0
-    assert ozimmu.launch_plan(64, 64, 16385, 8)["int32_block_steps"] == 512
+    assert ozimmu.launch_plan(4096, 4096, 16384, 8)["int32_block_steps"] == 0
+    assert ozimmu.launch_plan(4096, 4096, 16385, 8)["int32_block_steps"] == 512
     for s in range(1, 17):
-        steps = ozimmu.launch_plan(1, 1, 1 << 22, s)["int32_block_steps"]
+        steps = ozimmu.launch_plan(1024, 2048, 1 << 22, s)["int32_block_steps"]
         assert steps * 32 * s <= ozimmu.INT32_BLOCK < (steps + 1) * 32 * s
+    # few tiles: several workgroups share each, and every part of k fits the INT32 sums
+    for k in (16384, 16385, 200000):
+        plan = ozimmu.launch_plan(64, 64, k, 8)
+        parts = plan["workgroups"]
+        assert 1 < parts <= 512 and plan["int32_block_steps"] == 0
+        assert -(-k // parts) * 8 <= ozimmu.INT32_BLOCK
+        # the room for their INT32 sums is part of what the workspace query reports
+        assert ozimmu.workspace_bytes(64, 64, k, 8) >= parts * 8 * 4 * plan["tile_rows"] * plan["tile_cols"] + 2 * 8 * 128 * k
+    assert ozimmu.launch_plan(1, 1, 1 << 22, 16)["int32_block_steps"] == 256     # more parts than a tile is shared by
+    assert ozimmu.launch_plan(64, 64, 256, 8)["workgroups"] == 1                 # too short to be shared
     L = ozimmu.lib()
     plan = ozimmu.Plan()
     assert L.ozimmu_launch_plan(-1, 1, 1, 3, ctypes.byref(plan)) == 1
