@@ -121,8 +121,8 @@ ozimmu_status_t ozimmu_slice_gemm(int64_t m, int64_t n, int64_t k, const int8_t*
 /*
  * Workspace size for ozimmu_dgemm / ozimmu_zgemm: slices of A and B, exponents, column maxima, and
  * -- only when num_slices * k_padded > OZIMMU_INT32_BLOCK (k-blocking) -- num_slices INT64 sums per
- * element of C. Otherwise every integer sum stays in registers. A complex product adds two m x n FP64
- * planes in which its real and imaginary parts are formed when k-blocking makes it four launches,
+ * element of C. Otherwise every integer sum stays in registers. A complex product adds, with
+ * k-blocking (which makes it four launches), two m x n FP64 planes in which its real and imaginary parts are formed,
  * and, with k and n small enough, room for B's slices in the form the kernel wants that splits A on
  * the fly (see ozimmu_zgemm). A product with fewer tiles than compute units and a long inner dimension adds
  * room for the INT32 sums of the workgroups that share a tile's walk along k (in all at most

@@ -72,8 +72,8 @@ Layout make_layout(int64_t m, int64_t n, int64_t k, int s, bool cplx) {
     off = align_up(off + sizeof(unsigned long long) * planes * (L.n_pad > L.m_pad ? L.n_pad : L.m_pad));  // either operand may be split by columns (complex: both planes at once)
     L.off_d = off;
     if (L.wide) off = align_up(off + (size_t)s * L.tiles_m * L.tiles_n * L.tile_rows * L.tile_cols * sizeof(long long));
-    L.off_z = off;   // complex: the real and imaginary parts of the result as two m x n planes
-    if (cplx) off = align_up(off + (size_t)2 * m * n * sizeof(double));
+    L.off_z = off;   // complex with k-blocking: the real and imaginary parts of the result as two m x n planes
+    if (cplx && L.wide) off = align_up(off + (size_t)2 * m * n * sizeof(double));
     L.off_gate = off;   // complex with a small B: its slice tensors for the kernel that splits A on the fly
     if (cplx) off = align_up(off + gate_scratch_bytes(n, k, s));
     L.off_scan = off;   // the counters of splitters that count for the slice-count check: first operand, then second

@@ -50,6 +50,11 @@ def test_geometry_and_workspace_size():
     ws_wide = ozimmu.workspace_bytes(4096, 4096, 131072, 8)
     assert ws_wide >= 8 * 4096 * 131072 * 2 + 8 * 4096 * 4096 * 8
     assert ozimmu.workspace_bytes(64, 64, 64, 3, True) > ozimmu.workspace_bytes(64, 64, 64, 3, False)
+    # a complex product in one launch keeps nothing of the size of C; with k-blocking two planes of it wait in the workspace
+    slices = 2 * 7 * (4096 + 4096) * 256
+    assert slices < ozimmu.workspace_bytes(4096, 4096, 256, 7, True) < slices + (1 << 20)
+    slices = 2 * 2 * (4096 + 4096) * 65568
+    assert ozimmu.workspace_bytes(4096, 4096, 65568, 2, True) >= slices + 2 * 8 * 4096 * 4096
 
 
 def test_slice_offset_is_a_bijection_with_contiguous_fragments():
