@@ -174,7 +174,9 @@ ozimmu_status_t ozimmu_dgemm_static(int64_t m, int64_t n, int64_t k, const doubl
 /*
  * The stages of ozimmu_dgemm run one at a time, for per-stage timing and profiling
  * (the time breakdown of Section 4.3): stage 0 = split A, 1 = split B, 2 = slice products
- * with the fused FP64 sum. Stages must be run in order with the same arguments.
+ * with the fused FP64 sum. Stages must be run in order with the same arguments. The result is that of
+ * ozimmu_dgemm, bit for bit, and so are the kernels, except that ozimmu_dgemm splits both operands by one launch where
+ * they are small (about 64 MiB together, k <= 2048): the two stages are then slower than what the call does.
  */
 ozimmu_status_t ozimmu_dgemm_stage(int stage, int64_t m, int64_t n, int64_t k, const double* A,
                                    int64_t lda, const double* B, int64_t ldb, double* C,

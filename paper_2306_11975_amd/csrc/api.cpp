@@ -21,7 +21,7 @@ bool dims_ok(int64_t a, int64_t b, int64_t c) {
 
 // A diagonal d = p + q holds d - 1 pairs; the longest one (d = s + 1) sums s * k_pad products
 // per output element. If that exceeds the INT32 block the kernel moves its INT32 sums into INT64
-// sums in the workspace every block_steps steps of 32 products per pair (k-blocking).
+// sums in the workspace every block_steps slabs of 32 products per pair (k-blocking).
 bool needs_wide(int s, int64_t k_pad) { return (int64_t)s * k_pad > OZIMMU_INT32_BLOCK; }
 int block_steps_for(int s) { return OZIMMU_INT32_BLOCK / (s * kSlab); }
 
@@ -163,8 +163,6 @@ hipError_t split_complex_rows(const double* Z, int64_t ld, int64_t rows, int64_t
     return e;
 }
 
-// One real Ozaki product from already split planes: G = sum over diagonals, combined into C as
-// c_mode says (C_lo != nullptr: double-double sum into C, C_lo).
 // An operand of a product as it is stored: `count` vectors along k, rows or columns of a row-major array.
 struct Stored {
     const double* X;
@@ -230,6 +228,8 @@ void set_split(GemmArgs& g, const Layout& L, int s, const Room& room) {
     if (sp.splits > 1) g.block_steps = 0;   // every part fits INT32 sums
 }
 
+// One real Ozaki product from already split planes: G = sum over diagonals, combined into C as
+// c_mode says (C_lo != nullptr: double-double sum into C, C_lo).
 hipError_t run_product(const Layout& L, int64_t m, int64_t n, int s, unsigned char* ws, int plane_a, int plane_b,
                        double* C, int64_t ldc, int c_mode, hipStream_t st, const Room& room, double alpha = 1.0, double beta = 0.0,
                        double* C_lo = nullptr, double* Zr = nullptr, double* Cz = nullptr, int64_t ldcz = 0) {
@@ -608,6 +608,10 @@ ozimmu_status_t ozimmu_dgemm_stage(int stage, int64_t m, int64_t n, int64_t k, c
     unsigned char* ws = static_cast<unsigned char*>(workspace);
     switch (stage) {
         case 0:
+            if (split_rows_in_pieces(L.m_pad, L.k_pad))
+                return hip_status(launch_split_rows_pieces(A, lda, m, k, num_slices, reinterpret_cast<int8_t*>(ws + L.off_sa[0]), L.m_pad, L.k_pad,
+                                                           reinterpret_cast<int32_t*>(ws + L.off_ea[0]),
+                                                           reinterpret_cast<unsigned long long*>(ws + L.off_colmax), st));
             return hip_status(launch_split_rows(A, lda, 1, m, k, num_slices,
                                                 reinterpret_cast<int8_t*>(ws + L.off_sa[0]), L.m_pad, L.k_pad,
                                                 reinterpret_cast<int32_t*>(ws + L.off_ea[0]), st));

@@ -338,6 +338,19 @@ def test_degenerate_shapes():
     torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("m,n,k,s", [(300, 200, 500, 8), (2100, 2000, 2200, 6), (40, 60, 20000, 3)])
+def test_stages_are_the_call(m, n, k, s):
+    """Operands that the call splits by one launch, by one each, and rows too long for the register cache, few of them."""
+    A, B = wl.phi_pair(m, n, k, 1.0, seed=12)
+    dA, dB = dev(A), dev(B)
+    C = torch.full((m, n), float("nan"), dtype=torch.float64, device=DEV)
+    ws = ozimmu.alloc_workspace(m, n, k, s)
+    for stage in range(3):
+        ozimmu.dgemm_stage(stage, dA, dB, C, s, ws)
+    torch.cuda.synchronize()
+    assert np.array_equal(bits(C.cpu().numpy()), bits(gpu_dgemm(A, B, s)))
+
+
 def test_two_runs_identical_and_stream_argument():
     A, B = wl.phi_pair(300, 300, 700, 1.0, seed=11)
     C1 = gpu_dgemm(A, B, 8)
