@@ -233,6 +233,8 @@ def main():
     ws = ozimmu.alloc_workspace(m, n, k, s)
     stream = torch.cuda.current_stream()
 
+    # the three stages are what ozimmu_dgemm runs for operands of more than 64 MiB, the default workload's among them
+    # (smaller ones it splits by one launch, which these stages do not time)
     def step(events=None):
         ozimmu.dgemm_stage(0, A, B, C, s, ws)
         if events is not None:
@@ -311,12 +313,13 @@ def main():
         z16, z16_mhz = ozimmu.probe_int8_mfma(0, shape=1)
         r16, r16_mhz = ozimmu.probe_int8_mfma(2, shape=1)
         out["context_int8_mfma_issue_loop"] = {
+            # 32x32x32, the other shape
             "zero_operands": {"TOPs": z_tops, "shader_MHz": z_mhz},
             "random_7bit_operands": {"TOPs": r_tops, "shader_MHz": r_mhz},
-            "kernel_vs_random_7bit_loop": achieved_tops / r_tops if r_tops > 0 else None,
-            # the shape that the product kernel uses; the two above and the next key are of 32x32x32
+            # the shape that the product kernel uses, and the kernel's rate against its loop
             "mfma_16x16x64": {"zero_operands": {"TOPs": z16, "shader_MHz": z16_mhz},
                               "random_7bit_operands": {"TOPs": r16, "shader_MHz": r16_mhz}},
+            "kernel_vs_random_7bit_loop": achieved_tops / r16 if r16 > 0 else None,
         }
         # context only: the vendor's own INT8 -> INT32 GEMM (what torch._int_mm dispatches to) at the same
         # m, n, k on operands distributed like the slices, and on zeros: it shows the same dependence of the

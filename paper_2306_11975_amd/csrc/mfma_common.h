@@ -133,9 +133,9 @@ __device__ __forceinline__ void mfma16_acc(const v4i& a, const v4i& b, v4i& c) {
 __device__ __forceinline__ void mfma16_new(const v4i& a, const v4i& b, v4i& c) {
     asm("v_mfma_i32_16x16x64_i8 %0, %1, %2, 0" : "=a"(c) : "v"(a), "v"(b));
 }
-// The same with a direct load (dma_load16 below) issued in the shadow of the MFMA, which with the wait states behind it
-// stands between the writes of M0 and of src and the load. Completion is awaited by an explicit vmcnt only. (M0 is written here; the compiler refuses it as a clobber. The build checks the generated assembly
-// for any other use of M0 in these kernels.)
+// The same with a direct load (dma_load16 above) issued in the shadow of the MFMA, which with the wait states behind it
+// stands between the writes of M0 and of src and the load. Completion is awaited by an explicit vmcnt only. (M0 is written
+// here; the compiler refuses it as a clobber. The build checks the generated assembly for any other use of M0 in these kernels.)
 template <unsigned IMM>
 __device__ __forceinline__ void mfma16_acc_and_load(const v4i& a, const v4i& b, v4i& c, const void* src, unsigned voff, unsigned lds_addr) {
     asm volatile(

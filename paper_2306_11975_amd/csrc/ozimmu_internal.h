@@ -9,16 +9,16 @@
 namespace ozimmu {
 
 constexpr int kRowAlign = OZIMMU_ROW_ALIGN;   // slice rows are padded to a multiple of this (128)
-constexpr int kSlab = OZIMMU_K_ALIGN;         // k-extent of one MFMA operand fragment and of one pipeline step (32)
+constexpr int kSlab = OZIMMU_K_ALIGN;         // k-extent of a fragment of a slice tensor (32); a step of the walk takes two
 constexpr int kFragRows = 32;                 // rows of one fragment
-constexpr int kFragBytes = kFragRows * kSlab; // 1 KiB: what one wave-wide direct load moves and one ds_read_b128 reads
+constexpr int kFragBytes = kFragRows * kSlab; // 1 KiB: what one wave-wide direct load moves
 constexpr int kBand = 8;                      // anti-diagonals whose INT32 sums a wavefront holds at a time
 
 static inline int64_t round_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 
-// Wavefront grid of the product kernel: 2 x 4 wavefronts of 32 x 32 outputs (a 64 x 128 tile of C) while two
-// pipeline stages of all slices fit the LDS, 2 x 2 (64 x 64) beyond. `small`: 2 x 2 also for up to nine slices,
-// two such workgroups per compute unit (see use_small_tiles).
+// Wavefront grid of the product kernel: 2 x 4 wavefronts of 32 x 32 outputs (a 64 x 128 tile of C) up to thirteen slices, whose
+// steps of the walk (one stage and at most a part of a second) fit the LDS, 2 x 2 (64 x 64) beyond. `small`: 2 x 2 also for
+// up to nine slices, two such workgroups per compute unit (see use_small_tiles).
 static inline void tile_waves(int s, bool small, int* wm, int* wn) {
     *wm = 2;
     *wn = (s > 13 || (small && s <= 9)) ? 2 : 4;
@@ -50,7 +50,7 @@ struct GemmArgs {
     int splits;              // workgroups per tile, each with split_slabs slabs of the walk (1: one, the whole walk)
     int split_slabs;         // (even)
     int* partial;            // splits > 1: their INT32 sums, [split][slice count][tile][16][threads of a tile]
-    int block_steps;         // steps after which the INT32 sums are moved into the INT64 sums in D (0: never)
+    int block_steps;         // slabs after which the INT32 sums are moved into the INT64 sums in D (0: never)
     long long* D;            // INT64 diagonal sums (k-blocking only)
     int32_t* P;              // pair mode (P != nullptr): raw INT32 product of the slices SA, SB point at
     int64_t ldp;
@@ -58,10 +58,9 @@ struct GemmArgs {
     int64_t ldc;             // in doubles
     int c_mode;              // 0: C = G, 1: C = C + G, 2: C = C - G, 3: C = alpha G (+ beta C if beta != 0),
                              // 4: (Zr, C + G) -> Cz as interleaved (re, im) pairs (C is read only)
-    double* Zr;              // c_mode 4: finished real parts, same shape and leading dimension as C (complex
-                             // mode: the plane the real part is formed in)
-    double* Cz;              // c_mode 4: complex output
-    int64_t ldcz;            // c_mode 4: its leading dimension in complex elements
+    double* Zr;              // c_mode 4: finished real parts, same shape and leading dimension as C
+    double* Cz;              // c_mode 4 and complex mode: complex output
+    int64_t ldcz;            // its leading dimension in complex elements
     double alpha, beta;      // c_mode 3 only
     double* C_lo;            // low parts of a double-double result (double-double summing-up only)
     const int32_t* EA;
@@ -162,7 +161,7 @@ hipError_t launch_loss_scan_cols_complex_small(const double* B, int64_t ldb, int
                                                unsigned long long* sums_re, unsigned long long* sums_im, hipStream_t st);
 // Slice products of the pairs p + q <= s + 1 with the FP64 sum. mode 0: FP64 sum; 1: double-double sum
 // into C, C_lo; 2: the four real products of a complex one in one launch (no k-blocking: block_steps == 0),
-// real part formed in the plane Zr, imaginary part in the plane C, result interleaved in Cz.
+// written to Cz as (re, im) pairs. splits > 1: the launch that adds the parts' sums up follows.
 hipError_t launch_slice_gemm(const GemmArgs& args, int s, int mode, hipStream_t st);
 // Slice-count scan: adds, for s = 1 .. 16, the mantissa bits s slices would lose into sums[s - 1].
 hipError_t launch_loss_scan_rows(const double* A, int64_t lda, int inc, int64_t m, int64_t k,
