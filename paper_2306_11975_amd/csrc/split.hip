@@ -1096,14 +1096,15 @@ static bool long_rows(const SplitOperand& a, const SplitOperand& b, int planes, 
     const int64_t of_rows = ((a.by_cols ? 0 : a.padded) + (b.by_cols ? 0 : b.padded)) * k_pad * planes;
     return planes == 2 ? k_pad >= 256 && of_rows >= (int64_t)5 << 19 : of_rows >= (int64_t)(k_pad >= 256 ? 1 : 2) << 20;
 }
-static PairShape pair_shape(const SplitOperand& a, const SplitOperand& b, int planes, int64_t k_pad) {
+static PairShape pair_shape(const SplitOperand& a, const SplitOperand& b, int planes, int64_t k_pad, int s, bool counting) {
     const bool two = k_pad > 1024, any_cols = a.by_cols || b.by_cols;
     PairShape p{};
     p.waves = two ? 16 : (unsigned)((k_pad + 63) / 64);   // sixteen positions of a column to a thread
     p.row_words = two ? 2 : 1;
     // Rows of some size are read four words to a thread, for four times the loads in flight: by as few wavefronts as that asks
-    // for, or, beside columns, which need the others, by workgroups of several groups of four rows.
-    if (long_rows(a, b, planes, k_pad)) {
+    // for, or, beside columns, which need the others, by workgroups of several groups of four rows. (Not where more than nine
+    // slices are cut and counted: the registers for four words are missing, 2048^3 at twelve 464 -> 467 us.)
+    if (long_rows(a, b, planes, k_pad) && !(s > 9 && counting)) {
         const unsigned segments = (unsigned)((k_pad + 255) / 256);   // wavefronts along a row
         p.row_words = 4;
         p.row_shift = !any_cols ? 0 : two ? 1 : 2;
@@ -1120,7 +1121,7 @@ static PairShape pair_shape(const SplitOperand& a, const SplitOperand& b, int pl
 bool split_pair_applies(const SplitOperand& a, const SplitOperand& b, int planes, int64_t k_pad, int s, bool counting) {
     if (k_pad < 1 || k_pad > (planes == 2 ? 1024 : 2048)) return false;
     if (planes == 2 && ((reinterpret_cast<uintptr_t>(a.X) | reinterpret_cast<uintptr_t>(b.X)) % 16 != 0)) return false;
-    const PairShape shape = pair_shape(a, b, planes, k_pad);
+    const PairShape shape = pair_shape(a, b, planes, k_pad, s, counting);
     const int64_t blocks = (int64_t)shape.blocks[0] + shape.blocks[1];
     if (counting && (size_t)blocks * kScanCounters * planes * sizeof(unsigned) > 2 * scan_slots_bytes(planes)) return false;
     // Complex rows of more than nine slices: four words of both planes leave no registers for the cut, one word too few loads in
@@ -1137,7 +1138,7 @@ bool split_pair_applies(const SplitOperand& a, const SplitOperand& b, int planes
 hipError_t launch_split_pair(const SplitOperand& a, const SplitOperand& b, int planes, int64_t k, int64_t k_pad, int s, hipStream_t st,
                              unsigned* partials, unsigned long long* sums_a, unsigned long long* sums_b) {
     if (!split_pair_applies(a, b, planes, k_pad, s, partials != nullptr)) return hipErrorInvalidValue;
-    const PairShape shape = pair_shape(a, b, planes, k_pad);
+    const PairShape shape = pair_shape(a, b, planes, k_pad, s, partials != nullptr);
     auto side = [&](const SplitOperand& x, int i) {
         SplitSide y{};
         y.X = x.X;
@@ -1161,8 +1162,9 @@ hipError_t launch_split_pair(const SplitOperand& a, const SplitOperand& b, int p
     const dim3 grid(sa.blocks + sb.blocks), block(64 * shape.waves);
 #define OZ_PAIR(W, SC, PL, R) split_pair_kernel<W, SC, PL, R><<<grid, block, 0, st>>>(sa, sb, (int)k, (int)k_pad, s, partials, scan.edge_g, scan.edge_h)
 #define OZ_PAIRS(W, SC) do { \
-        if (planes == 2) { if (shape.row_words == 4) OZ_PAIR(W, SC, 2, 4); else OZ_PAIR(W, SC, 2, 1); } \
-        else if (shape.row_words == 4) OZ_PAIR(W, SC, 1, 4); else if (shape.row_words == 2) OZ_PAIR(W, SC, 1, 2); else OZ_PAIR(W, SC, 1, 1); \
+        if (planes == 2) { if (!W && shape.row_words == 4) OZ_PAIR(W, SC, 2, W ? 1 : 4); else OZ_PAIR(W, SC, 2, 1); } \
+        else if (!(W && SC) && shape.row_words == 4) OZ_PAIR(W, SC, 1, W && SC ? 1 : 4); \
+        else if (shape.row_words == 2) OZ_PAIR(W, SC, 1, 2); else OZ_PAIR(W, SC, 1, 1); \
     } while (0)
     if (s > 9) { if (partials) OZ_PAIRS(true, true); else OZ_PAIRS(true, false); }
     else       { if (partials) OZ_PAIRS(false, true); else OZ_PAIRS(false, false); }
