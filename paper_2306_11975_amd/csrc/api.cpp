@@ -56,10 +56,9 @@ Layout make_layout(int64_t m, int64_t n, int64_t k, int s, bool cplx) {
     L.n_pad = round_up(n, kRowAlign);
     L.k_pad = round_up(k, kSlab);
     L.wide = needs_wide(s, L.k_pad);
-    // a complex product without k-blocking runs in one launch (on 64 x 64 tiles only where the large ones would leave
-    // compute units without a tile)
+    // a complex product without k-blocking runs in one launch
     const bool one_launch = cplx && !L.wide;
-    set_tiles(L, m, n, s, one_launch ? use_small_tiles(2 * m, 2 * n, INT64_MAX, s, L.wide) : use_small_tiles(m, n, L.k_pad, s, L.wide), one_launch);
+    set_tiles(L, m, n, s, one_launch ? use_small_tiles(2 * m, 2 * n, L.k_pad, s, L.wide) : use_small_tiles(m, n, L.k_pad, s, L.wide), one_launch);
     L.sa_bytes = (size_t)s * L.m_pad * L.k_pad;
     L.sb_bytes = (size_t)s * L.n_pad * L.k_pad;
     const int planes = cplx ? 2 : 1;

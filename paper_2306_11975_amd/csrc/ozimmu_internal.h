@@ -14,6 +14,8 @@ constexpr int kFragRows = 32;                 // rows of one fragment
 constexpr int kFragBytes = kFragRows * kSlab; // 1 KiB: what one wave-wide direct load moves
 constexpr int kBand = 8;                      // anti-diagonals whose INT32 sums a wavefront holds at a time
 
+constexpr int kComputeUnits = 256;            // MI355X
+
 static inline int64_t round_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 
 // Wavefront grid of the product kernel: 2 x 4 wavefronts of 32 x 32 outputs (a 64 x 128 tile of C) up to thirteen slices, whose
@@ -23,18 +25,29 @@ static inline void tile_waves(int s, bool small, int* wm, int* wn) {
     *wm = 2;
     *wn = (s > 13 || (small && s <= 9)) ? 2 : 4;
 }
-// Whether a product of this shape runs on 64 x 64 tiles, two workgroups per compute unit (a complex product in one
-// launch: asked with k_pad = INT64_MAX, i.e. only for the second reason): when the inner
-// dimension is short (a tile is then mostly start-up, fold and stores, and two independent workgroups overlap
-// one's with the other's matrix-core work) or when the 64 x 128 tiling leaves compute units without a tile.
-// Never with k-blocking, so that the workspace layout does not depend on it.
+// Whether a product of this shape runs on 64 x 64 tiles, two workgroups per compute unit, instead of 64 x 128 ones, one (a complex product
+// in one launch: asked with twice its rows and columns; never with k-blocking, so that the workspace layout does not depend on it).
+// Two independent workgroups overlap one's start, fold and stores with the other's matrix-core work, and a last round that is not full
+// costs less; the small tiles move a third more bytes into the LDS. So: small where the inner dimension is short or the large ones leave
+// compute units without a tile; otherwise by an estimate of the time, rounds times a tile's time, whose constants are fitted to 150
+// products of three to nine slices with k = 256 .. 8192 timed both ways (call, large -> small): complex 4096 x 4096 x 256 at seven slices
+// 456 -> 392 us, x 1024 at eight 1735 -> 1690, x 2048 at six 2080 -> 2140 (stays large); real 1500 x 1800 x 1500 at nine (two rounds
+// of large ones) 191 -> 153, 3500 x 3500 x 1536 at eight 529 -> 483, 8192 x 8192 x 8192 at eight 12910 -> 13090 (stays large). One round of
+// large tiles is one of small ones as well and takes as long (1024 x 2048 x 1024 70.5, 71.4).
 static inline bool use_small_tiles(int64_t m, int64_t n, int64_t k_pad, int s, bool wide) {
     if (s > 9 || wide) return false;
-    const int64_t big_tiles = ((m + 63) / 64) * ((n + 127) / 128);
-    return k_pad <= 512 || big_tiles < 256;
+    const int64_t row_tiles = (m + 63) / 64, large = row_tiles * ((n + 127) / 128), small = row_tiles * ((n + 63) / 64);
+    if (k_pad <= 512 || large < kComputeUnits) return true;
+    if (large == kComputeUnits) return false;
+    // a step of a round, and what a step of the small tiles takes more (five and six slices: their loads are covered least)
+    const double step_us = 0.08 * (s * (s + 1) / 2) + 0.17, more = s == 9 ? -0.01 : s == 8 ? 0.012 : s == 7 ? 0.015 : 0.065;
+    const double walk_us = (double)((k_pad + 63) / 64) * step_us, ends_us = 3.0, ends_alone_us = 5.0;
+    // a last round of small tiles with a compute unit to each takes 0.6 of one with two
+    const int64_t pairs = 2 * kComputeUnits, rest = small % pairs;
+    const double small_rounds = (double)(small / pairs) + (rest == 0 ? 0.0 : rest <= kComputeUnits ? 0.6 : 1.0);
+    const double large_rounds = (double)((large + kComputeUnits - 1) / kComputeUnits);
+    return small_rounds * (walk_us * (1.0 + more) + ends_us) < large_rounds * (walk_us + ends_alone_us);
 }
-
-constexpr int kComputeUnits = 256;            // MI355X
 
 // Arguments of the slice-product kernel. One launch covers every tile of C.
 struct GemmArgs {

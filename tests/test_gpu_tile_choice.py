@@ -1,0 +1,48 @@
+"""Either side of the rule that picks 64 x 64 tiles by an estimate (more than one round of the larger ones, k > 512), and complex products
+on both, against the oracle on sampled rows, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2306_11975_amd import ozimmu
+from paper_2306_11975_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def bits(x):
+    return np.ascontiguousarray(x).view(np.uint64)
+
+
+def sampled(m):
+    """A row of every 16: every fragment and, complex, every 32-row tile is among them, and the last."""
+    rows = list(range(3, m, 16)) + [m - 1]
+    return torch.tensor(sorted(set(rows)), device="cuda")
+
+
+# just beyond one round of 64 x 128 tiles (257 .. 288 of them); two rounds of either; odd sizes, odd numbers of slabs
+@pytest.mark.parametrize("m,n,k,s,cols", [(1030, 2050, 545, 9, 64), (1030, 2050, 545, 8, 64), (1601, 1409, 700, 3, 64), (2049, 1111, 513, 5, 64),
+                                          (1024, 4096, 2300, 6, 128), (1024, 4096, 576, 6, 64), (1500, 1800, 1033, 7, 64), (2048, 2048, 4100, 7, 128)])
+def test_real_products_across_the_estimate(m, n, k, s, cols):
+    assert ozimmu.launch_plan(m, n, k, s)["tile_cols"] == cols
+    A, B = wl.phi_matrix_device(m, k, 1.0, 11), wl.phi_matrix_device(k, n, 1.0, 12)
+    C = torch.full((m, n), float("nan"), dtype=torch.float64, device="cuda")
+    ozimmu.dgemm(A, B, C, s, ozimmu.alloc_workspace(m, n, k, s))
+    rows = sampled(m)[::4]
+    want = oracle.dgemm(A[rows].cpu().numpy(), B.cpu().numpy(), s)
+    assert not torch.isnan(C).any()
+    assert np.array_equal(bits(C[rows].cpu().numpy()), bits(want))
+
+
+# complex: 64 x 64 tiles hold 32 x 32 complex elements; more than 256 of the larger tiles each, so that k and the slice count decide
+@pytest.mark.parametrize("m,n,k,s", [(520, 1030, 33, 1), (520, 1030, 100, 7), (511, 1057, 512, 9), (530, 1000, 700, 8), (515, 1030, 1600, 5), (520, 1030, 64, 10)])
+def test_complex_products_on_small_and_large_tiles(m, n, k, s):
+    A, B = wl.gaussian_complex_device(m, k, 21), wl.gaussian_complex_device(k, n, 22)
+    C = torch.full((m, n + 2), float("nan"), dtype=torch.complex128, device="cuda")
+    ozimmu.zgemm(A, B, C[:, :n], s, ozimmu.alloc_workspace(m, n, k, s, True))
+    rows = sampled(m)
+    want = oracle.zgemm(A[rows].cpu().numpy(), B.cpu().numpy(), s)
+    got = C.cpu().numpy()
+    assert np.array_equal(bits(got[rows.cpu().numpy()][:, :n]), bits(want))
+    assert np.isnan(got[:, n:]).all() and not np.isnan(got[:, :n]).any()
