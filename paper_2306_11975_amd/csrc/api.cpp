@@ -927,7 +927,8 @@ ozimmu_status_t ozimmu_launch_plan(int64_t m, int64_t n, int64_t k, int num_slic
     plan->tile_cols = L.tile_cols;
     const int parts = k > 0 ? choose_split(L, num_slices, split_available(L.total)).splits : 1;
     plan->workgroups = (int64_t)L.tiles_m * L.tiles_n * parts;
-    plan->bands = num_slices > kBand ? 2 : 1;
+    const bool alone = L.tile_cols == 64 && (num_slices > 9 || plan->workgroups <= kComputeUnits);
+    plan->bands = num_slices > resident_diagonals(num_slices, alone) ? 2 : 1;
     plan->int32_block_steps = L.wide && parts == 1 ? block_steps_for(num_slices) : 0;
     return OZIMMU_OK;
 }

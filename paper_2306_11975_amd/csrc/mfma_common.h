@@ -165,9 +165,9 @@ __device__ __forceinline__ void last_mfma_issued() {
 // acc = RN(acc + S_e 2^(-7 (e + 2))) for the diagonals of a band, least significant first. The
 // product of an integer below 2^31 and a power of two is exact, so the fused operation rounds
 // exactly like the sum it stands for.
-template <int SB>
-__device__ __forceinline__ void fold_band(double (&sum)[16], const v4i (&acc)[kBand][4]) {
-    constexpr int ND = SB < kBand ? SB : kBand, E0 = SB - ND;
+template <int SB, int KB>
+__device__ __forceinline__ void fold_band(double (&sum)[16], const v4i (&acc)[KB][4]) {
+    constexpr int ND = SB < KB ? SB : KB, E0 = SB - ND;
     mfma_results_ready();
 #pragma unroll
     for (int e = SB - 1; e >= E0; --e) {

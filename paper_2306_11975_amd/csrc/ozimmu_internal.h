@@ -12,7 +12,11 @@ constexpr int kRowAlign = OZIMMU_ROW_ALIGN;   // slice rows are padded to a mult
 constexpr int kSlab = OZIMMU_K_ALIGN;         // k-extent of a fragment of a slice tensor (32); a step of the walk takes two
 constexpr int kFragRows = 32;                 // rows of one fragment
 constexpr int kFragBytes = kFragRows * kSlab; // 1 KiB: what one wave-wide direct load moves
-constexpr int kBand = 8;                      // anti-diagonals whose INT32 sums a wavefront holds at a time
+constexpr int kBand = 8;                      // anti-diagonals whose INT32 sums a wavefront holds at a time where two wavefronts share a SIMD
+// The same where a wavefront has a SIMD to itself (64 x 64 tiles, one workgroup to a compute unit): twice the registers, and all diagonals
+// of 9, 14 and 15 slices are walked at once, which saves the second walk its loads, barriers and start (per call: 1024^3 at nine slices 49.9 -> 46.7 us,
+// 2000 x 1500 x 1000 at fifteen 258 -> 237, double-double 1501 x 1301 x 1107 at fourteen 185.6 -> 168.6; sixteen keep two bands of eight).
+constexpr int resident_diagonals(int s, bool alone) { return alone && (s == 9 || s == 14 || s == 15) ? s : kBand; }
 
 constexpr int kComputeUnits = 256;            // MI355X
 

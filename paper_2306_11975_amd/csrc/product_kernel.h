@@ -14,7 +14,8 @@
 //
 // More than eight slices: the diagonals are walked in two bands, the upper eight first, then the
 // remaining s - 8 (which are exactly the diagonals of the s - 8 slice problem); the FP64 sum of the
-// first band waits in registers. Long k (more than 2^17 products per INT32 sum, cf. Section 2.4 on
+// first band waits in registers. Where a wavefront has a SIMD and its registers to itself one band holds all diagonals of 9, 14
+// and 15 slices (resident_diagonals). Long k (more than 2^17 products per INT32 sum, cf. Section 2.4 on
 // splitting long k): every block_steps slabs the INT32 sums are added into INT64 sums in the
 // workspace (k-blocking) and the FP64 sum is formed from those.
 //
@@ -67,9 +68,10 @@ constexpr int kStepBytes = 2 * kFragBytes;    // two slabs: what a step advances
 // buffer is filled again as soon as every wavefront has read it, and its loads have the time up to the other barrier to
 // land; one stage and at most a part of a second are enough, which is what lets a step be 64 positions long at up to
 // 13 slices.
-template <int SB, int WM, int WN, bool SOLO>
+// KB: diagonals that a wavefront's registers hold.
+template <int SB, int KB, int WM, int WN, bool SOLO>
 struct Band {
-    static constexpr int ND = SB < kBand ? SB : kBand;    // resident diagonals
+    static constexpr int ND = SB < KB ? SB : KB;          // resident diagonals
     static constexpr int E0 = SB - ND;                    // lowest one (e = p + q, 0-based; d = e + 2)
     static constexpr int NW = WM * WN;
     static constexpr int SLOT = (WM + WN) * kStepBytes;   // LDS of one slice of A and one of B
@@ -185,8 +187,9 @@ struct Band {
 
 template <int S, int WM, int WN, bool SOLO>
 struct Shape {
-    static constexpr int LDS1 = Band<S, WM, WN, SOLO>::LDS;
-    static constexpr int LDS2 = S > kBand ? Band<(S > kBand ? S - kBand : 1), WM, WN, SOLO>::LDS : 0;
+    static constexpr int KB = resident_diagonals(S, WM * WN == 4 && (S > 9 || SOLO));
+    static constexpr int LDS1 = Band<S, KB, WM, WN, SOLO>::LDS;
+    static constexpr int LDS2 = S > KB ? Band<(S > KB ? S - KB : 1), KB, WM, WN, SOLO>::LDS : 0;
     static constexpr int LDS = LDS1 > LDS2 ? LDS1 : LDS2;
 };
 
@@ -231,10 +234,10 @@ __device__ __forceinline__ unsigned operand_offset(int lane) {
 // The walk of one band over the slabs [w.t_begin, w.t_end): acc[e - E0] receives the pairs of diagonal e;
 // while_filling() is called once when the first loads are on their way, and clears acc; after_step(slabs done) is called
 // after every step (k-blocking hooks in there). HEAD: the number of slabs is odd, and acc need not be cleared. All LDS traffic of the walk is complete when it returns.
-template <int SB, int WM, int WN, bool SOLO, bool CPLX, bool HEAD, class WhileFilling, class AfterStep>
-__device__ __forceinline__ void band_walk(v4i (&acc)[kBand][4], const GemmArgs& g, const Walk& w, WhileFilling&& while_filling,
+template <int SB, int KB, int WM, int WN, bool SOLO, bool CPLX, bool HEAD, class WhileFilling, class AfterStep>
+__device__ __forceinline__ void band_walk(v4i (&acc)[KB][4], const GemmArgs& g, const Walk& w, WhileFilling&& while_filling,
                                           AfterStep&& after_step) {
-    using B = Band<SB, WM, WN, SOLO>;
+    using B = Band<SB, KB, WM, WN, SOLO>;
     constexpr int ND = B::ND, E0 = B::E0, Y = B::Y;
     static_assert(!CPLX || WM == 2, "one row group of a complex tile is real, one imaginary");
     const int slabs = w.t_end - w.t_begin;
@@ -583,9 +586,9 @@ __device__ __forceinline__ void dd_add(double& h, double& l, double t) {
     l = l2 - (hn - sh);
     h = hn;
 }
-template <int SB>
-__device__ __forceinline__ void fold_band_dd(double (&h)[16], double (&l)[16], const v4i (&acc)[kBand][4]) {
-    constexpr int ND = SB < kBand ? SB : kBand, E0 = SB - ND;
+template <int SB, int KB>
+__device__ __forceinline__ void fold_band_dd(double (&h)[16], double (&l)[16], const v4i (&acc)[KB][4]) {
+    constexpr int ND = SB < KB ? SB : KB, E0 = SB - ND;
     mfma_results_ready();
 #pragma unroll
     for (int e = SB - 1; e >= E0; --e) {
@@ -623,7 +626,8 @@ __attribute__((amdgpu_waves_per_eu((WM * WN == 4 && S <= 9 && !SOLO) ? 2 : WM * 
 void product_kernel(const GemmArgs g) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     constexpr int T = 64 * WM * WN;
-    constexpr int S2 = S > kBand ? S - kBand : 1;   // slice count of the second band (unused if S <= 8)
+    constexpr int KB = Shape<S, WM, WN, SOLO>::KB;
+    constexpr int S2 = S > KB ? S - KB : 1;         // slice count of the second band (unused if there is one)
     constexpr bool CPLX = MODE == kModeComplex;
     constexpr int NEX = CPLX ? 2 : 1;                     // exponent sets staged (one per plane)
     constexpr int TR = (CPLX ? 16 : 32) * WM, TC = (CPLX ? 16 : 32) * WN;   // tile of C (complex: in complex elements)
@@ -662,7 +666,7 @@ void product_kernel(const GemmArgs g) {
         if (pos < (is_a ? g.m : g.n)) my_exponent = E[pos];
     }
 
-    v4i acc[kBand][4];
+    v4i acc[KB][4];
     auto zero_acc = [&](int nd) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < nd; ++i)
@@ -678,7 +682,7 @@ void product_kernel(const GemmArgs g) {
         const int64_t diag_stride = num_tiles * 16 * T - 16 * T;
         mfma_results_ready();
 #pragma unroll
-        for (int i = 0; i < kBand; ++i) {
+        for (int i = 0; i < KB; ++i) {
             if (i < nd) {
 #pragma unroll
                 for (int u = 0; u < 16; ++u) {
@@ -864,16 +868,16 @@ void product_kernel(const GemmArgs g) {
     // the band's sums into the FP64 sum
     auto fold = [&](auto sb_tag) __attribute__((always_inline)) {
         if (!wide && !g.P) {
-            if constexpr (MODE == kModeDD) fold_band_dd<decltype(sb_tag)::value>(sum, lo, acc);
-            else fold_band<decltype(sb_tag)::value>(sum, acc);
+            if constexpr (MODE == kModeDD) fold_band_dd<decltype(sb_tag)::value, KB>(sum, lo, acc);
+            else fold_band<decltype(sb_tag)::value, KB>(sum, acc);
         }
     };
     auto walk = [&](auto sb_tag, auto&& while_filling) __attribute__((always_inline)) {
         constexpr int SB = decltype(sb_tag)::value;
-        using B = Band<SB, WM, WN, SOLO>;
+        using B = Band<SB, KB, WM, WN, SOLO>;
         first_block = true;
         until_flush = g.block_steps;
-        band_walk<SB, WM, WN, SOLO, CPLX, HEAD>(acc, g, w, while_filling, [&](int done) __attribute__((always_inline)) {
+        band_walk<SB, KB, WM, WN, SOLO, CPLX, HEAD>(acc, g, w, while_filling, [&](int done) __attribute__((always_inline)) {
             // a step adds two slabs: the block is full when it has no room for two more
             if (wide && ((until_flush -= 2) < 2 || done == w.t_end - w.t_begin)) {
                 flush(B::E0, B::ND, first_block);
@@ -889,7 +893,7 @@ void product_kernel(const GemmArgs g) {
     // One of several workgroups on a tile, each with a part of k: the INT32 sums go to the workspace as they are, where
     // fold_kernel adds them up. Thread t owns element t of every run, [split][diagonal][tile][u].
     auto put_partial = [&](auto sb_tag) __attribute__((always_inline)) {
-        using B = Band<decltype(sb_tag)::value, WM, WN, SOLO>;
+        using B = Band<decltype(sb_tag)::value, KB, WM, WN, SOLO>;
         mfma_results_ready();
         int* q = g.partial + ((((int64_t)split * S + B::E0) * num_tiles + tile_id) * 16) * T + (w.wave * 64 + lane_here());
 #pragma unroll
@@ -901,7 +905,7 @@ void product_kernel(const GemmArgs g) {
     };
     walk(std::integral_constant<int, S>{}, [&]() __attribute__((always_inline)) {
         if (w.tid < NEX * (TR + TC)) ex[w.tid] = my_exponent;
-        if constexpr (!HEAD) zero_acc(S < kBand ? S : kBand);
+        if constexpr (!HEAD) zero_acc(S < KB ? S : KB);
     });
     clear_sum();
     // a band's sums into the FP64 sum, or to where all parts' sums meet
@@ -909,21 +913,21 @@ void product_kernel(const GemmArgs g) {
         if (MODE != kModeDD && g.splits > 1) put_partial(sb_tag);
         else fold(sb_tag);
     };
-    if constexpr (S > kBand) {
+    if constexpr (S > KB) {
         // the first band is taken while the second one's first loads are on their way (before them where the sum takes
         // two registers per part: there is no room for both)
         if constexpr (MODE == kModeDD) take(std::integral_constant<int, S>{});
         walk(std::integral_constant<int, S2>{}, [&]() __attribute__((always_inline)) {
             if constexpr (MODE != kModeDD) take(std::integral_constant<int, S>{});
-            if constexpr (!HEAD) zero_acc(S2 < kBand ? S2 : kBand);
+            if constexpr (!HEAD) zero_acc(S2 < KB ? S2 : KB);
         });
     }
     if (MODE != kModeDD && g.splits > 1) {
-        put_partial(std::integral_constant<int, (S > kBand ? S2 : S)>{});
+        put_partial(std::integral_constant<int, (S > KB ? S2 : S)>{});
         return;
     }
     if constexpr (MODE == kModeReal) fetch_old(old_c, g.C, !g.P && c_mode_reads(g, g.c_mode));
-    fold(std::integral_constant<int, (S > kBand ? S2 : S)>{});
+    fold(std::integral_constant<int, (S > KB ? S2 : S)>{});
     finish_product();
 }
 

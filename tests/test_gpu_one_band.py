@@ -1,0 +1,62 @@
+"""9, 14 and 15 slices on 64 x 64 tiles with one workgroup to a compute unit, whose diagonals are all walked in one band: real, double-double
+and complex products against the oracle, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2306_11975_amd import ozimmu
+from paper_2306_11975_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def bits(x):
+    return np.ascontiguousarray(x).view(np.uint64)
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+# one slab, one step, a step and a slab, three slabs, an odd and an even number of slabs that fill the pipeline
+SIZES = [(64, 64, 1), (65, 63, 64), (1, 130, 65), (129, 66, 96), (70, 200, 1000), (64, 128, 513)]
+
+
+@pytest.mark.parametrize("s", [9, 14, 15])
+@pytest.mark.parametrize("m,n,k", SIZES)
+def test_real_and_double_double(m, n, k, s):
+    assert ozimmu.launch_plan(m, n, k, s)["bands"] == 1
+    A, B = wl.phi_pair(m, n, k, 1.0, seed=k + s)
+    dA, dB = dev(A), dev(B)
+    C = torch.full((m, n), float("nan"), dtype=torch.float64, device="cuda")
+    lo = torch.full_like(C, float("nan"))
+    ws = ozimmu.alloc_workspace(m, n, k, s)
+    ozimmu.dgemm(dA, dB, C, s, ws)
+    assert np.array_equal(bits(C.cpu().numpy()), bits(oracle.dgemm(A, B, s)))
+    C.fill_(float("nan"))
+    ozimmu.dgemm_dd(dA, dB, C, lo, s, ws)
+    hi_want, lo_want = oracle.dgemm_dd(A, B, s)
+    assert np.array_equal(bits(C.cpu().numpy()), bits(hi_want)) and np.array_equal(bits(lo.cpu().numpy()), bits(lo_want))
+
+
+@pytest.mark.parametrize("s", [9, 14, 15])
+@pytest.mark.parametrize("m,n,k", [(33, 200, 129), (64, 140, 1000)])
+def test_complex(m, n, k, s):
+    rng = np.random.default_rng(s + k)
+    A = rng.standard_normal((m, k)) + 1j * rng.standard_normal((m, k))
+    B = rng.standard_normal((k, n)) + 1j * rng.standard_normal((k, n))
+    C = torch.full((m, n), float("nan"), dtype=torch.complex128, device="cuda")
+    ozimmu.zgemm(dev(A), dev(B), C, s, ozimmu.alloc_workspace(m, n, k, s, True))
+    assert np.array_equal(bits(C.cpu().numpy()), bits(oracle.zgemm(A, B, s)))
+
+
+@pytest.mark.parametrize("s", [9, 15])
+def test_largest_sums(s):
+    """Every slice at its largest: the sums of all diagonals at once, up to the INT32 block's end."""
+    k = ozimmu.INT32_BLOCK // s // 64 * 64
+    A = np.full((3, k), 1.0 - 2.0 ** -53)
+    B = np.full((k, 70), 1.0 - 2.0 ** -53)
+    C = torch.full((3, 70), float("nan"), dtype=torch.float64, device="cuda")
+    ozimmu.dgemm(dev(A), dev(B), C, s, ozimmu.alloc_workspace(3, 70, k, s))
+    assert np.array_equal(bits(C.cpu().numpy()), bits(oracle.dgemm(A, B, s)))
