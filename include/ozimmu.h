@@ -186,11 +186,12 @@ ozimmu_status_t ozimmu_dgemm_stage(int stage, int64_t m, int64_t n, int64_t k, c
 /*
  * How ozimmu_dgemm runs a shape with a workspace of ozimmu_workspace_bytes, on the host only (nothing is launched;
  * for tests and for callers who want to know): the tile of C one workgroup owns, or shares with others that walk other
- * parts of k (64 x 128; 64 x 64 from fourteen slices on, and up to nine slices when k <= 512, when fewer than 256 of the
- * larger tiles exist, or when an estimate has two of the smaller ones at a time on a compute unit ahead), the number of workgroups of the slice products (a multiple of the number of tiles where
+ * parts of k (64 x 128; 64 x 64 from fourteen slices on, up to nine slices when k <= 512, when fewer than 256 of the
+ * larger tiles exist, or when an estimate has two of the smaller ones at a time on a compute unit ahead, and from eleven to thirteen
+ * when they fill the rounds better), the number of workgroups of the slice products (a multiple of the number of tiles where
  * they share tiles; a second launch then adds their sums up), the number of bands the anti-diagonals are walked in (a
  * wavefront holds the INT32 sums of at most eight diagonals at a time, fifteen where it has a SIMD to itself: 2 bands beyond eight
- * slices, but for 9, 14 and 15 on 64 x 64 tiles with one workgroup to a compute unit), and
+ * slices, but for 9 and 11 to 15 on 64 x 64 tiles with one workgroup to a compute unit), and
  * int32_block_steps = the largest number of slabs of OZIMMU_K_ALIGN positions after which the INT32 sums are moved into
  * INT64 sums (k-blocking; the walk takes two slabs at a time), 0 if all products of a diagonal that one workgroup adds
  * up fit one INT32 sum. With a smaller workspace that the call still accepts, fewer workgroups share a tile, or none

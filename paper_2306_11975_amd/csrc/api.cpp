@@ -586,7 +586,7 @@ ozimmu_status_t ozimmu_workspace_bytes(int64_t m, int64_t n, int64_t k, int num_
     if (!bytes) return OZIMMU_ERR_NULL;
     Layout L = make_layout(m, n, k, num_slices, is_complex != 0);
     size_t room = split_room(L, num_slices, L.total);
-    if (!is_complex) {   // a double-double product runs on the large tiles
+    if (!is_complex && num_slices <= 9) {   // a double-double product then runs on the large tiles
         set_tiles(L, m, n, num_slices, false, false);
         room = std::max(room, split_room(L, num_slices, L.total));
     }
@@ -914,7 +914,7 @@ ozimmu_status_t ozimmu_dgemm_dd(int64_t m, int64_t n, int64_t k, const double* A
     unsigned char* ws = static_cast<unsigned char*>(workspace);
     const hipError_t e = split_operands(L, false, Stored{A, lda, m, false, false}, Stored{B, ldb, n, true, false}, k, num_slices, ws, st);
     if (e != hipSuccess) return OZIMMU_ERR_HIP;
-    set_tiles(L, m, n, num_slices, false, false);   // the double-double kernels exist for the large tiles only
+    if (num_slices <= 9) set_tiles(L, m, n, num_slices, false, false);   // the double-double kernels of so few slices exist for the large tiles only
     return hip_status(run_product(L, m, n, num_slices, ws, 0, 0, C_hi, ldc, 0, st, room_behind(ws, L.total, workspace_bytes), 1.0, 0.0, C_lo));
 }
 

@@ -14,9 +14,9 @@ constexpr int kFragRows = 32;                 // rows of one fragment
 constexpr int kFragBytes = kFragRows * kSlab; // 1 KiB: what one wave-wide direct load moves
 constexpr int kBand = 8;                      // anti-diagonals whose INT32 sums a wavefront holds at a time where two wavefronts share a SIMD
 // The same where a wavefront has a SIMD to itself (64 x 64 tiles, one workgroup to a compute unit): twice the registers, and all diagonals
-// of 9, 14 and 15 slices are walked at once, which saves the second walk its loads, barriers and start (per call: 1024^3 at nine slices 49.9 -> 46.7 us,
+// of nine and of eleven to fifteen slices are walked at once, which saves the second walk its loads, barriers and start (per call: 1024^3 at nine slices 49.9 -> 46.7 us,
 // 2000 x 1500 x 1000 at fifteen 258 -> 237, double-double 1501 x 1301 x 1107 at fourteen 185.6 -> 168.6; sixteen keep two bands of eight).
-constexpr int resident_diagonals(int s, bool alone) { return alone && (s == 9 || s == 14 || s == 15) ? s : kBand; }
+constexpr int resident_diagonals(int s, bool alone) { return alone && (s == 9 || (s >= 11 && s <= 15)) ? s : kBand; }
 
 constexpr int kComputeUnits = 256;            // MI355X
 
@@ -24,33 +24,41 @@ static inline int64_t round_up(int64_t x, int64_t a) { return (x + a - 1) / a * 
 
 // Wavefront grid of the product kernel: 2 x 4 wavefronts of 32 x 32 outputs (a 64 x 128 tile of C) up to thirteen slices, whose
 // steps of the walk (one stage and at most a part of a second) fit the LDS, 2 x 2 (64 x 64) beyond. `small`: 2 x 2 also for
-// up to nine slices, two such workgroups per compute unit (see use_small_tiles).
+// fewer, up to nine with two such workgroups per compute unit (see use_small_tiles).
 static inline void tile_waves(int s, bool small, int* wm, int* wn) {
     *wm = 2;
-    *wn = (s > 13 || (small && s <= 9)) ? 2 : 4;
+    *wn = s > 13 || small ? 2 : 4;
 }
-// Whether a product of this shape runs on 64 x 64 tiles, two workgroups per compute unit, instead of 64 x 128 ones, one (a complex product
+// Whether a product of this shape runs on 64 x 64 tiles instead of 64 x 128 ones (a complex product
 // in one launch: asked with twice its rows and columns; never with k-blocking, so that the workspace layout does not depend on it).
-// Two independent workgroups overlap one's start, fold and stores with the other's matrix-core work, and a last round that is not full
+// Up to nine slices: two workgroups per compute unit instead of one. Two independent workgroups overlap one's start, fold and stores with the other's matrix-core work, and a last round that is not full
 // costs less; the small tiles move a third more bytes into the LDS. So: small where the inner dimension is short or the large ones leave
 // compute units without a tile; otherwise by an estimate of the time, rounds times a tile's time, whose constants are fitted to 150
 // products of three to nine slices with k = 256 .. 8192 timed both ways (call, large -> small): complex 4096 x 4096 x 256 at seven slices
 // 456 -> 392 us, x 1024 at eight 1735 -> 1690, x 2048 at six 2080 -> 2140 (stays large); real 1500 x 1800 x 1500 at nine (two rounds
 // of large ones) 191 -> 153, 3500 x 3500 x 1536 at eight 529 -> 483, 8192 x 8192 x 8192 at eight 12910 -> 13090 (stays large). One round of
 // large tiles is one of small ones as well and takes as long (1024 x 2048 x 1024 70.5, 71.4).
+// Eleven to thirteen: one workgroup per compute unit of either, and the same rate (4096^3 at eleven 2822, 2838 us; 4096 x 4096 x 512 396, 413), so rounds decide:
+// 1024^3 at twelve 103 -> 71, 300^3 42 -> 28, 1500 x 1500 x 1000 205 -> 171, complex 300^3 48 -> 35. (Ten keep the large tiles, which the
+// interface's tests of ozimmu_launch_plan ask for.)
 static inline bool use_small_tiles(int64_t m, int64_t n, int64_t k_pad, int s, bool wide) {
-    if (s > 9 || wide) return false;
+    if (wide || s == 10 || s > 13) return false;
     const int64_t row_tiles = (m + 63) / 64, large = row_tiles * ((n + 127) / 128), small = row_tiles * ((n + 63) / 64);
+    const int64_t large_rounds = (large + kComputeUnits - 1) / kComputeUnits;
+    const double step_us = 0.08 * (s * (s + 1) / 2) + 0.17;   // of a round of 64 x 128 tiles
+    const double walk_us = (double)((k_pad + 63) / 64) * step_us, ends_us = 3.0, ends_alone_us = 5.0;
+    if (s > 10) {   // one workgroup of either to a compute unit, small tiles with half the work: what they save is rounds that are not full
+        const int64_t rounds = (small + kComputeUnits - 1) / kComputeUnits;
+        return (double)rounds * (0.5 * walk_us + ends_us) < (double)large_rounds * (walk_us + ends_us);
+    }
     if (k_pad <= 512 || large < kComputeUnits) return true;
     if (large == kComputeUnits) return false;
-    // a step of a round, and what a step of the small tiles takes more (five and six slices: their loads are covered least)
-    const double step_us = 0.08 * (s * (s + 1) / 2) + 0.17, more = s == 9 ? -0.01 : s == 8 ? 0.012 : s == 7 ? 0.015 : 0.065;
-    const double walk_us = (double)((k_pad + 63) / 64) * step_us, ends_us = 3.0, ends_alone_us = 5.0;
+    // what a step of the small tiles takes more (five and six slices: their loads are covered least)
+    const double more = s == 9 ? -0.01 : s == 8 ? 0.012 : s == 7 ? 0.015 : 0.065;
     // a last round of small tiles with a compute unit to each takes 0.6 of one with two
     const int64_t pairs = 2 * kComputeUnits, rest = small % pairs;
     const double small_rounds = (double)(small / pairs) + (rest == 0 ? 0.0 : rest <= kComputeUnits ? 0.6 : 1.0);
-    const double large_rounds = (double)((large + kComputeUnits - 1) / kComputeUnits);
-    return small_rounds * (walk_us * (1.0 + more) + ends_us) < large_rounds * (walk_us + ends_alone_us);
+    return small_rounds * (walk_us * (1.0 + more) + ends_us) < (double)large_rounds * (walk_us + ends_alone_us);
 }
 
 // Arguments of the slice-product kernel. One launch covers every tile of C.

@@ -14,8 +14,8 @@
 //
 // More than eight slices: the diagonals are walked in two bands, the upper eight first, then the
 // remaining s - 8 (which are exactly the diagonals of the s - 8 slice problem); the FP64 sum of the
-// first band waits in registers. Where a wavefront has a SIMD and its registers to itself one band holds all diagonals of 9, 14
-// and 15 slices (resident_diagonals). Long k (more than 2^17 products per INT32 sum, cf. Section 2.4 on
+// first band waits in registers. Where a wavefront has a SIMD and its registers to itself one band holds all diagonals of 9 and
+// of 11 to 15 slices (resident_diagonals). Long k (more than 2^17 products per INT32 sum, cf. Section 2.4 on
 // splitting long k): every block_steps slabs the INT32 sums are added into INT64 sums in the
 // workspace (k-blocking) and the FP64 sum is formed from those.
 //
@@ -1067,7 +1067,10 @@ hipError_t launch_for(const GemmArgs& g, int s, hipStream_t st) {
         OZ_CASE(1, 4) OZ_CASE(2, 4) OZ_CASE(3, 4) OZ_CASE(4, 4) OZ_CASE(5, 4) OZ_CASE(6, 4) OZ_CASE(7, 4) OZ_CASE(8, 4) OZ_CASE(9, 4)
 #undef OZ_CASE
 #define OZ_CASE(S_, WN_) case S_: return head ? launch_one<S_, 2, WN_, MODE, false, true>(g, st) : launch_one<S_, 2, WN_, MODE>(g, st);
-        OZ_CASE(10, 4) OZ_CASE(11, 4) OZ_CASE(12, 4) OZ_CASE(13, 4) OZ_CASE(14, 2) OZ_CASE(15, 2) OZ_CASE(16, 2)
+#define OZ_BOTH(S_) case S_: if (g.tile_cols == 64) return head ? launch_one<S_, 2, 2, MODE, false, true>(g, st) : launch_one<S_, 2, 2, MODE>(g, st); \
+                             return head ? launch_one<S_, 2, 4, MODE, false, true>(g, st) : launch_one<S_, 2, 4, MODE>(g, st);
+        OZ_CASE(10, 4) OZ_BOTH(11) OZ_BOTH(12) OZ_BOTH(13) OZ_CASE(14, 2) OZ_CASE(15, 2) OZ_CASE(16, 2)
+#undef OZ_BOTH
 #undef OZ_CASE
     }
     return hipErrorInvalidValue;

@@ -1,5 +1,5 @@
-"""9, 14 and 15 slices on 64 x 64 tiles with one workgroup to a compute unit, whose diagonals are all walked in one band: real, double-double
-and complex products against the oracle, bit for bit."""
+"""9 and 11 to 15 slices on 64 x 64 tiles with one workgroup to a compute unit, whose diagonals are all walked in one band: real, double-double
+and complex products against the oracle, bit for bit; and 11 to 13 on 64 x 128 tiles, where those fill their rounds."""
 import numpy as np
 import pytest
 import torch
@@ -23,7 +23,7 @@ def dev(a):
 SIZES = [(64, 64, 1), (65, 63, 64), (1, 130, 65), (129, 66, 96), (70, 200, 1000), (64, 128, 513)]
 
 
-@pytest.mark.parametrize("s", [9, 14, 15])
+@pytest.mark.parametrize("s", [9, 11, 12, 13, 14, 15])
 @pytest.mark.parametrize("m,n,k", SIZES)
 def test_real_and_double_double(m, n, k, s):
     assert ozimmu.launch_plan(m, n, k, s)["bands"] == 1
@@ -40,7 +40,7 @@ def test_real_and_double_double(m, n, k, s):
     assert np.array_equal(bits(C.cpu().numpy()), bits(hi_want)) and np.array_equal(bits(lo.cpu().numpy()), bits(lo_want))
 
 
-@pytest.mark.parametrize("s", [9, 14, 15])
+@pytest.mark.parametrize("s", [9, 11, 12, 13, 14, 15])
 @pytest.mark.parametrize("m,n,k", [(33, 200, 129), (64, 140, 1000)])
 def test_complex(m, n, k, s):
     rng = np.random.default_rng(s + k)
@@ -51,7 +51,7 @@ def test_complex(m, n, k, s):
     assert np.array_equal(bits(C.cpu().numpy()), bits(oracle.zgemm(A, B, s)))
 
 
-@pytest.mark.parametrize("s", [9, 15])
+@pytest.mark.parametrize("s", [9, 11, 15])
 def test_largest_sums(s):
     """Every slice at its largest: the sums of all diagonals at once, up to the INT32 block's end."""
     k = ozimmu.INT32_BLOCK // s // 64 * 64
@@ -60,3 +60,29 @@ def test_largest_sums(s):
     C = torch.full((3, 70), float("nan"), dtype=torch.float64, device="cuda")
     ozimmu.dgemm(dev(A), dev(B), C, s, ozimmu.alloc_workspace(3, 70, k, s))
     assert np.array_equal(bits(C.cpu().numpy()), bits(oracle.dgemm(A, B, s)))
+
+
+# 256 tiles of 64 x 128: one round of them, two of the smaller ones
+@pytest.mark.parametrize("s", [11, 12, 13])
+@pytest.mark.parametrize("k", [97, 128])
+def test_large_tiles(k, s):
+    m, n = 1024, 2048
+    assert ozimmu.launch_plan(m, n, k, s)["tile_cols"] == 128
+    A, B = wl.phi_matrix_device(m, k, 1.0, 31), wl.phi_matrix_device(k, n, 1.0, 32)
+    C = torch.full((m, n), float("nan"), dtype=torch.float64, device="cuda")
+    lo = torch.full_like(C, float("nan"))
+    rows = torch.arange(5, m, 48, device="cuda")
+    a, b = A[rows].cpu().numpy(), B.cpu().numpy()
+    ozimmu.dgemm(A, B, C, s, ozimmu.alloc_workspace(m, n, k, s))
+    assert np.array_equal(bits(C[rows].cpu().numpy()), bits(oracle.dgemm(a, b, s)))
+    ozimmu.dgemm_dd(A, B, C, lo, s, ozimmu.alloc_workspace(m, n, k, s))
+    hi_want, lo_want = oracle.dgemm_dd(a, b, s)
+    assert np.array_equal(bits(C[rows].cpu().numpy()), bits(hi_want)) and np.array_equal(bits(lo[rows].cpu().numpy()), bits(lo_want))
+    assert not torch.isnan(C).any()
+    Z = wl.gaussian_complex_device(m // 2, k, 33)
+    W = wl.gaussian_complex_device(k, n // 2, 34)
+    D = torch.full((m // 2, n // 2), float("nan"), dtype=torch.complex128, device="cuda")
+    ozimmu.zgemm(Z, W, D, s, ozimmu.alloc_workspace(m // 2, n // 2, k, s, True))
+    half = rows[rows < m // 2]
+    assert np.array_equal(bits(D[half].cpu().numpy()), bits(oracle.zgemm(Z[half].cpu().numpy(), W.cpu().numpy(), s)))
+    assert not torch.isnan(D).any()
