@@ -191,10 +191,16 @@ constexpr int gate_waves(int cls, int few) { return cls == 2 ? 16 : few == 3 ? 2
 // the zeros of the gate's fragments), so that eight such workgroups share a compute unit. A tile of so few bytes is all
 // latency, and twice as many in flight take two thirds of the time (2 qubits of 24: 552 -> 360 us).
 // FEW: 1 = four wavefronts, k <= 32; 2 = four wavefronts, two words to a lane; 3 = two wavefronts, k <= 16, n <= 8
-template <int S, int CLS, bool SCAN, int FEW = 0>
+// BOTH: a wavefront takes both row fragments of the tile, one after the other, with the gate's fragments it has loaded, instead of sharing the
+// columns with a wavefront on the other sixteen rows: half the fragments on their way from the L2, which were the largest part of the time beside the MFMAs
+// (6 qubits of 24 at eight slices 206 -> 189 us, at five 153 -> 137, at eleven 305 -> 296, 5 qubits 202 -> 192). Where that leaves a wavefront
+// no more walks than before (launch_gate), and with one step only: with more, both fragments' sums would have to be resident, and four wavefronts
+// to a SIMD have no registers for them.
+template <int S, int CLS, bool SCAN, int FEW, bool BOTH>
 __global__ __launch_bounds__(64 * gate_waves(CLS, FEW)) __attribute__((amdgpu_waves_per_eu(S <= kBand ? 4 : 2, S <= kBand ? 4 : 2)))
 void gate_kernel(const GateArgs g) {
     static_assert(!FEW || CLS == 0, "four wavefronts: the smallest class only");
+    static_assert(!BOTH || CLS == 0, "both row fragments: one step");
     constexpr bool WIDE = S > 9;   // the slices beyond the ninth come from the lower word of the fixed-point fraction
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     constexpr int KS = 1 << CLS, NFR = 8 << CLS, WAVES = gate_waves(CLS, FEW), NT = 64 * WAVES;
@@ -209,12 +215,13 @@ void gate_kernel(const GateArgs g) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t row_tile = (int64_t)blockIdx.x * kGateRows;
 
-    // ---- this wavefront's patches: rows 16 rf .. + 15 of the tile, complex columns 8 f .. 8 f + 7 for f = cg, cg + WAVES / 2, ...
-    const int rf = wave & 1, cg = wave >> 1;
-    const unsigned char* a_rd = lds + rf * FRAG + 16 * (FEW == 3 ? lane & 15 : lane);
+    // ---- this wavefront's patches: rows 16 rf .. + 15 of the tile, complex columns 8 f .. 8 f + 7 for f = cg, cg + CGS, ...
+    constexpr int CGS = BOTH ? WAVES : WAVES / 2, RF = BOTH ? 2 : 1;   // wavefronts side by side over the fragments of B; row fragments of each
+    const int rf0 = BOTH ? 0 : wave & 1, cg = BOTH ? wave : wave >> 1;
+    const unsigned char* a_rd = lds + rf0 * FRAG + 16 * (FEW == 3 ? lane & 15 : lane);
     constexpr int BSLICE = NFR * KS * kFragBytes, TENSOR = S * BSLICE;
-    auto read_a = [&](int plane, int p, int step) __attribute__((always_inline)) -> v4i {
-        return *reinterpret_cast<const v4i*>(a_rd + plane * PLANE + p * SLICE + step * 2 * FRAG);
+    auto read_a = [&](int rf, int plane, int p, int step) __attribute__((always_inline)) -> v4i {   // rf: from rf0 on
+        return *reinterpret_cast<const v4i*>(a_rd + rf * FRAG + plane * PLANE + p * SLICE + step * 2 * FRAG);
     };
     // fragments of the gate: a wave-uniform byte offset (tensor, fragment) plus the lane's 16 bytes, unsigned, so that the
     // loads take the tensor's address as their scalar base and a 32-bit register as offset
@@ -385,110 +392,113 @@ void gate_kernel(const GateArgs g) {
 
     // ---- the products
     // accumulator layout of the 16x16 MFMA: lane holds column (lane % 16); register u holds row 4 (lane / 16) + u
-    const int lrow0 = rf * 16 + 4 * (lane >> 4), c8 = lane & 7;
+    const int lrow_first = rf0 * 16 + 4 * (lane >> 4), c8 = lane & 7;
     const bool is_im = (lane & 8) != 0;
     // patches of this wavefront that hold a column of C at all (wave-uniform)
-    constexpr int CGS = WAVES / 2;   // wavefronts side by side over the fragments of B
     const int np = g.n > 8 * cg ? (g.n - 8 * cg - 1) / (8 * CGS) + 1 : 0;
     if (np == 0) return;
 
     v4i acc[S];
     v4i a[S];
-    double part[4];
+    double part[RF][4];
     // iteration it: patch it / 2, pass it % 2 (0: Ar with T1, 1: Ai with T2)
     for (int it = 0; it < 2 * np; ++it) {
         const int pass = it & 1, f = cg + CGS * (it >> 1);
         const int nit = it + 1 < 2 * np ? it + 1 : 0;   // (after the last one the first one's fragments again, unused)
         const unsigned b_this = b_base(pass, f), b_next = b_base(nit & 1, cg + CGS * (nit >> 1));
-        static_for<0, S>([&](auto pc) __attribute__((always_inline)) { a[decltype(pc)::value] = read_a(pass, decltype(pc)::value, 0); });
-        __builtin_amdgcn_sched_barrier(0);
-        // Group q of a step = the MFMAs of B fragment q with the A fragments S - 1 - q .. 0, each into the sum of
-        // its anti-diagonal p + q: b[q] and a[S - 1 - q] have their last use of the step there and are fetched again,
-        // in place, for the next step. Across the end of a walk only the B fragments are (they come from memory); the
-        // A fragments are read from LDS after the fold, which needs their registers.
-        static_for<0, KS>([&](auto sc) __attribute__((always_inline)) {
-            constexpr int step = decltype(sc)::value;
-            constexpr bool last_step = step == KS - 1;
-            static_for<0, S>([&](auto qc) __attribute__((always_inline)) {
-                constexpr int q = decltype(qc)::value, pmax = S - 1 - q;
-                static_for<0, pmax + 1>([&](auto ic) __attribute__((always_inline)) {
-                    constexpr int p = pmax - decltype(ic)::value;
-                    if constexpr (step == 0 && q == 0) acc[p] = mfma16(a[p], b[0], v4i{0, 0, 0, 0});
-                    else acc[p + q] = mfma16(a[p], b[q], acc[p + q]);
+        static_for<0, RF>([&](auto rc) __attribute__((always_inline)) {
+            constexpr int rf = decltype(rc)::value;
+            static_for<0, S>([&](auto pc) __attribute__((always_inline)) { a[decltype(pc)::value] = read_a(rf, pass, decltype(pc)::value, 0); });
+            __builtin_amdgcn_sched_barrier(0);
+            // Group q of a step = the MFMAs of B fragment q with the A fragments S - 1 - q .. 0, each into the sum of
+            // its anti-diagonal p + q: b[q] and a[S - 1 - q] have their last use of the step there and are fetched again,
+            // in place, for the next step. Across the end of a walk only the B fragments are (they come from memory); the
+            // A fragments are read from LDS after the fold, which needs their registers.
+            static_for<0, KS>([&](auto sc) __attribute__((always_inline)) {
+                constexpr int step = decltype(sc)::value;
+                constexpr bool last_step = step == KS - 1;
+                static_for<0, S>([&](auto qc) __attribute__((always_inline)) {
+                    constexpr int q = decltype(qc)::value, pmax = S - 1 - q;
+                    static_for<0, pmax + 1>([&](auto ic) __attribute__((always_inline)) {
+                        constexpr int p = pmax - decltype(ic)::value;
+                        if constexpr (step == 0 && q == 0) acc[p] = mfma16(a[p], b[0], v4i{0, 0, 0, 0});
+                        else acc[p + q] = mfma16(a[p], b[q], acc[p + q]);
+                    });
+                    if constexpr (last_step) {
+                        if constexpr (rf == RF - 1) b[q] = load_b(b_next, q, 0);
+                    } else {
+                        b[q] = load_b(b_this, q, step + 1);
+                        a[pmax] = read_a(rf, pass, pmax, step + 1);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
                 });
-                if constexpr (last_step) {
-                    b[q] = load_b(b_next, q, 0);
-                } else {
-                    b[q] = load_b(b_this, q, step + 1);
-                    a[pmax] = read_a(pass, pmax, step + 1);
-                }
-                __builtin_amdgcn_sched_barrier(0);
             });
-        });
-        // G = the diagonals, least significant first: acc = RN(acc + S_e 2^(-7 (e + 2))) (the product of an integer
-        // below 2^31 and a power of two is exact, so the fused operation rounds like the sum it stands for) ...
-        // (the first term as a plain product: RN(0 + t) = t, and t is exact)
-        // The four least significant diagonals, two at a time as one integer 2^7 S_(e-1) + S_e: diagonal e sums e + 1 slice
-        // products of at most 64 KS positions and 127^2 each, so while ((S - 1) 2^7 + S) 64 KS 127^2 < 2^31 that integer
-        // fits 32 bits; and the partial sums of those four terms are integers of less than 2^53 units of 2^(-7 (S + 1)),
-        // so no rounding happens among them and any grouping gives the value the one-by-one sequence gives.
-        constexpr bool MERGE = S >= 4 && ((long long)(S - 1) * 128 + S) * (64 * KS) * (127 * 127) < (1ll << 31);
-        constexpr int E_FIRST = MERGE ? S - 5 : S - 2;   // the diagonals from here down are added one by one
-        auto scale_of = [](int e) __attribute__((always_inline)) {
-            return __longlong_as_double((long long)(1023 - OZIMMU_SLICE_BITS * (e + 2)) << 52);
-        };
-        double sum[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if constexpr (MERGE) {
-                const int low = acc[S - 2][u] * (1 << OZIMMU_SLICE_BITS) + acc[S - 1][u];
-                const int next = acc[S - 4][u] * (1 << OZIMMU_SLICE_BITS) + acc[S - 3][u];
-                sum[u] = fma((double)next, scale_of(S - 3), (double)low * scale_of(S - 1));
-            } else {
-                sum[u] = (double)acc[S - 1][u] * scale_of(S - 1);
-            }
-        }
-#pragma unroll
-        for (int e = E_FIRST; e >= 0; --e) {
-            const double sc = scale_of(e);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) sum[u] = fma((double)acc[e][u], sc, sum[u]);
-        }
-        // ... times 2^(EA_i + EB_j)
-        const v4i ea = *reinterpret_cast<const v4i*>(ex + pass * kGateRows + lrow0);   // four consecutive rows
-        const int eb = ex_gate[pass * (NFR * 16) + f * 16 + (lane & 15)];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) sum[u] = ldexp(sum[u], ea[u] + eb);
-        if (pass == 0) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) part[u] = sum[u];
-        } else {
-            // lanes 0..7 of every 16: re = G(Ar,Br) - G(Ai,Bi); lanes 8..15: im = G(Ar,Bi) + G(Ai,Br)
-            // (the subtraction as the addition of the negated term: one flipped sign bit, no selection)
-            const long long flip = is_im ? 0ll : (long long)(1ull << 63);
-            double other[4];
-#pragma unroll
+            // G = the diagonals, least significant first: acc = RN(acc + S_e 2^(-7 (e + 2))) (the product of an integer
+            // below 2^31 and a power of two is exact, so the fused operation rounds like the sum it stands for) ...
+            // (the first term as a plain product: RN(0 + t) = t, and t is exact)
+            // The four least significant diagonals, two at a time as one integer 2^7 S_(e-1) + S_e: diagonal e sums e + 1 slice
+            // products of at most 64 KS positions and 127^2 each, so while ((S - 1) 2^7 + S) 64 KS 127^2 < 2^31 that integer
+            // fits 32 bits; and the partial sums of those four terms are integers of less than 2^53 units of 2^(-7 (S + 1)),
+            // so no rounding happens among them and any grouping gives the value the one-by-one sequence gives.
+            constexpr bool MERGE = S >= 4 && ((long long)(S - 1) * 128 + S) * (64 * KS) * (127 * 127) < (1ll << 31);
+            constexpr int E_FIRST = MERGE ? S - 5 : S - 2;   // the diagonals from here down are added one by one
+            auto scale_of = [](int e) __attribute__((always_inline)) {
+                return __longlong_as_double((long long)(1023 - OZIMMU_SLICE_BITS * (e + 2)) << 52);
+            };
+            double sum[4];
+    #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                sum[u] = part[u] + __longlong_as_double(__double_as_longlong(sum[u]) ^ flip);
-                // the other part of the same element, from the lane 8 further (rotation of the row of 16 lanes by 8)
-                const unsigned long long x = (unsigned long long)__double_as_longlong(sum[u]);
-                const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)x, 0x128, 0xf, 0xf, false);
-                const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(x >> 32), 0x128, 0xf, 0xf, false);
-                other[u] = __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+                if constexpr (MERGE) {
+                    const int low = acc[S - 2][u] * (1 << OZIMMU_SLICE_BITS) + acc[S - 1][u];
+                    const int next = acc[S - 4][u] * (1 << OZIMMU_SLICE_BITS) + acc[S - 3][u];
+                    sum[u] = fma((double)next, scale_of(S - 3), (double)low * scale_of(S - 1));
+                } else {
+                    sum[u] = (double)acc[S - 1][u] * scale_of(S - 1);
+                }
             }
-            // the lane with the real parts stores rows 0 and 1 of its four, the one with the imaginary parts rows 2 and 3
-            const int col = f * 8 + c8;
-            const int64_t row0 = row_tile + lrow0 + (is_im ? 2 : 0);
-            double* c = g.Cz + 2 * (row0 * g.ldcz + col);
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                double2 z;
-                z.x = is_im ? other[u + 2] : sum[u];
-                z.y = is_im ? sum[u + 2] : other[u];
-                if (row0 + u < g.m && col < g.n) *reinterpret_cast<double2*>(c + 2 * (int64_t)u * g.ldcz) = z;
+    #pragma unroll
+            for (int e = E_FIRST; e >= 0; --e) {
+                const double sc = scale_of(e);
+    #pragma unroll
+                for (int u = 0; u < 4; ++u) sum[u] = fma((double)acc[e][u], sc, sum[u]);
             }
-        }
-        __builtin_amdgcn_sched_barrier(0);
+            // ... times 2^(EA_i + EB_j)
+            const int lrow0 = lrow_first + 16 * rf;
+            const v4i ea = *reinterpret_cast<const v4i*>(ex + pass * kGateRows + lrow0);   // four consecutive rows
+            const int eb = ex_gate[pass * (NFR * 16) + f * 16 + (lane & 15)];
+    #pragma unroll
+            for (int u = 0; u < 4; ++u) sum[u] = ldexp(sum[u], ea[u] + eb);
+            if (pass == 0) {
+    #pragma unroll
+                for (int u = 0; u < 4; ++u) part[rf][u] = sum[u];
+            } else {
+                // lanes 0..7 of every 16: re = G(Ar,Br) - G(Ai,Bi); lanes 8..15: im = G(Ar,Bi) + G(Ai,Br)
+                // (the subtraction as the addition of the negated term: one flipped sign bit, no selection)
+                const long long flip = is_im ? 0ll : (long long)(1ull << 63);
+                double other[4];
+    #pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    sum[u] = part[rf][u] + __longlong_as_double(__double_as_longlong(sum[u]) ^ flip);
+                    // the other part of the same element, from the lane 8 further (rotation of the row of 16 lanes by 8)
+                    const unsigned long long x = (unsigned long long)__double_as_longlong(sum[u]);
+                    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)x, 0x128, 0xf, 0xf, false);
+                    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(x >> 32), 0x128, 0xf, 0xf, false);
+                    other[u] = __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+                }
+                // the lane with the real parts stores rows 0 and 1 of its four, the one with the imaginary parts rows 2 and 3
+                const int col = f * 8 + c8;
+                const int64_t row0 = row_tile + lrow0 + (is_im ? 2 : 0);
+                double* c = g.Cz + 2 * (row0 * g.ldcz + col);
+    #pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    double2 z;
+                    z.x = is_im ? other[u + 2] : sum[u];
+                    z.y = is_im ? sum[u + 2] : other[u];
+                    if (row0 + u < g.m && col < g.n) *reinterpret_cast<double2*>(c + 2 * (int64_t)u * g.ldcz) = z;
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
     }
 }
 
@@ -538,16 +548,25 @@ __global__ __launch_bounds__(1024) void gate_scan_reduce_kernel(const unsigned* 
     }
 }
 
-template <int S, int CLS, bool SCAN, int FEW>
-hipError_t launch_gate(const GateArgs& g, hipStream_t st) {
+template <int S, int CLS, bool SCAN, int FEW, bool BOTH>
+hipError_t launch_gate_one(const GateArgs& g, hipStream_t st) {
     constexpr int lds = 2 * S * (1 << CLS) * 2 * (FEW == 3 ? kFragBytes / 4 : kFragBytes) + (2 * kGateRows + 2 * (8 << CLS) * 16 + 16 * 2 * kScanCounters) * (int)sizeof(int);
     static_assert(lds <= 160 * 1024 && (S > kBand || CLS == 2 || 2 * lds <= 160 * 1024) && (!FEW || S > kBand || (FEW == 3 ? 8 : 4) * lds <= 160 * 1024),
                   "the LDS of a compute unit: two workgroups of eight wavefronts (four of four) up to eight slices, else one workgroup");
-    hipError_t e = allow_dynamic_lds<&gate_kernel<S, CLS, SCAN, FEW>>(lds);
+    hipError_t e = allow_dynamic_lds<&gate_kernel<S, CLS, SCAN, FEW, BOTH>>(lds);
     if (e != hipSuccess) return e;
     const unsigned grid = (unsigned)((g.m + kGateRows - 1) / kGateRows);
-    gate_kernel<S, CLS, SCAN, FEW><<<dim3(grid), dim3(64 * gate_waves(CLS, FEW)), lds, st>>>(g);
+    gate_kernel<S, CLS, SCAN, FEW, BOTH><<<dim3(grid), dim3(64 * gate_waves(CLS, FEW)), lds, st>>>(g);
     return hipGetLastError();
+}
+template <int S, int CLS, bool SCAN, int FEW>
+hipError_t launch_gate(const GateArgs& g, hipStream_t st) {
+    if constexpr (CLS == 0 && FEW != 3) {
+        constexpr int waves = gate_waves(CLS, FEW);
+        const int fragments = (g.n + 7) / 8, walks = (fragments + waves / 2 - 1) / (waves / 2), walks_both = 2 * ((fragments + waves - 1) / waves);
+        if (walks_both <= walks) return launch_gate_one<S, CLS, SCAN, FEW, true>(g, st);
+    }
+    return launch_gate_one<S, CLS, SCAN, FEW, false>(g, st);
 }
 template <int S, int CLS>
 hipError_t launch_gate(const GateArgs& g, hipStream_t st) {
