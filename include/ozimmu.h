@@ -195,7 +195,9 @@ ozimmu_status_t ozimmu_dgemm_stage(int stage, int64_t m, int64_t n, int64_t k, c
  * int32_block_steps = the largest number of slabs of OZIMMU_K_ALIGN positions after which the INT32 sums are moved into
  * INT64 sums (k-blocking; the walk takes two slabs at a time), 0 if all products of a diagonal that one workgroup adds
  * up fit one INT32 sum. With a smaller workspace that the call still accepts, fewer workgroups share a tile, or none
- * do, and a product with OZIMMU_INT32_BLOCK < num_slices * k_padded then runs with k-blocking.
+ * do, and a product with OZIMMU_INT32_BLOCK < num_slices * k_padded then runs with k-blocking. (A product of few tiles with
+ * k <= 128, or 256 up to eight slices, is split and multiplied by one kernel on 32 x 32 tiles; what is reported for it is how the slice
+ * products alone, ozimmu_dgemm_stage 2, run.)
  */
 typedef struct {
     int tile_rows, tile_cols;

@@ -634,6 +634,9 @@ ozimmu_status_t ozimmu_dgemm(int64_t m, int64_t n, int64_t k, const double* A, i
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (k == 0) return hip_status(launch_fill_f64(C, ldc, 1, m, n, 0.0, st));
     unsigned char* ws = static_cast<unsigned char*>(workspace);
+    // a few tiles and a short inner dimension: one launch, without the workspace
+    if (small_product_applies(m, n, k, num_slices))
+        return hip_status(launch_small_product(SmallArgs{{{A, lda, false}, {B, ldb, true}}, (int)m, (int)n, (int)k, C, ldc, 0, 1.0, 0.0, nullptr}, num_slices, st));
     hipError_t e = split_operands(L, false, Stored{A, lda, m, false, false}, Stored{B, ldb, n, true, false}, k, num_slices, ws, st);
     if (e == hipSuccess) e = run_product(L, m, n, num_slices, ws, 0, 0, C, ldc, 0, st, room_behind(ws, L.total, workspace_bytes));
     return hip_status(e);
@@ -741,6 +744,8 @@ static ozimmu_status_t dgemm_blas_impl(char transa, char transb, int64_t m, int6
         return OZIMMU_ERR_WORKSPACE;
     unsigned char* ws = static_cast<unsigned char*>(workspace);
     // op(B)^T: n rows of length k (B stored k x n by columns, or n x k); op(A): m rows of length k (A m x k, or k x m)
+    if (!count_sums && small_product_applies(n, m, k, num_slices))
+        return hip_status(launch_small_product(SmallArgs{{{B, ldb, tb}, {A, lda, !ta}}, (int)n, (int)m, (int)k, C, ldc, 3, alpha, beta, nullptr}, num_slices, st));
     hipError_t e = split_operands(L, false, Stored{B, ldb, n, tb, false}, Stored{A, lda, m, !ta, false}, k, num_slices, ws, st,
                                   count_sums ? count_sums + OZIMMU_MAX_SLICES : nullptr, count_sums);
     if (e == hipSuccess) e = run_product(L, n, m, num_slices, ws, 0, 0, C, ldc, 3, st, room_behind(ws, L.total, workspace_bytes), alpha, beta);
@@ -912,6 +917,8 @@ ozimmu_status_t ozimmu_dgemm_dd(int64_t m, int64_t n, int64_t k, const double* A
         return hip_status(e0);
     }
     unsigned char* ws = static_cast<unsigned char*>(workspace);
+    if (small_product_applies(m, n, k, num_slices))
+        return hip_status(launch_small_product(SmallArgs{{{A, lda, false}, {B, ldb, true}}, (int)m, (int)n, (int)k, C_hi, ldc, 0, 1.0, 0.0, C_lo}, num_slices, st));
     const hipError_t e = split_operands(L, false, Stored{A, lda, m, false, false}, Stored{B, ldb, n, true, false}, k, num_slices, ws, st);
     if (e != hipSuccess) return OZIMMU_ERR_HIP;
     if (num_slices <= 9) set_tiles(L, m, n, num_slices, false, false);   // the double-double kernels of so few slices exist for the large tiles only

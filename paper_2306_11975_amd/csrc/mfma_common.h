@@ -178,6 +178,17 @@ __device__ __forceinline__ void fold_band(double (&sum)[16], const v4i (&acc)[KB
     }
 }
 
+// Double-double running sum (Section 2.3.4: summing-up in higher precision): TwoSum of the high
+// part and the exact term, error into the low part, FastTwoSum to renormalise.
+__device__ __forceinline__ void dd_add(double& h, double& l, double t) {
+    const double sh = h + t;
+    const double bb = sh - h;
+    const double e = (h - (sh - bb)) + (t - bb);
+    const double l2 = l + e;
+    const double hn = sh + l2;
+    l = l2 - (hn - sh);
+    h = hn;
+}
 // Raise a kernel's dynamic LDS limit once per device instead of before every launch (the call
 // is a host-side driver round trip, and it keeps the launch path free of anything but the launch).
 // One instantiation, hence one set of flags, per kernel. Two host threads racing here both make

@@ -126,6 +126,25 @@ hipError_t launch_gate_product(const double* Z, int64_t ldz, int64_t m, int64_t 
                                int s, void* scratch, double* Cz, int64_t ldcz, hipStream_t st,
                                unsigned* scan_partials = nullptr, unsigned long long* scan_sums = nullptr);
 
+// A small real product in one launch (small.hip): m vectors of the first operand times n of the second, each the rows of a stored row-major
+// array or its columns (leading dimension ld), all of length k.
+struct SmallOperand {
+    const double* X;
+    int64_t ld;
+    bool by_cols;
+};
+struct SmallArgs {
+    SmallOperand x[2];
+    int m, n, k;
+    double* C;               // m x n, row-major
+    int64_t ldc;
+    int c_mode;              // 0: C = G, 3: C = alpha G (+ beta C if beta != 0)
+    double alpha, beta;
+    double* C_lo;            // not null: double-double sum, its low parts (c_mode 0)
+};
+bool small_product_applies(int64_t m, int64_t n, int64_t k, int s);
+hipError_t launch_small_product(const SmallArgs& g, int s, hipStream_t st);
+
 // negate: emit the slices of -A (-B) instead: same exponents, every slice with the opposite sign
 // (how a conjugated operand's imaginary plane is split)
 // Counting while splitting (the check of s as the automatic slice count, Section 4.4): scan_slots, if not null, is a

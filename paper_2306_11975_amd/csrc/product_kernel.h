@@ -575,17 +575,6 @@ __device__ __forceinline__ void band_walk(v4i (&acc)[KB][4], const GemmArgs& g, 
     workgroup_barrier();
 }
 
-// Double-double running sum (Section 2.3.4: summing-up in higher precision): TwoSum of the high
-// part and the exact term, error into the low part, FastTwoSum to renormalise.
-__device__ __forceinline__ void dd_add(double& h, double& l, double t) {
-    const double sh = h + t;
-    const double bb = sh - h;
-    const double e = (h - (sh - bb)) + (t - bb);
-    const double l2 = l + e;
-    const double hn = sh + l2;
-    l = l2 - (hn - sh);
-    h = hn;
-}
 template <int SB, int KB>
 __device__ __forceinline__ void fold_band_dd(double (&h)[16], double (&l)[16], const v4i (&acc)[KB][4]) {
     constexpr int ND = SB < KB ? SB : KB, E0 = SB - ND;

@@ -25,19 +25,30 @@ SIZES = [(64, 64, 1), (65, 63, 64), (1, 130, 65), (129, 66, 96), (70, 200, 1000)
 
 @pytest.mark.parametrize("s", [9, 11, 12, 13, 14, 15])
 @pytest.mark.parametrize("m,n,k", SIZES)
-def test_real_and_double_double(m, n, k, s):
+def test_real(m, n, k, s):
+    """By stages: the call itself takes another kernel where k is short."""
     assert ozimmu.launch_plan(m, n, k, s)["bands"] == 1
     A, B = wl.phi_pair(m, n, k, 1.0, seed=k + s)
     dA, dB = dev(A), dev(B)
     C = torch.full((m, n), float("nan"), dtype=torch.float64, device="cuda")
-    lo = torch.full_like(C, float("nan"))
     ws = ozimmu.alloc_workspace(m, n, k, s)
-    ozimmu.dgemm(dA, dB, C, s, ws)
+    for stage in range(3):
+        ozimmu.dgemm_stage(stage, dA, dB, C, s, ws)
     assert np.array_equal(bits(C.cpu().numpy()), bits(oracle.dgemm(A, B, s)))
-    C.fill_(float("nan"))
-    ozimmu.dgemm_dd(dA, dB, C, lo, s, ws)
-    hi_want, lo_want = oracle.dgemm_dd(A, B, s)
-    assert np.array_equal(bits(C.cpu().numpy()), bits(hi_want)) and np.array_equal(bits(lo.cpu().numpy()), bits(lo_want))
+
+
+# (1030 x 1030: more tiles than the kernel for small products takes, so that the shortest walks are reached)
+@pytest.mark.parametrize("s", [11, 12, 13, 14, 15])
+@pytest.mark.parametrize("m,n,k", [(1030, 1030, 20), (1030, 1030, 64), (1030, 1030, 90), (70, 200, 1000), (64, 128, 513), (129, 66, 300)])
+def test_double_double(m, n, k, s):
+    A, B = wl.phi_matrix_device(m, k, 1.0, k + s), wl.phi_matrix_device(k, n, 1.0, k + s + 1)
+    C = torch.full((m, n), float("nan"), dtype=torch.float64, device="cuda")
+    lo = torch.full_like(C, float("nan"))
+    ozimmu.dgemm_dd(A, B, C, lo, s, ozimmu.alloc_workspace(m, n, k, s))
+    rows = torch.arange(0, m, 1 + m // 40, device="cuda")
+    hi_want, lo_want = oracle.dgemm_dd(A[rows].cpu().numpy(), B.cpu().numpy(), s)
+    assert np.array_equal(bits(C[rows].cpu().numpy()), bits(hi_want)) and np.array_equal(bits(lo[rows].cpu().numpy()), bits(lo_want))
+    assert not torch.isnan(C).any()
 
 
 @pytest.mark.parametrize("s", [9, 11, 12, 13, 14, 15])
