@@ -293,6 +293,8 @@ ozimmu_status_t ozimmu_auto_num_slices(int64_t m, int64_t n, int64_t k, const do
  * *num_slices receives the count, C the product; both are exactly what the two calls give. `guess` is
  * the caller's expectation of the count (say, the one the previous product of this shape took; 0: none).
  * With a guess the product is formed with it at once:
+ *   - where few tiles and a short inner dimension make it one kernel (see ozimmu_launch_plan), that kernel counts on its way and leaves
+ *     its counts in mapped host memory;
  *   - where ozimmu_zgemm runs as the kernel that splits A on the fly (see there), that kernel and the
  *     splitter of B count on their way what the check of the guess needs: a right guess means A has
  *     been read once instead of twice;
@@ -303,7 +305,7 @@ ozimmu_status_t ozimmu_auto_num_slices(int64_t m, int64_t n, int64_t k, const do
  * workspace: at least the largest ozimmu_workspace_bytes(m, n, k, s, is_complex) over
  * s = 1 .. max_slices; scratch: as for ozimmu_auto_num_slices. Waits for the stream like
  * ozimmu_auto_num_slices; errors as there and as for ozimmu_dgemm. These calls and
- * ozimmu_auto_num_slices receive their sums in 512 bytes of mapped host memory that the first such
+ * ozimmu_auto_num_slices receive their sums in 17 KiB of mapped host memory that the first such
  * call of a thread allocates and that is kept until the process ends.
  */
 ozimmu_status_t ozimmu_dgemm_auto(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,

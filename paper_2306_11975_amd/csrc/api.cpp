@@ -341,12 +341,16 @@ hipError_t scan_operand(const ScanOperand& z, int o, int is_complex, unsigned lo
     return e;
 }
 
-// 4 x 16 sums in host memory that kernels of any device can write (one buffer per calling thread, kept until the process ends)
+// The counters that the kernels for small products leave, per tile of rows and of columns, two planes at most
+constexpr int kMappedSums = 4 * OZIMMU_MAX_SLICES, kMappedCounts = 4 * (kSmallMaxTiles + 1);
+
+// 4 x 16 sums, and room for those counters behind them, in host memory that kernels of any device can write (one buffer per calling
+// thread, kept until the process ends)
 unsigned long long* mapped_sums() {
     thread_local unsigned long long* p = nullptr;
     if (!p) {
         void* q = nullptr;
-        if (hipHostMalloc(&q, 4 * OZIMMU_MAX_SLICES * sizeof(unsigned long long), hipHostMallocMapped | hipHostMallocPortable) == hipSuccess)
+        if (hipHostMalloc(&q, kMappedSums * sizeof(unsigned long long) + kMappedCounts * sizeof(unsigned), hipHostMallocMapped | hipHostMallocPortable) == hipSuccess)
             p = static_cast<unsigned long long*>(q);
     }
     return p;
@@ -444,7 +448,28 @@ ozimmu_status_t gemm_auto(bool cplx, int64_t m, int64_t n, int64_t k, const doub
     const bool have_guess = guess >= 1 && guess <= max_slices && m > 0 && n > 0 && k > 0;
     const double count_a = (double)m * (double)k, count_b = (double)k * (double)n;
     unsigned long long* host = have_guess ? mapped_sums() : nullptr;                   // [4][16]
-    if (host && cplx && gate_product_applies(A, B, C, n, k, guess)) {
+    if (host && (cplx ? small_complex_applies(m, n, k, guess) : small_product_applies(m, n, k, guess))) {
+        // A few tiles and a short inner dimension: one kernel does it all and leaves its counts per tile in the mapped memory.
+        unsigned* counts = reinterpret_cast<unsigned*>(host + kMappedSums);
+        const SmallArgs g{{{A, lda, false}, {B, ldb, true}}, (int)m, (int)n, (int)k, C, ldc, 0, 1.0, 0.0, nullptr, counts};
+        hipError_t e = cplx ? launch_small_complex(g, guess, st) : launch_small_product(g, guess, st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e != hipSuccess) return OZIMMU_ERR_HIP;
+        const int planes = cplx ? 2 : 1;
+        const int64_t tiles[2] = {(m + kSmallTileRows - 1) / kSmallTileRows, (n + kSmallTileRows - 1) / kSmallTileRows};
+        for (int o = 0; o < 2; ++o)
+            for (int pl = 0; pl < planes; ++pl) {
+                unsigned long long lost[2] = {0, 0};
+                for (int64_t i = 0; i < tiles[o]; ++i)
+                    for (int j = 0; j < 2; ++j) lost[j] += counts[2 * (planes * ((o ? tiles[0] : 0) + i) + pl) + j];
+                for (int j = 0; j < 2 && guess > j; ++j) host[(o * planes + pl) * OZIMMU_MAX_SLICES + guess - 1 - j] = lost[j];
+            }
+        if (guess_holds(host, 2 * planes, count_a, count_b, threshold, guess, max_slices)) {
+            *num_slices = guess;
+            if (guess_confirmed) *guess_confirmed = 1;
+            return OZIMMU_OK;
+        }
+    } else if (host && cplx && gate_product_applies(A, B, C, n, k, guess)) {
         // Multiply with the guessed count; the kernels that split B and that walk over A count, on their way, what the
         // check of the guess needs (the bits each plane loses with `guess` and with `guess - 1` slices) and a last small
         // kernel writes the eight sums into mapped host memory: no pass of its own over A, no copy.
@@ -636,7 +661,7 @@ ozimmu_status_t ozimmu_dgemm(int64_t m, int64_t n, int64_t k, const double* A, i
     unsigned char* ws = static_cast<unsigned char*>(workspace);
     // a few tiles and a short inner dimension: one launch, without the workspace
     if (small_product_applies(m, n, k, num_slices))
-        return hip_status(launch_small_product(SmallArgs{{{A, lda, false}, {B, ldb, true}}, (int)m, (int)n, (int)k, C, ldc, 0, 1.0, 0.0, nullptr}, num_slices, st));
+        return hip_status(launch_small_product(SmallArgs{{{A, lda, false}, {B, ldb, true}}, (int)m, (int)n, (int)k, C, ldc, 0, 1.0, 0.0, nullptr, nullptr}, num_slices, st));
     hipError_t e = split_operands(L, false, Stored{A, lda, m, false, false}, Stored{B, ldb, n, true, false}, k, num_slices, ws, st);
     if (e == hipSuccess) e = run_product(L, m, n, num_slices, ws, 0, 0, C, ldc, 0, st, room_behind(ws, L.total, workspace_bytes));
     return hip_status(e);
@@ -658,6 +683,9 @@ ozimmu_status_t ozimmu_zgemm(int64_t m, int64_t n, int64_t k, const double* A, i
     unsigned char* ws = static_cast<unsigned char*>(workspace);
     const int s = num_slices;
     hipError_t e = hipSuccess;
+    // a few tiles and a short inner dimension: one launch, without the workspace
+    if (small_complex_applies(m, n, k, s))
+        return hip_status(launch_small_complex(SmallArgs{{{A, lda, false}, {B, ldb, true}}, (int)m, (int)n, (int)k, C, ldc, 0, 1.0, 0.0, nullptr, nullptr}, s, st));
     // a small B on a tall A (a gate on a state vector): one kernel that splits A on the fly and reads it once
     if (gate_product_applies(A, B, C, n, k, s)) return hip_status(launch_gate_product(A, lda, m, k, n, B, ldb, s, ws + L.off_gate, C, ldc, st));
     // the real and imaginary planes are separated while splitting
@@ -745,7 +773,7 @@ static ozimmu_status_t dgemm_blas_impl(char transa, char transb, int64_t m, int6
     unsigned char* ws = static_cast<unsigned char*>(workspace);
     // op(B)^T: n rows of length k (B stored k x n by columns, or n x k); op(A): m rows of length k (A m x k, or k x m)
     if (!count_sums && small_product_applies(n, m, k, num_slices))
-        return hip_status(launch_small_product(SmallArgs{{{B, ldb, tb}, {A, lda, !ta}}, (int)n, (int)m, (int)k, C, ldc, 3, alpha, beta, nullptr}, num_slices, st));
+        return hip_status(launch_small_product(SmallArgs{{{B, ldb, tb}, {A, lda, !ta}}, (int)n, (int)m, (int)k, C, ldc, 3, alpha, beta, nullptr, nullptr}, num_slices, st));
     hipError_t e = split_operands(L, false, Stored{B, ldb, n, tb, false}, Stored{A, lda, m, !ta, false}, k, num_slices, ws, st,
                                   count_sums ? count_sums + OZIMMU_MAX_SLICES : nullptr, count_sums);
     if (e == hipSuccess) e = run_product(L, n, m, num_slices, ws, 0, 0, C, ldc, 3, st, room_behind(ws, L.total, workspace_bytes), alpha, beta);
@@ -810,8 +838,11 @@ static ozimmu_status_t zgemm_blas_impl(char transa, char transb, int64_t m, int6
     const int64_t ldg = beta_zero ? ldc : m;
     // Neither operand transposed, a small A on a wide B (a gate on a state vector whose amplitudes are the columns'
     // entries): the row-major product B^T A^T has the state as its tall operand and takes the one-kernel path.
-    if (!count_sums && !ta && !tb && gate_product_applies(B, A, G, m, k, num_slices)) {
-        e = launch_gate_product(B, ldb, n, k, m, A, lda, num_slices, ws + L.off_gate, G, ldg, st);
+    // (Few tiles and a short inner dimension: in one launch.)
+    const bool small = small_complex_applies(n, m, k, num_slices);
+    if (!count_sums && !ta && !tb && (small || gate_product_applies(B, A, G, m, k, num_slices))) {
+        e = small ? launch_small_complex(SmallArgs{{{B, ldb, false}, {A, lda, true}}, (int)n, (int)m, (int)k, G, ldg, 0, 1.0, 0.0, nullptr, nullptr}, num_slices, st)
+                  : launch_gate_product(B, ldb, n, k, m, A, lda, num_slices, ws + L.off_gate, G, ldg, st);
         if (e == hipSuccess && !(beta_zero && alpha_one)) e = launch_zaxpby(G, ldg, C, ldc, n, m, ar, ai, br, bi, st);
         return hip_status(e);
     }
@@ -918,7 +949,7 @@ ozimmu_status_t ozimmu_dgemm_dd(int64_t m, int64_t n, int64_t k, const double* A
     }
     unsigned char* ws = static_cast<unsigned char*>(workspace);
     if (small_product_applies(m, n, k, num_slices))
-        return hip_status(launch_small_product(SmallArgs{{{A, lda, false}, {B, ldb, true}}, (int)m, (int)n, (int)k, C_hi, ldc, 0, 1.0, 0.0, C_lo}, num_slices, st));
+        return hip_status(launch_small_product(SmallArgs{{{A, lda, false}, {B, ldb, true}}, (int)m, (int)n, (int)k, C_hi, ldc, 0, 1.0, 0.0, C_lo, nullptr}, num_slices, st));
     const hipError_t e = split_operands(L, false, Stored{A, lda, m, false, false}, Stored{B, ldb, n, true, false}, k, num_slices, ws, st);
     if (e != hipSuccess) return OZIMMU_ERR_HIP;
     if (num_slices <= 9) set_tiles(L, m, n, num_slices, false, false);   // the double-double kernels of so few slices exist for the large tiles only

@@ -424,12 +424,16 @@ hipError_t launch_gate_one(const GateArgs& g, hipStream_t st) {
 }
 template <int S, int CLS, bool SCAN, int FEW>
 hipError_t launch_gate(const GateArgs& g, hipStream_t st) {
-    if constexpr (CLS == 0 && FEW != 3) {
-        constexpr int waves = gate_waves(CLS, FEW);
-        const int fragments = (g.n + 7) / 8, walks = (fragments + waves / 2 - 1) / (waves / 2), walks_both = 2 * ((fragments + waves - 1) / waves);
-        if (walks_both <= walks) return launch_gate_one<S, CLS, SCAN, FEW, true>(g, st);
+    if constexpr (CLS == 0 && FEW == 0) {   // (more than 32 columns: fewer, with so few rows, are a product for small_complex.hip)
+        return launch_gate_one<S, CLS, SCAN, FEW, true>(g, st);
+    } else {
+        if constexpr (CLS == 0 && FEW != 3) {
+            constexpr int waves = gate_waves(CLS, FEW);
+            const int fragments = (g.n + 7) / 8, walks = (fragments + waves / 2 - 1) / (waves / 2), walks_both = 2 * ((fragments + waves - 1) / waves);
+            if (walks_both <= walks) return launch_gate_one<S, CLS, SCAN, FEW, true>(g, st);
+        }
+        return launch_gate_one<S, CLS, SCAN, FEW, false>(g, st);
     }
-    return launch_gate_one<S, CLS, SCAN, FEW, false>(g, st);
 }
 template <int S, int CLS>
 hipError_t launch_gate(const GateArgs& g, hipStream_t st) {

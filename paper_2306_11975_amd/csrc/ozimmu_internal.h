@@ -141,9 +141,16 @@ struct SmallArgs {
     int c_mode;              // 0: C = G, 3: C = alpha G (+ beta C if beta != 0)
     double alpha, beta;
     double* C_lo;            // not null: double-double sum, its low parts (c_mode 0)
+    unsigned* counts;        // not null (device or mapped host memory): [row tiles, then column tiles][planes][2], the bits that a tile's rows
+                             // (columns) lose with s and with s - 1 slices
 };
 bool small_product_applies(int64_t m, int64_t n, int64_t k, int s);
 hipError_t launch_small_product(const SmallArgs& g, int s, hipStream_t st);
+// The same for a complex product, its operands and C interleaved (leading dimensions in complex elements; c_mode 0).
+bool small_complex_applies(int64_t m, int64_t n, int64_t k, int s);
+hipError_t launch_small_complex(const SmallArgs& g, int s, hipStream_t st);
+constexpr int kSmallTileRows = 32;   // rows and columns of their tiles
+constexpr int kSmallMaxTiles = 1024; // and at most so many of them
 
 // negate: emit the slices of -A (-B) instead: same exponents, every slice with the opposite sign
 // (how a conjugated operand's imaginary plane is split)

@@ -6,29 +6,22 @@
 // multiply a 16 x 16 patch each, all diagonals resident. What bounds it is latency (a launch, a trip to memory, three barriers), and
 // the splitting that the tiles of a row or column repeat: so few tiles and a short k only (small_product_applies). Per call, two launches
 // -> one (about 9 us is what the host takes for one): 64^3 at five slices 12.0 -> 9.0 us, at thirteen 22.2 -> 9.0; 512 x 512 x 128 at eight 15.1 -> 9.3.
-#include "mfma_common.h"
-#include "split_common.h"
+#include "small_common.h"
 
 namespace ozimmu {
 namespace {
-
-constexpr int kSmallThreads = 512;
-constexpr int kSmallTile = 32;       // rows and columns of C per workgroup
-constexpr int kSmallStep = 64;       // positions of k per MFMA
-
-// byte of a fragment that holds (row, position): lane l of the operand takes row l % 16, positions 16 (l / 16) .. + 15
-__device__ __forceinline__ int small_offset(int row, int pos) { return ((pos >> 4) * 16 + row) * 16 + (pos & 15); }
 
 // KS steps of 64 positions cover k. DD: double-double sum into C and C_lo.
 template <int S, int KS, bool DD>
 __global__ __launch_bounds__(kSmallThreads) void small_product_kernel(const SmallArgs g) {
     constexpr bool WIDE = S > 9;
-    constexpr int GROUPS = kSmallThreads / kSmallTile;               // threads that share a vector of an operand
+    constexpr int GROUPS = kSmallGroups;
     constexpr int W = KS * (kSmallStep / 4) / GROUPS;                // words of four consecutive positions to a thread
     constexpr int STEP = 2 * kFragBytes, SLICE = KS * STEP, OPERAND = S * SLICE;   // [operand][slice][step][fragment of 16 rows]
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     __shared__ unsigned long long maxima[2][GROUPS][kSmallTile];
     __shared__ int ex[2][kSmallTile];
+    __shared__ unsigned count_lds[2][2];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tiles_n = (g.n + kSmallTile - 1) / kSmallTile;
@@ -66,6 +59,7 @@ __global__ __launch_bounds__(kSmallThreads) void small_product_kernel(const Smal
             }
         maxima[o][group[o]][vec[o]] = mx;
     }
+    if (tid < 4) count_lds[tid >> 1][tid & 1] = 0u;
     __syncthreads();
 #pragma unroll
     for (int o = 0; o < 2; ++o) {
@@ -89,6 +83,13 @@ __global__ __launch_bounds__(kSmallThreads) void small_product_kernel(const Smal
                 constexpr int p = decltype(pc)::value;
                 *reinterpret_cast<uint32_t*>(dst + (p - 1) * SLICE) = packed_slice<WIDE>(x, sm, p);
             });
+        }
+        // the check of S as the automatic slice count: every vector is counted by one workgroup
+        if (g.counts && (o ? tm : tn) == 0) {
+            unsigned lost[2] = {0u, 0u};
+#pragma unroll
+            for (int i = 0; i < W; ++i) small_count(lost, v[o][i], E, S);
+            small_put_counts(lost, count_lds[o], g.counts + 2 * (o ? (g.m + kSmallTile - 1) / kSmallTile + tn : tm));
         }
     }
     __syncthreads();
@@ -144,8 +145,6 @@ __global__ __launch_bounds__(kSmallThreads) void small_product_kernel(const Smal
         if (row0 + u < g.m && col < g.n) g.C[(int64_t)(row0 + u) * g.ldc + col] = val;
     }
 }
-
-inline int64_t small_tiles(int64_t m, int64_t n) { return ((m + kSmallTile - 1) / kSmallTile) * ((n + kSmallTile - 1) / kSmallTile); }
 
 template <int S, int KS, bool DD>
 hipError_t launch_small_one(const SmallArgs& g, hipStream_t st) {

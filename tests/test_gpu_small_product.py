@@ -101,3 +101,52 @@ def test_blas_form(transa, transb, alpha, beta, m, n, k, s):
     got = dC.cpu().numpy()
     want = oracle.dgemm_blas(ta, tb, alpha, A.T if ta else A, B.T if tb else B, beta, C, s)
     assert np.array_equal(bits(got[:, :m].T), bits(want)) and np.isnan(got[:, m:]).all()
+
+
+# complex: up to 256 tiles; (1, 64, 64): a small register's gate; k = 65: two steps up to eight slices, the other kernels beyond
+@pytest.mark.parametrize("s", range(1, 17))
+@pytest.mark.parametrize("m,n,k", [(1, 1, 1), (32, 32, 64), (33, 31, 63), (1024, 64, 64), (5, 40, 3), (40, 70, 65), (33, 20, 128), (512, 512, 5), (515, 512, 5),
+                                   (500, 510, 70)])
+def test_complex(m, n, k, s):
+    rng = np.random.default_rng(m + k + s)
+    A = rng.standard_normal((m, k)) + 1j * rng.standard_normal((m, k))
+    B = rng.standard_normal((k, n)) + 1j * rng.standard_normal((k, n))
+    A[m // 2] = 0.0
+    A[m - 1, k - 1] = 3e-310 - 5e-324j
+    B[:, 0] = B[:, 0].real
+    pad = s % 3
+    dA, dC = torch.zeros((m, k + pad), dtype=torch.complex128, device="cuda"), torch.full((m, n + pad), float("nan"), dtype=torch.complex128, device="cuda")
+    dA[:, :k] = dev(A)
+    ozimmu.zgemm(dA[:, :k], dev(B), dC[:, :n], s, ozimmu.alloc_workspace(m, n, k, s, True))
+    got = dC.cpu().numpy()
+    assert np.array_equal(bits(got[:, :n]), bits(oracle.zgemm(A, B, s))) and np.isnan(got[:, n:]).all()
+
+
+# the choice checked from the counts per tile: right, wrong and extreme guesses, several tiles of rows and of columns
+@pytest.mark.parametrize("cplx,m,n,k", [(False, 100, 70, 50), (False, 33, 300, 128), (False, 40, 33, 200), (False, 1, 1, 1), (True, 100, 70, 50), (True, 1024, 64, 64),
+                                        (True, 40, 33, 100), (True, 3, 2, 1)])
+def test_guess_is_checked_from_the_counts_of_the_tiles(cplx, m, n, k):
+    A, B = (wl.gaussian_complex(m, k, 5), wl.gaussian_complex(k, n, 6)) if cplx else wl.phi_pair(m, n, k, 1.0, seed=4)
+    A[m // 2] = 0.0
+    dA, dB = dev(A), dev(B)
+    auto, product = (ozimmu.zgemm_auto, oracle.zgemm) if cplx else (ozimmu.dgemm_auto, oracle.dgemm)
+    for T in (0.0, 1.0, 3.0):
+        right, _ = oracle.auto_num_slices(A, B, T)
+        want = product(A, B, right)
+        for guess in {max(1, right - 1), right, min(16, right + 1), 1, 16}:
+            C = torch.full((m, n), float("nan"), dtype=dA.dtype, device="cuda")
+            got, confirmed = auto(dA, dB, C, T, guess=guess)
+            assert got == right and confirmed == (guess == right), (T, guess)
+            assert np.array_equal(bits(C.cpu().numpy()), bits(want))
+
+
+# the complex BLAS-style call of plain operands, with scalars (held beside C, then combined) and without
+@pytest.mark.parametrize("alpha,beta", [(1.0, 0.0), (0.5 - 2.0j, 0.0), (1.5j, -0.75 + 1.0j)])
+@pytest.mark.parametrize("m,n,k,s", [(20, 45, 33, 8), (40, 33, 100, 5), (33, 70, 64, 11)])
+def test_complex_blas_form(m, n, k, s, alpha, beta):
+    A, B, C = wl.gaussian_complex(m, k, 1), wl.gaussian_complex(k, n, 2), wl.gaussian_complex(m, n, 3)
+    dA, dB, dC = dev(A.T), dev(B.T), dev(C.T if beta else np.full((n, m), np.nan + 0j))   # column-major as row-major transposes
+    ws = torch.empty(ozimmu.zgemm_blas_workspace_bytes(m, n, k, s, beta == 0), dtype=torch.uint8, device="cuda")
+    ozimmu.zgemm_blas("N", "N", m, n, k, alpha, dA, m, dB, k, beta, dC, m, s, ws)
+    want = oracle.zgemm_blas("N", "N", alpha, A, B, beta, C, s)
+    assert np.array_equal(bits(dC.cpu().numpy().T), bits(want))
