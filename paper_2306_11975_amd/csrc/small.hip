@@ -84,65 +84,71 @@ __global__ __launch_bounds__(kSmallThreads) void small_product_kernel(const Smal
                 *reinterpret_cast<uint32_t*>(dst + (p - 1) * SLICE) = packed_slice<WIDE>(x, sm, p);
             });
         }
-        // the check of S as the automatic slice count: every vector is counted by one workgroup
-        if (g.counts && (o ? tm : tn) == 0) {
-            unsigned lost[2] = {0u, 0u};
-#pragma unroll
-            for (int i = 0; i < W; ++i) small_count(lost, v[o][i], E, S);
-            small_put_counts(lost, count_lds[o], g.counts + 2 * (o ? (g.m + kSmallTile - 1) / kSmallTile + tn : tm));
-        }
     }
     __syncthreads();
 
     // ---- a 16 x 16 patch to a wavefront
-    if (wave >= 4) return;
-    const int pi = wave >> 1, pj = wave & 1;
-    const int row0 = tm * kSmallTile + 16 * pi + 4 * (lane >> 4), col = tn * kSmallTile + 16 * pj + (lane & 15);
-    double old_c[4] = {0.0, 0.0, 0.0, 0.0};
-    if (g.c_mode != 0 && g.beta != 0.0) {   // requested ahead of the products
+    if (wave < 4) {
+        const int pi = wave >> 1, pj = wave & 1;
+        const int row0 = tm * kSmallTile + 16 * pi + 4 * (lane >> 4), col = tn * kSmallTile + 16 * pj + (lane & 15);
+        double old_c[4] = {0.0, 0.0, 0.0, 0.0};
+        if (g.c_mode != 0 && g.beta != 0.0) {   // requested ahead of the products
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (row0 + u < g.m && col < g.n) old_c[u] = g.C[(int64_t)(row0 + u) * g.ldc + col];
-    }
-    v4i acc[S];
-#pragma unroll
-    for (int e = 0; e < S; ++e) acc[e] = v4i{0, 0, 0, 0};
-#pragma unroll
-    for (int step = 0; step < KS; ++step) {
-        v4i a[S], b[S];
-#pragma unroll
-        for (int p = 0; p < S; ++p) {
-            a[p] = *reinterpret_cast<const v4i*>(lds + p * SLICE + step * STEP + pi * kFragBytes + 16 * lane);
-            b[p] = *reinterpret_cast<const v4i*>(lds + OPERAND + p * SLICE + step * STEP + pj * kFragBytes + 16 * lane);
+            for (int u = 0; u < 4; ++u)
+                if (row0 + u < g.m && col < g.n) old_c[u] = g.C[(int64_t)(row0 + u) * g.ldc + col];
         }
+        v4i acc[S];
 #pragma unroll
-        for (int q = 0; q < S; ++q)
+        for (int e = 0; e < S; ++e) acc[e] = v4i{0, 0, 0, 0};
 #pragma unroll
-            for (int p = S - 1 - q; p >= 0; --p) acc[p + q] = mfma16(a[p], b[q], acc[p + q]);
-    }
-    // the diagonals, least significant first (a product with a power of two is exact, so the fused operation rounds like the sum), ...
-    double sum[4] = {0.0, 0.0, 0.0, 0.0}, lo[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int step = 0; step < KS; ++step) {
+            v4i a[S], b[S];
 #pragma unroll
-    for (int e = S - 1; e >= 0; --e) {
-        const double sc = __longlong_as_double((long long)(1023 - OZIMMU_SLICE_BITS * (e + 2)) << 52);
+            for (int p = 0; p < S; ++p) {
+                a[p] = *reinterpret_cast<const v4i*>(lds + p * SLICE + step * STEP + pi * kFragBytes + 16 * lane);
+                b[p] = *reinterpret_cast<const v4i*>(lds + OPERAND + p * SLICE + step * STEP + pj * kFragBytes + 16 * lane);
+            }
+#pragma unroll
+            for (int q = 0; q < S; ++q)
+#pragma unroll
+                for (int p = S - 1 - q; p >= 0; --p) acc[p + q] = mfma16(a[p], b[q], acc[p + q]);
+        }
+        // the diagonals, least significant first (a product with a power of two is exact, so the fused operation rounds like the sum), ...
+        double sum[4] = {0.0, 0.0, 0.0, 0.0}, lo[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int e = S - 1; e >= 0; --e) {
+            const double sc = __longlong_as_double((long long)(1023 - OZIMMU_SLICE_BITS * (e + 2)) << 52);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if constexpr (DD) dd_add(sum[u], lo[u], (double)acc[e][u] * sc);
+                else sum[u] = fma((double)acc[e][u], sc, sum[u]);
+            }
+        }
+        // ... scaled, combined and stored
+        const int eb = ex[1][16 * pj + (lane & 15)];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            if constexpr (DD) dd_add(sum[u], lo[u], (double)acc[e][u] * sc);
-            else sum[u] = fma((double)acc[e][u], sc, sum[u]);
+            const int e = ex[0][16 * pi + 4 * (lane >> 4) + u] + eb;
+            double val = ldexp(sum[u], e);
+            if (DD && row0 + u < g.m && col < g.n) g.C_lo[(int64_t)(row0 + u) * g.ldc + col] = ldexp(lo[u], e);
+            if (g.c_mode != 0) {   // RN(alpha G), then RN(RN(alpha G) + RN(beta C)); C is not read if beta == 0
+                val = g.alpha * val;
+                if (g.beta != 0.0) val = val + g.beta * old_c[u];
+            }
+            if (row0 + u < g.m && col < g.n) g.C[(int64_t)(row0 + u) * g.ldc + col] = val;
         }
     }
-    // ... scaled, combined and stored
-    const int eb = ex[1][16 * pj + (lane & 15)];
+
+    // ---- the check of S as the automatic slice count (the other wavefronts count while those four multiply)
+    if (!g.counts) return;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int e = ex[0][16 * pi + 4 * (lane >> 4) + u] + eb;
-        double val = ldexp(sum[u], e);
-        if (DD && row0 + u < g.m && col < g.n) g.C_lo[(int64_t)(row0 + u) * g.ldc + col] = ldexp(lo[u], e);
-        if (g.c_mode != 0) {   // RN(alpha G), then RN(RN(alpha G) + RN(beta C)); C is not read if beta == 0
-            val = g.alpha * val;
-            if (g.beta != 0.0) val = val + g.beta * old_c[u];
-        }
-        if (row0 + u < g.m && col < g.n) g.C[(int64_t)(row0 + u) * g.ldc + col] = val;
+    for (int o = 0; o < 2; ++o) {
+        if (!(o ? small_counts_columns(tm, tn, g) : small_counts_rows(tm, tn, g))) continue;
+        unsigned lost[2] = {0u, 0u};
+        const int E = ex[o][vec[o]];
+#pragma unroll
+        for (int i = 0; i < W; ++i) small_count(lost, v[o][i], E, S);
+        small_put_counts(lost, count_lds[o], g.counts + 2 * (o ? (g.m + kSmallTile - 1) / kSmallTile + tn : tm));
     }
 }
 

@@ -30,6 +30,14 @@ __device__ __forceinline__ void small_count(unsigned (&lost)[2], const unsigned 
         }
     }
 }
+// Which workgroup counts a tile of rows, and which a tile of columns: one each, and not the same one where that can be had.
+__device__ __forceinline__ bool small_counts_rows(int tm, int tn, const SmallArgs& g) {
+    return tn == tm % ((g.n + kSmallTile - 1) / kSmallTile);
+}
+__device__ __forceinline__ bool small_counts_columns(int tm, int tn, const SmallArgs& g) {
+    const int last = (g.m + kSmallTile - 1) / kSmallTile - 1, next = (tn + 1) % ((g.n + kSmallTile - 1) / kSmallTile);
+    return tm == (next < last ? next : last);
+}
 // The counts of a workgroup's vectors of one operand (N per thread) to N words of `out`; lds: N zeroed words. A tile counts at most
 // 32 x 256 elements of fewer than 166 bits. Every thread calls this.
 template <int N>

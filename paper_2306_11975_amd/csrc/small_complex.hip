@@ -1,6 +1,6 @@
 // Small complex products in one launch: as small.hip, with both planes of every element and four real products to a patch. A gate on a
 // small register, above all: what such a call takes is launches (gate split, product and the counters' sums were three). Per call: 1024 x 64 x 64 with the
-// slice count checked on the way 36.8 -> 30.0 us (most of it the wait for the device), without 12.3 -> 9.8; 256 x 256 x 64 at eight slices 54.8 -> 9.7.
+// slice count checked on the way 36.8 -> 28.6 us (most of it the wait for the device), without 12.3 -> 9.8; 256 x 256 x 64 at eight slices 54.8 -> 9.7.
 #include "small_common.h"
 
 namespace ozimmu {
@@ -61,8 +61,6 @@ __global__ __launch_bounds__(kSmallThreads) void small_complex_kernel(const Smal
     __syncthreads();
 #pragma unroll
     for (int o = 0; o < 2; ++o) {
-        unsigned lost[4] = {0u, 0u, 0u, 0u};
-        const bool counted = g.counts && (o ? tm : tn) == 0;   // every vector is counted by one workgroup
 #pragma unroll
         for (int pl = 0; pl < 2; ++pl) {
             unsigned long long mx = 0;
@@ -85,65 +83,77 @@ __global__ __launch_bounds__(kSmallThreads) void small_complex_kernel(const Smal
                     constexpr int p = decltype(pc)::value;
                     *reinterpret_cast<uint32_t*>(dst + (p - 1) * SLICE) = packed_slice<WIDE>(x, sm, p);
                 });
-                if (counted) {
-                    unsigned l2[2] = {lost[2 * pl], lost[2 * pl + 1]};
-                    small_count(l2, v[o][pl][i], E, S);
-                    lost[2 * pl] = l2[0];
-                    lost[2 * pl + 1] = l2[1];
-                }
             }
         }
-        if (counted) small_put_counts(lost, count_lds[o], g.counts + 4 * (o ? (g.m + kSmallTile - 1) / kSmallTile + tn : tm));
     }
     __syncthreads();
 
     // ---- 16 x 16 complex elements to a wavefront: G(Ar,Br), G(Ai,Bi), G(Ar,Bi), G(Ai,Br) in turn
-    if (wave >= 4) return;
-    const int pi = wave >> 1, pj = wave & 1;
-    const int row0 = tm * kSmallTile + 16 * pi + 4 * (lane >> 4), col = tn * kSmallTile + 16 * pj + (lane & 15);
-    double re[4], im[4];
-    static_for<0, 4>([&](auto ic) __attribute__((always_inline)) {
-        constexpr int product = decltype(ic)::value, pa = product & 1, pb = product == 1 || product == 2 ? 1 : 0;
-        v4i acc[S];
+    if (wave < 4) {
+        const int pi = wave >> 1, pj = wave & 1;
+        const int row0 = tm * kSmallTile + 16 * pi + 4 * (lane >> 4), col = tn * kSmallTile + 16 * pj + (lane & 15);
+        double re[4], im[4];
+        static_for<0, 4>([&](auto ic) __attribute__((always_inline)) {
+            constexpr int product = decltype(ic)::value, pa = product & 1, pb = product == 1 || product == 2 ? 1 : 0;
+            v4i acc[S];
 #pragma unroll
-        for (int e = 0; e < S; ++e) acc[e] = v4i{0, 0, 0, 0};
+            for (int e = 0; e < S; ++e) acc[e] = v4i{0, 0, 0, 0};
 #pragma unroll
-        for (int step = 0; step < KS; ++step) {
-            v4i a[S], b[S];
+            for (int step = 0; step < KS; ++step) {
+                v4i a[S], b[S];
 #pragma unroll
-            for (int p = 0; p < S; ++p) {
-                a[p] = *reinterpret_cast<const v4i*>(lds + pa * PLANE + p * SLICE + step * STEP + pi * kFragBytes + 16 * lane);
-                b[p] = *reinterpret_cast<const v4i*>(lds + OPERAND + pb * PLANE + p * SLICE + step * STEP + pj * kFragBytes + 16 * lane);
+                for (int p = 0; p < S; ++p) {
+                    a[p] = *reinterpret_cast<const v4i*>(lds + pa * PLANE + p * SLICE + step * STEP + pi * kFragBytes + 16 * lane);
+                    b[p] = *reinterpret_cast<const v4i*>(lds + OPERAND + pb * PLANE + p * SLICE + step * STEP + pj * kFragBytes + 16 * lane);
+                }
+#pragma unroll
+                for (int q = 0; q < S; ++q)
+#pragma unroll
+                    for (int p = S - 1 - q; p >= 0; --p) acc[p + q] = mfma16(a[p], b[q], acc[p + q]);
             }
+            double sum[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int q = 0; q < S; ++q)
+            for (int e = S - 1; e >= 0; --e) {
+                const double sc = __longlong_as_double((long long)(1023 - OZIMMU_SLICE_BITS * (e + 2)) << 52);
 #pragma unroll
-                for (int p = S - 1 - q; p >= 0; --p) acc[p + q] = mfma16(a[p], b[q], acc[p + q]);
+                for (int u = 0; u < 4; ++u) sum[u] = fma((double)acc[e][u], sc, sum[u]);
+            }
+            const int eb = ex[1][pb][16 * pj + (lane & 15)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const double val = ldexp(sum[u], ex[0][pa][16 * pi + 4 * (lane >> 4) + u] + eb);
+                if constexpr (product == 0) re[u] = val;
+                else if constexpr (product == 1) re[u] = re[u] - val;
+                else if constexpr (product == 2) im[u] = val;
+                else im[u] = im[u] + val;
+            }
+        });
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (row0 + u < g.m && col < g.n) {
+                double* c = g.C + 2 * ((int64_t)(row0 + u) * g.ldc + col);
+                c[0] = re[u];
+                c[1] = im[u];
+            }
+    }
+
+    // ---- the check of S as the automatic slice count (the other wavefronts count while those four multiply)
+    if (!g.counts) return;
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+        if (!(o ? small_counts_columns(tm, tn, g) : small_counts_rows(tm, tn, g))) continue;
+        unsigned lost[4];
+#pragma unroll
+        for (int pl = 0; pl < 2; ++pl) {
+            unsigned of_plane[2] = {0u, 0u};
+            const int E = ex[o][pl][vec[o]];
+#pragma unroll
+            for (int i = 0; i < W; ++i) small_count(of_plane, v[o][pl][i], E, S);
+            lost[2 * pl] = of_plane[0];
+            lost[2 * pl + 1] = of_plane[1];
         }
-        double sum[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int e = S - 1; e >= 0; --e) {
-            const double sc = __longlong_as_double((long long)(1023 - OZIMMU_SLICE_BITS * (e + 2)) << 52);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) sum[u] = fma((double)acc[e][u], sc, sum[u]);
-        }
-        const int eb = ex[1][pb][16 * pj + (lane & 15)];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const double val = ldexp(sum[u], ex[0][pa][16 * pi + 4 * (lane >> 4) + u] + eb);
-            if constexpr (product == 0) re[u] = val;
-            else if constexpr (product == 1) re[u] = re[u] - val;
-            else if constexpr (product == 2) im[u] = val;
-            else im[u] = im[u] + val;
-        }
-    });
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-        if (row0 + u < g.m && col < g.n) {
-            double* c = g.C + 2 * ((int64_t)(row0 + u) * g.ldc + col);
-            c[0] = re[u];
-            c[1] = im[u];
-        }
+        small_put_counts(lost, count_lds[o], g.counts + 4 * (o ? (g.m + kSmallTile - 1) / kSmallTile + tn : tm));
+    }
 }
 
 template <int S, int KS>
