@@ -305,7 +305,7 @@ ozimmu_status_t ozimmu_auto_num_slices(int64_t m, int64_t n, int64_t k, const do
  * workspace: at least the largest ozimmu_workspace_bytes(m, n, k, s, is_complex) over
  * s = 1 .. max_slices; scratch: as for ozimmu_auto_num_slices. Waits for the stream like
  * ozimmu_auto_num_slices; errors as there and as for ozimmu_dgemm. These calls and
- * ozimmu_auto_num_slices receive their sums in 17 KiB of mapped host memory that the first such
+ * ozimmu_auto_num_slices receive their sums in 33 KiB of mapped host memory that the first such
  * call of a thread allocates and that is kept until the process ends.
  */
 ozimmu_status_t ozimmu_dgemm_auto(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,

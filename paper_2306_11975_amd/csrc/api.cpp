@@ -172,7 +172,7 @@ struct Stored {
 // [planes][16], device or mapped host memory): the splitters also count for the check of s as the automatic slice count
 // (Section 4.4), and the bits the planes lose with s and with s - 1 slices arrive there.
 hipError_t split_operands(const Layout& L, bool cplx, const Stored& a, const Stored& b, int64_t k, int s, unsigned char* ws,
-                          hipStream_t st, unsigned long long* sums_a = nullptr, unsigned long long* sums_b = nullptr) {
+                          hipStream_t st, unsigned long long* sums_a = nullptr, unsigned long long* sums_b = nullptr, PairCounts* to_host = nullptr) {
     const int planes = cplx ? 2 : 1;
     unsigned long long* colmax = reinterpret_cast<unsigned long long*>(ws + L.off_colmax);
     unsigned long long* slots[2] = {nullptr, nullptr};
@@ -186,7 +186,7 @@ hipError_t split_operands(const Layout& L, bool cplx, const Stored& a, const Sto
         }
     }
     if (split_pair_applies(x[0], x[1], planes, L.k_pad, s, sums_a != nullptr))
-        return launch_split_pair(x[0], x[1], planes, k, L.k_pad, s, st, sums_a ? reinterpret_cast<unsigned*>(ws + L.off_scan) : nullptr, sums_a, sums_b);
+        return launch_split_pair(x[0], x[1], planes, k, L.k_pad, s, st, sums_a ? reinterpret_cast<unsigned*>(ws + L.off_scan) : nullptr, sums_a, sums_b, to_host);
     hipError_t e = hipSuccess;
     if (sums_a) {
         slots[0] = reinterpret_cast<unsigned long long*>(ws + L.off_scan);
@@ -341,8 +341,8 @@ hipError_t scan_operand(const ScanOperand& z, int o, int is_complex, unsigned lo
     return e;
 }
 
-// The counters that the kernels for small products leave, per tile of rows and of columns, two planes at most
-constexpr int kMappedSums = 4 * OZIMMU_MAX_SLICES, kMappedCounts = 4 * (kSmallMaxTiles + 1);
+// The counters that the kernels for small products leave, per tile of rows and of columns, two planes at most, or the splitter of both operands
+constexpr int kMappedSums = 4 * OZIMMU_MAX_SLICES, kMappedCounts = std::max(4 * (kSmallMaxTiles + 1), kPairCountWords);
 
 // 4 x 16 sums, and room for those counters behind them, in host memory that kernels of any device can write (one buffer per calling
 // thread, kept until the process ends)
@@ -491,13 +491,15 @@ ozimmu_status_t gemm_auto(bool cplx, int64_t m, int64_t n, int64_t k, const doub
         // sums for `guess` and `guess - 1` in the mapped buffer, and the product follows at once; one wait at the end.
         L = make_layout(m, n, k, guess, cplx);
         unsigned char* ws = static_cast<unsigned char*>(workspace);
-        hipError_t e = split_operands(L, cplx, Stored{A, lda, m, false, false}, Stored{B, ldb, n, true, false}, k, guess, ws, st, host,
-                                      host + (cplx ? 2 : 1) * OZIMMU_MAX_SLICES);
+        unsigned long long* const host_b = host + (cplx ? 2 : 1) * OZIMMU_MAX_SLICES;
+        PairCounts counts{reinterpret_cast<unsigned*>(host + kMappedSums), 0, 0};
+        hipError_t e = split_operands(L, cplx, Stored{A, lda, m, false, false}, Stored{B, ldb, n, true, false}, k, guess, ws, st, host, host_b, &counts);
         if (e == hipSuccess)
             e = cplx ? run_complex_products(L, m, n, guess, ws, C, ldc, st, room_behind(ws, L.total, workspace_bytes))
                      : run_product(L, m, n, guess, ws, 0, 0, C, ldc, 0, st, room_behind(ws, L.total, workspace_bytes));
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) return OZIMMU_ERR_HIP;
+        if (counts.blocks) add_pair_counts(counts, cplx ? 2 : 1, guess, host, host_b);
         if (guess_holds(host, cplx ? 4 : 2, count_a, count_b, threshold, guess, max_slices)) {
             *num_slices = guess;
             if (guess_confirmed) *guess_confirmed = 1;

@@ -174,8 +174,17 @@ struct SplitOperand {
 // bytes, need not be cleared): it also counts, and the bits the planes lose with s and with s - 1 slices arrive in sums_a
 // and sums_b ([planes][16]; device or mapped host memory).
 bool split_pair_applies(const SplitOperand& a, const SplitOperand& b, int planes, int64_t k_pad, int s, bool counting);
+// to_host (optional; its words: kPairCountWords of mapped host memory): where they fit, the counters of its workgroups go there instead and no launch adds
+// them up (its blocks is then set); add_pair_counts does, once the stream has been waited for. (Automatic mode, per call: 376 x 2594 x 67 at threshold
+// 1 45.9 -> 39.9 us, 508 x 2683 x 390 65.4 -> 60.4, 2048^3 at twelve slices 486 -> 480. More words than that: the launch that adds them up takes less than the host.)
+constexpr int kPairCountWords = 8192;
+struct PairCounts {
+    unsigned* words;
+    unsigned first, blocks;      // workgroups of the first operand, and of both (0: not used)
+};
 hipError_t launch_split_pair(const SplitOperand& a, const SplitOperand& b, int planes, int64_t k, int64_t k_pad, int s, hipStream_t st,
-                             unsigned* partials, unsigned long long* sums_a, unsigned long long* sums_b);
+                             unsigned* partials, unsigned long long* sums_a, unsigned long long* sums_b, PairCounts* to_host);
+void add_pair_counts(const PairCounts& c, int planes, int s, unsigned long long* sums_a, unsigned long long* sums_b);
 hipError_t launch_scan_reduce(const unsigned long long* slots, int planes, int s, unsigned long long* out_first,
                               unsigned long long* out_second, hipStream_t st);
 hipError_t launch_split_rows(const double* A, int64_t lda, int inc, int64_t m, int64_t k, int s,

@@ -447,7 +447,7 @@ struct SplitSide {
 // PL planes (2: interleaved complex), four words of four positions per thread of a column, R per thread of a row.
 template <bool WIDE, bool SCAN, int PL, int R>
 __global__ __launch_bounds__(64 * kRowWavesMax) void split_pair_kernel(const SplitSide first, const SplitSide second, int k, int k_pad, int s,
-                                                                       unsigned* __restrict__ partials, uint32_t edge_g, uint32_t edge_h) {
+                                                                       unsigned* __restrict__ partials, bool by_block, uint32_t edge_g, uint32_t edge_h) {
     constexpr int J = 4;
     const bool is_first = blockIdx.x < first.blocks;
     const SplitSide& side = is_first ? first : second;
@@ -568,7 +568,8 @@ __global__ __launch_bounds__(64 * kRowWavesMax) void split_pair_kernel(const Spl
         }
     }
     if constexpr (SCAN) {
-        // this workgroup's counters, [counter][workgroup]: nothing to clear, nothing to add up atomically
+        // this workgroup's counters, [counter][workgroup] (by_block: the other way round, so that a workgroup writes in one piece what goes to
+        // host memory): nothing to clear, nothing to add up atomically
 #pragma unroll
         for (int pl = 0; pl < PL; ++pl) {
             unsigned c[kScanCounters] = {cnt[pl].sv_g, cnt[pl].sz_g, cnt[pl].sv_h, cnt[pl].sz_h, cnt[pl].bits};
@@ -583,7 +584,7 @@ __global__ __launch_bounds__(64 * kRowWavesMax) void split_pair_kernel(const Spl
         if (tid < PL * kScanCounters) {
             unsigned total = 0;
             for (int w = 0; w < nwaves; ++w) total += counts[tid][w];
-            partials[(size_t)tid * gridDim.x + blockIdx.x] = total;
+            partials[by_block ? (size_t)blockIdx.x * (PL * kScanCounters) + tid : (size_t)tid * gridDim.x + blockIdx.x] = total;
         }
     }
 }
@@ -1135,8 +1136,23 @@ bool split_pair_applies(const SplitOperand& a, const SplitOperand& b, int planes
     return (a.padded + b.padded) * k_pad * planes <= (int64_t)8 << 20;
 }
 
+void add_pair_counts(const PairCounts& c, int planes, int s, unsigned long long* sums_a, unsigned long long* sums_b) {
+    const int nc = planes * kScanCounters;
+    for (int o = 0; o < 2; ++o) {
+        unsigned long long sum[2 * kScanCounters] = {};
+        for (unsigned i = o ? c.first : 0; i < (o ? c.blocks : c.first); ++i)
+            for (int j = 0; j < nc; ++j) sum[j] += c.words[(size_t)i * nc + j];
+        unsigned long long* out = o ? sums_b : sums_a;
+        for (int pl = 0; pl < planes; ++pl) {
+            const unsigned long long* x = sum + pl * kScanCounters;
+            out[pl * OZIMMU_MAX_SLICES + s - 1] = (x[0] - x[1] + x[4]) >> 1;
+            if (s > 1) out[pl * OZIMMU_MAX_SLICES + s - 2] = (x[2] - x[3] + x[4]) >> 1;
+        }
+    }
+}
+
 hipError_t launch_split_pair(const SplitOperand& a, const SplitOperand& b, int planes, int64_t k, int64_t k_pad, int s, hipStream_t st,
-                             unsigned* partials, unsigned long long* sums_a, unsigned long long* sums_b) {
+                             unsigned* partials, unsigned long long* sums_a, unsigned long long* sums_b, PairCounts* to_host) {
     if (!split_pair_applies(a, b, planes, k_pad, s, partials != nullptr)) return hipErrorInvalidValue;
     const PairShape shape = pair_shape(a, b, planes, k_pad, s, partials != nullptr);
     auto side = [&](const SplitOperand& x, int i) {
@@ -1160,7 +1176,13 @@ hipError_t launch_split_pair(const SplitOperand& a, const SplitOperand& b, int p
     const SplitSide sa = side(a, 0), sb = side(b, 1);
     const ScanTarget scan = scan_target(nullptr, 0, s);
     const dim3 grid(sa.blocks + sb.blocks), block(64 * shape.waves);
-#define OZ_PAIR(W, SC, PL, R) split_pair_kernel<W, SC, PL, R><<<grid, block, 0, st>>>(sa, sb, (int)k, (int)k_pad, s, partials, scan.edge_g, scan.edge_h)
+    const bool by_block = partials && to_host && to_host->words && grid.x * planes * kScanCounters <= kPairCountWords;
+    if (by_block) {
+        partials = to_host->words;
+        to_host->first = sa.blocks;
+        to_host->blocks = grid.x;
+    }
+#define OZ_PAIR(W, SC, PL, R) split_pair_kernel<W, SC, PL, R><<<grid, block, 0, st>>>(sa, sb, (int)k, (int)k_pad, s, partials, by_block, scan.edge_g, scan.edge_h)
 #define OZ_PAIRS(W, SC) do { \
         if (planes == 2) { if (!W && shape.row_words == 4) OZ_PAIR(W, SC, 2, W ? 1 : 4); else OZ_PAIR(W, SC, 2, 1); } \
         else if (!(W && SC) && shape.row_words == 4) OZ_PAIR(W, SC, 1, W && SC ? 1 : 4); \
@@ -1171,7 +1193,7 @@ hipError_t launch_split_pair(const SplitOperand& a, const SplitOperand& b, int p
 #undef OZ_PAIRS
 #undef OZ_PAIR
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess && partials) {
+    if (e == hipSuccess && partials && !by_block) {
         split_pair_reduce_kernel<<<dim3(1), dim3(1024), 0, st>>>(partials, sa.blocks, grid.x, planes, s, sums_a, sums_b);
         e = hipGetLastError();
     }
