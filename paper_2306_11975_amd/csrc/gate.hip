@@ -104,15 +104,16 @@ __global__ __launch_bounds__(512) void gate_split_kernel(const double* __restric
 // The counters of all tiles ([counter][tile]) and of the gate's fragments (behind them, [4][nfr]) -> the bits the two
 // planes of Z (planes 0, 1) and of B (planes 2, 3) lose with s and with s - 1 slices: out[plane * 16 + s - 1] and
 // out[plane * 16 + s - 2], the layout of the slice-count sums. `out` may be mapped host memory. One workgroup.
+// U: tiles to a thread at a time.
+template <int U>
 __global__ __launch_bounds__(1024) void gate_scan_reduce_kernel(const unsigned* __restrict__ partials, int64_t tiles, int nfr,
                                                                 int s, unsigned long long* __restrict__ out) {
     __shared__ unsigned long long sums[2 * kScanCounters + 4];
     if (threadIdx.x < 2 * kScanCounters + 4) sums[threadIdx.x] = 0ull;
     __syncthreads();
-    // eighty loads in flight per thread (the words come from beyond the L2, written by other XCDs); a tile index past
+    // ten U loads in flight per thread (the words come from beyond the L2, written by other XCDs); a tile index past
     // the end reads the last tile and adds nothing
     unsigned long long mine[2 * kScanCounters] = {};
-    constexpr int U = 8;
     for (int64_t base = threadIdx.x; base < tiles; base += 1024 * U) {
         unsigned v[U][2 * kScanCounters];
 #pragma unroll
@@ -201,7 +202,9 @@ hipError_t launch_gate_product(const double* Z, int64_t ldz, int64_t m, int64_t 
         default: e = launch_gate_many(g, cls, s, st);
     }
     if (e == hipSuccess && scan_partials) {
-        gate_scan_reduce_kernel<<<dim3(1), dim3(1024), 0, st>>>(scan_partials, tiles, nfr, s, scan_sums);
+        // (with few tiles the loads past the end would be most of them)
+        if (tiles <= 2048) gate_scan_reduce_kernel<2><<<dim3(1), dim3(1024), 0, st>>>(scan_partials, tiles, nfr, s, scan_sums);
+        else gate_scan_reduce_kernel<8><<<dim3(1), dim3(1024), 0, st>>>(scan_partials, tiles, nfr, s, scan_sums);
         e = hipGetLastError();
     }
     return e;
