@@ -53,8 +53,10 @@ static inline bool use_small_tiles(int64_t m, int64_t n, int64_t k_pad, int s, b
     }
     if (k_pad <= 512 || large < kComputeUnits) return true;
     if (large == kComputeUnits) return false;
-    // what a step of the small tiles takes more (five and six slices: their loads are covered least)
-    const double more = s == 9 ? -0.01 : s == 8 ? 0.012 : s == 7 ? 0.015 : 0.065;
+    // what a step of the small tiles takes more (five and six slices: their loads are covered least; of seven and eight, in few rounds, less is
+    // covered than in many: complex 217 x 3797 x 1568 at seven, two rounds of either, 195 -> 201 us, 808 x 1024 x 1024 97 -> 99: both stay large)
+    const double few = large_rounds < 8 ? 0.04 : 0.0;
+    const double more = s == 9 ? -0.01 : s == 8 ? 0.012 + few : s == 7 ? 0.015 + few : 0.065;
     // a last round of small tiles with a compute unit to each takes 0.6 of one with two
     const int64_t pairs = 2 * kComputeUnits, rest = small % pairs;
     const double small_rounds = (double)(small / pairs) + (rest == 0 ? 0.0 : rest <= kComputeUnits ? 0.6 : 1.0);
