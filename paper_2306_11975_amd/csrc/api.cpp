@@ -686,7 +686,7 @@ ozimmu_status_t ozimmu_zgemm(int64_t m, int64_t n, int64_t k, const double* A, i
     const int s = num_slices;
     hipError_t e = hipSuccess;
     // a few tiles and a short inner dimension: one launch, without the workspace
-    if (small_complex_applies(m, n, k, s))
+    if (small_complex_ahead(A, B, C, m, n, k, s))
         return hip_status(launch_small_complex(SmallArgs{{{A, lda, false}, {B, ldb, true}}, (int)m, (int)n, (int)k, C, ldc, 0, 1.0, 0.0, nullptr, nullptr}, s, st));
     // a small B on a tall A (a gate on a state vector): one kernel that splits A on the fly and reads it once
     if (gate_product_applies(A, B, C, n, k, s)) return hip_status(launch_gate_product(A, lda, m, k, n, B, ldb, s, ws + L.off_gate, C, ldc, st));
@@ -841,7 +841,7 @@ static ozimmu_status_t zgemm_blas_impl(char transa, char transb, int64_t m, int6
     // Neither operand transposed, a small A on a wide B (a gate on a state vector whose amplitudes are the columns'
     // entries): the row-major product B^T A^T has the state as its tall operand and takes the one-kernel path.
     // (Few tiles and a short inner dimension: in one launch.)
-    const bool small = small_complex_applies(n, m, k, num_slices);
+    const bool small = small_complex_ahead(B, A, G, n, m, k, num_slices);
     if (!count_sums && !ta && !tb && (small || gate_product_applies(B, A, G, m, k, num_slices))) {
         e = small ? launch_small_complex(SmallArgs{{{B, ldb, false}, {A, lda, true}}, (int)n, (int)m, (int)k, G, ldg, 0, 1.0, 0.0, nullptr, nullptr}, num_slices, st)
                   : launch_gate_product(B, ldb, n, k, m, A, lda, num_slices, ws + L.off_gate, G, ldg, st);

@@ -424,7 +424,7 @@ hipError_t launch_gate_one(const GateArgs& g, hipStream_t st) {
 }
 template <int S, int CLS, bool SCAN, int FEW>
 hipError_t launch_gate(const GateArgs& g, hipStream_t st) {
-    if constexpr (CLS == 0 && FEW == 0) {   // (more than 32 columns: fewer, with so few rows, are a product for small_complex.hip)
+    if constexpr (CLS == 0 && FEW == 0 && (SCAN || S <= 11)) {   // (more than 32 columns: fewer, with so few rows, are small_complex.hip's, but for small_complex_ahead's)
         return launch_gate_one<S, CLS, SCAN, FEW, true>(g, st);
     } else {
         if constexpr (CLS == 0 && FEW != 3) {
@@ -438,8 +438,9 @@ hipError_t launch_gate(const GateArgs& g, hipStream_t st) {
 template <int S, int CLS>
 hipError_t launch_gate(const GateArgs& g, hipStream_t st) {
     if constexpr (CLS == 0) {
-        // no more tiles than compute units: eight wavefronts share a tile, whose time is what the call takes (1024 x 64 x 64
-        // 14.2 -> 13.0 us per call); with more tiles four wavefronts each, four tiles to a compute unit, are faster
+        // no more tiles than compute units: eight wavefronts share a tile, whose time is what the call takes; with more tiles
+        // four wavefronts each, four tiles to a compute unit, are faster (8192 x 64 x 64 at eight slices 14.7 us per call with four
+        // wavefronts, 13.3 with eight; 4200 x 64 x 64 at sixteen 24.0, 21.9)
         if (g.m <= (int64_t)kGateRows * kComputeUnits) return g.scan ? launch_gate<S, 0, true, 0>(g, st) : launch_gate<S, 0, false, 0>(g, st);
         if (g.k <= 16 && g.n <= 8) return g.scan ? launch_gate<S, 0, true, 3>(g, st) : launch_gate<S, 0, false, 3>(g, st);
         if (g.k <= 32 && g.n <= 32) return g.scan ? launch_gate<S, 0, true, 1>(g, st) : launch_gate<S, 0, false, 1>(g, st);

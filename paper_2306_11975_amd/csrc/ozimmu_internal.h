@@ -150,6 +150,8 @@ bool small_product_applies(int64_t m, int64_t n, int64_t k, int s);
 hipError_t launch_small_product(const SmallArgs& g, int s, hipStream_t st);
 // The same for a complex product, its operands and C interleaved (leading dimensions in complex elements; c_mode 0).
 bool small_complex_applies(int64_t m, int64_t n, int64_t k, int s);
+// Whether a product that is not counted takes it (Z, B, Cz: where the gate kernel could serve instead).
+bool small_complex_ahead(const double* Z, const double* B, const double* Cz, int64_t m, int64_t n, int64_t k, int s);
 hipError_t launch_small_complex(const SmallArgs& g, int s, hipStream_t st);
 constexpr int kSmallTileRows = 32;   // rows and columns of their tiles
 constexpr int kSmallMaxTiles = 1024; // and at most so many of them

@@ -84,6 +84,13 @@ bool small_complex_applies(int64_t m, int64_t n, int64_t k, int s) {
     return small_tiles(m, n) <= kComputeUnits;
 }
 
+// A gate of up to sixteen columns leaves half of a tile and more empty, and its MFMAs are what many slices take: there the gate kernel's two launches are
+// as fast at eleven slices and ahead beyond (per call, 8192 x 2 x 2 at eleven, thirteen and sixteen 11.5, 12.2, 13.5 us, here 11.3, 12.8, 14.9; 2000 x 16 x 16
+// at sixteen 13.6, here 14.7; 20 columns 14.6, here 14.7; counting, where that kernel takes a third launch, this one stays ahead).
+bool small_complex_ahead(const double* Z, const double* B, const double* Cz, int64_t m, int64_t n, int64_t k, int s) {
+    return small_complex_applies(m, n, k, s) && !(n <= 16 && s > 11 && gate_product_applies(Z, B, Cz, n, k, s));
+}
+
 hipError_t launch_small_complex(const SmallArgs& g, int s, hipStream_t st) {
     if (!small_complex_applies(g.m, g.n, g.k, s)) return hipErrorInvalidValue;
     switch (s) {

@@ -1,10 +1,13 @@
-"""The kernels for small products, as built: no instantiation spills registers (a complex patch's four products, and the elements kept for the check of
-the slice count, have to fit them at every slice count)."""
+"""The kernels for small products on the host: no instantiation spills registers (a complex patch's four products, and the elements kept for the check of
+the slice count, have to fit them at every slice count), and the rules that choose them keep to the sizes where they take less than two launches."""
+import ctypes
 import struct
 
 import msgpack
+import pytest
 
 from paper_2306_11975_amd import build
+from paper_2306_11975_amd import ozimmu
 
 
 def kernels_of(path):
@@ -36,3 +39,22 @@ def test_small_kernels_do_not_spill():
     assert len(small) > 60
     spilling = {n: k[".vgpr_spill_count"] for n, k in small.items() if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]}
     assert not spilling, spilling
+
+
+def rule(symbol, *types):
+    f = getattr(ozimmu.lib(), symbol)
+    f.restype, f.argtypes = ctypes.c_bool, types
+    return f
+
+
+I64, PTR = ctypes.c_int64, ctypes.c_void_p
+COMPLEX_AHEAD = "_ZN6ozimmu19small_complex_aheadEPKdS1_S1_llli"
+
+
+@pytest.mark.parametrize("m,n,k,s,ahead", [(8192, 2, 2, 11, True), (8192, 2, 2, 12, False), (300, 16, 16, 16, False), (300, 17, 16, 16, True), (2000, 16, 64, 13, False),
+                                           (4096, 64, 16, 16, True), (1, 1, 1, 12, False), (8225, 2, 2, 3, False)])
+def test_narrow_gates_of_many_slices_are_left_to_the_gate_kernel(m, n, k, s, ahead):
+    f = rule(COMPLEX_AHEAD, PTR, PTR, PTR, I64, I64, I64, ctypes.c_int)
+    assert f(256, 512, 1024, m, n, k, s) == ahead
+    # operands that the gate kernel does not take (8 bytes off a complex element's alignment) have only the general path otherwise
+    assert f(256, 512, 1032, m, n, k, s) == (m <= 8192)
