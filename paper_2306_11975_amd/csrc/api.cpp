@@ -774,7 +774,7 @@ static ozimmu_status_t dgemm_blas_impl(char transa, char transb, int64_t m, int6
         return OZIMMU_ERR_WORKSPACE;
     unsigned char* ws = static_cast<unsigned char*>(workspace);
     // op(B)^T: n rows of length k (B stored k x n by columns, or n x k); op(A): m rows of length k (A m x k, or k x m)
-    if (!count_sums && small_product_applies(n, m, k, num_slices))
+    if (!count_sums && small_product_applies(n, m, k, num_slices, ta && !tb))
         return hip_status(launch_small_product(SmallArgs{{{B, ldb, tb}, {A, lda, !ta}}, (int)n, (int)m, (int)k, C, ldc, 3, alpha, beta, nullptr, nullptr}, num_slices, st));
     hipError_t e = split_operands(L, false, Stored{B, ldb, n, tb, false}, Stored{A, lda, m, !ta, false}, k, num_slices, ws, st,
                                   count_sums ? count_sums + OZIMMU_MAX_SLICES : nullptr, count_sums);

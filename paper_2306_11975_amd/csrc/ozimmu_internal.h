@@ -146,7 +146,8 @@ struct SmallArgs {
     unsigned* counts;        // not null (device or mapped host memory): [row tiles, then column tiles][planes][2], the bits that a tile's rows
                              // (columns) lose with s and with s - 1 slices
 };
-bool small_product_applies(int64_t m, int64_t n, int64_t k, int s);
+// both_by_rows: neither operand by its columns
+bool small_product_applies(int64_t m, int64_t n, int64_t k, int s, bool both_by_rows = false);
 hipError_t launch_small_product(const SmallArgs& g, int s, hipStream_t st);
 // The same for a complex product, its operands and C interleaved (leading dimensions in complex elements; c_mode 0).
 bool small_complex_applies(int64_t m, int64_t n, int64_t k, int s);

@@ -79,16 +79,25 @@ hipError_t launch_small(const SmallArgs& g, hipStream_t st) {
 }  // namespace
 
 // All of k has to fit the LDS (128 KiB: two steps, four up to eight slices). What the tiles repeat makes the rest: a compute unit's time goes with its
-// tiles times steps, and four of those are where two launches are as fast (1024 x 1024 x 64 at three, eight and sixteen slices 11.5, 14.8 and 23.0 us, here 9.9, 13.1 and
-// 22.7; 2048 x 1024 x 64 at eight 17.8, here 22.1; 512 x 1024 x 128 at eight 15.3, here 10.9; 512 x 512 x 200 at eight 18.1, here 11.6, 512 x 1024 x 256 at five 14.8, here 19.4).
-bool small_product_applies(int64_t m, int64_t n, int64_t k, int s) {
+// tiles times steps, and four of those are where two launches are as fast (1024 x 1024 x 64 at three, eight and sixteen slices 12.0, 15.1 and 24.3 us, here 9.9, 12.9 and
+// 22.4; 2048 x 1024 x 64 at eight 17.8, here 22.1; 512 x 1024 x 128 at eight 15.5, here 10.9, at thirteen 29.6, here 20.5; 512 x 512 x 200 at eight 18.1, here 11.6,
+// 512 x 1024 x 256 at five 14.8, here 19.4). The two launches take less where
+//  - both operands are read along k (rows: the BLAS-style call of A transposed and B not): at one step three, but for ten to thirteen slices (1024 x 1024 x 64 in a graph at one, six, nine
+//    and sixteen 9.0, 12.3, 14.7 and 21.0 us, here 10.5, 13.0, 15.4 and 23.2; at thirteen 22.5, here 19.7);
+//  - the product kernel saves half a step of one (k up to 32 with more than nine slices): three for rows along k (1024 x 1024 x 30 at twelve 16.1, here 18.3), and from fourteen slices
+//    on one less of either (at fourteen 17.7, here 18.4, 768 x 1024 x 30 17.4, here 14.8; rows along k 768 x 1024 x 30 14.8, here 15.6, 512 x 1024 x 30 14.6, here 11.4).
+bool small_product_applies(int64_t m, int64_t n, int64_t k, int s, bool both_by_rows) {
     if (s < 1 || s > OZIMMU_MAX_SLICES || m < 1 || n < 1 || k < 1 || k > (s <= kBand ? 4 : 2) * kSmallStep) return false;
     const int64_t steps = k <= kSmallStep ? 1 : k <= 2 * kSmallStep ? 2 : 4;
-    return small_tiles(m, n) * steps <= 4 * kComputeUnits;
+    const bool half_step = k <= kSlab && s > 9;
+    int64_t per_unit = 4;
+    if (both_by_rows && steps == 1 && (s <= 9 || s >= 14 || half_step)) per_unit -= 1;
+    if (half_step && s >= 14) per_unit -= 1;
+    return small_tiles(m, n) * steps <= per_unit * kComputeUnits;
 }
 
 hipError_t launch_small_product(const SmallArgs& g, int s, hipStream_t st) {
-    if (!small_product_applies(g.m, g.n, g.k, s)) return hipErrorInvalidValue;
+    if (!small_product_applies(g.m, g.n, g.k, s, !g.x[0].by_cols && !g.x[1].by_cols)) return hipErrorInvalidValue;
     switch (s) {
 #define OZ_CASE(S_) case S_: return launch_small<S_>(g, st);
         OZ_CASE(1) OZ_CASE(2) OZ_CASE(3) OZ_CASE(4) OZ_CASE(5) OZ_CASE(6) OZ_CASE(7) OZ_CASE(8)

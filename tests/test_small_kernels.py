@@ -58,3 +58,18 @@ def test_narrow_gates_of_many_slices_are_left_to_the_gate_kernel(m, n, k, s, ahe
     assert f(256, 512, 1024, m, n, k, s) == ahead
     # operands that the gate kernel does not take (8 bytes off a complex element's alignment) have only the general path otherwise
     assert f(256, 512, 1032, m, n, k, s) == (m <= 8192)
+
+
+# 32 x 32 tiles times steps of 64 positions: four to a compute unit, fewer where two launches take less
+@pytest.mark.parametrize("m,n,k,s,by_rows,applies", [
+    (1024, 1024, 64, 8, False, True), (1025, 1024, 64, 8, False, False), (512, 1024, 128, 16, False, True), (512, 1024, 129, 8, False, False),
+    (256, 1024, 256, 8, False, True), (256, 1024, 256, 9, False, False),
+    # both operands along k, at one step: three, but four with ten to thirteen slices
+    (768, 1024, 64, 9, True, True), (769, 1024, 64, 9, True, False), (1024, 1024, 64, 10, True, True), (1024, 1024, 64, 13, True, True), (769, 1024, 64, 14, True, False),
+    (512, 1024, 128, 9, True, True), (256, 1024, 256, 3, True, True),
+    # half a step with more than nine slices
+    (1024, 1024, 32, 13, False, True), (1024, 1024, 32, 14, False, False), (768, 1024, 32, 16, False, True), (1024, 1024, 33, 16, False, True),
+    (769, 1024, 32, 10, True, False), (768, 1024, 32, 13, True, True), (513, 1024, 32, 14, True, False), (512, 1024, 32, 16, True, True)])
+def test_limits_of_the_small_product(m, n, k, s, by_rows, applies):
+    f = rule("_ZN6ozimmu21small_product_appliesElllib", I64, I64, I64, ctypes.c_int, ctypes.c_bool)
+    assert f(m, n, k, s, by_rows) == applies
