@@ -341,7 +341,8 @@ hipError_t scan_operand(const ScanOperand& z, int o, int is_complex, unsigned lo
     return e;
 }
 
-// The counters that the kernels for small products leave, per tile of rows and of columns, two planes at most, or the splitter of both operands
+// The counters that the kernels for small products leave, two per plane (two at most) and tile of rows or of columns (m tiles of rows times n of
+// columns are kSmallMaxTiles at most, so m + n are no more than those and one), or the splitter of both operands
 constexpr int kMappedSums = 4 * OZIMMU_MAX_SLICES, kMappedCounts = std::max(4 * (kSmallMaxTiles + 1), kPairCountWords);
 
 // 4 x 16 sums, and room for those counters behind them, in host memory that kernels of any device can write (one buffer per calling

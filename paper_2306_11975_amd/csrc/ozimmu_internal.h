@@ -155,7 +155,8 @@ bool small_complex_applies(int64_t m, int64_t n, int64_t k, int s);
 bool small_complex_ahead(const double* Z, const double* B, const double* Cz, int64_t m, int64_t n, int64_t k, int s);
 hipError_t launch_small_complex(const SmallArgs& g, int s, hipStream_t st);
 constexpr int kSmallTileRows = 32;   // rows and columns of their tiles
-constexpr int kSmallMaxTiles = 1024; // and at most so many of them
+constexpr int kSmallTilesPerUnit = 4;                                      // tiles times steps to a compute unit, at most
+constexpr int kSmallMaxTiles = kSmallTilesPerUnit * kComputeUnits;         // so that many tiles (complex: fewer), whose counters the caller has room for
 
 // negate: emit the slices of -A (-B) instead: same exponents, every slice with the opposite sign
 // (how a conjugated operand's imaginary plane is split)

@@ -90,7 +90,7 @@ bool small_product_applies(int64_t m, int64_t n, int64_t k, int s, bool both_by_
     if (s < 1 || s > OZIMMU_MAX_SLICES || m < 1 || n < 1 || k < 1 || k > (s <= kBand ? 4 : 2) * kSmallStep) return false;
     const int64_t steps = k <= kSmallStep ? 1 : k <= 2 * kSmallStep ? 2 : 4;
     const bool half_step = k <= kSlab && s > 9;
-    int64_t per_unit = 4;
+    int64_t per_unit = kSmallTilesPerUnit;
     if (both_by_rows && steps == 1 && (s <= 9 || s >= 14 || half_step)) per_unit -= 1;
     if (half_step && s >= 14) per_unit -= 1;
     return small_tiles(m, n) * steps <= per_unit * kComputeUnits;

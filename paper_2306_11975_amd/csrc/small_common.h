@@ -8,7 +8,7 @@ namespace ozimmu {
 namespace {
 
 constexpr int kSmallThreads = 512;
-constexpr int kSmallTile = 32;       // rows and columns of C per workgroup
+constexpr int kSmallTile = kSmallTileRows;   // rows and columns of C per workgroup
 constexpr int kSmallStep = 64;       // positions of k per MFMA
 constexpr int kSmallGroups = kSmallThreads / kSmallTile;   // threads that share a vector of an operand
 

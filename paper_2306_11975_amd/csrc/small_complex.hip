@@ -81,6 +81,7 @@ hipError_t launch_small_complex_for(const SmallArgs& g, hipStream_t st) {
 // two launches (complex 4096 x 64 x 64 at eight slices, 256 tiles, 12.4 us there, here 10.2; 8192 x 64 x 64 13.6, here 18.9).
 bool small_complex_applies(int64_t m, int64_t n, int64_t k, int s) {
     if (s < 1 || s > OZIMMU_MAX_SLICES || m < 1 || n < 1 || k < 1 || k > (s <= kBand ? 2 : 1) * kSmallStep) return false;
+    static_assert(kComputeUnits <= kSmallMaxTiles, "the room for the counters");
     return small_tiles(m, n) <= kComputeUnits;
 }
 

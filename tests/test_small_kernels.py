@@ -73,3 +73,17 @@ def test_narrow_gates_of_many_slices_are_left_to_the_gate_kernel(m, n, k, s, ahe
 def test_limits_of_the_small_product(m, n, k, s, by_rows, applies):
     f = rule("_ZN6ozimmu21small_product_appliesElllib", I64, I64, I64, ctypes.c_int, ctypes.c_bool)
     assert f(m, n, k, s, by_rows) == applies
+
+
+def test_counters_of_every_size_fit_their_buffer():
+    """8192 words behind the sums (the larger of what the small kernels and the splitter leave): two per plane and tile of rows or columns of 32."""
+    real = rule("_ZN6ozimmu21small_product_appliesElllib", I64, I64, I64, ctypes.c_int, ctypes.c_bool)
+    cplx = rule("_ZN6ozimmu21small_complex_appliesEllli", I64, I64, I64, ctypes.c_int)
+    largest = 0
+    for tiles_m in [*range(1, 70), *range(70, 2100, 13), 1023, 1024, 1025]:
+        for tiles_n in (1, 2, 3, 7, 16, 31, 32, 33, 256, 257, 1024, 1025):
+            for a, b in ((tiles_m, tiles_n), (tiles_n, tiles_m)):
+                for planes, takes in ((1, real(32 * a, 32 * b, 1, 3, False)), (2, cplx(32 * a, 32 * b, 1, 3))):
+                    if takes:
+                        largest = max(largest, 2 * planes * (a + b))
+    assert 2050 <= largest <= 8192
