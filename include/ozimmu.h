@@ -188,7 +188,7 @@ ozimmu_status_t ozimmu_dgemm_stage(int stage, int64_t m, int64_t n, int64_t k, c
  * for tests and for callers who want to know): the tile of C one workgroup owns, or shares with others that walk other
  * parts of k (64 x 128; 64 x 64 from fourteen slices on, up to nine slices when k <= 512, when fewer than 256 of the
  * larger tiles exist, or when an estimate has two of the smaller ones at a time on a compute unit ahead, and from eleven to thirteen
- * when they fill the rounds better), the number of workgroups of the slice products (a multiple of the number of tiles where
+ * when they fill the rounds better and more workgroups on each of the larger ones would not be ahead), the number of workgroups of the slice products (a multiple of the number of tiles where
  * they share tiles; a second launch then adds their sums up), the number of bands the anti-diagonals are walked in (a
  * wavefront holds the INT32 sums of at most eight diagonals at a time, fifteen where it has a SIMD to itself: 2 bands beyond eight
  * slices, but for 9 and 11 to 15 on 64 x 64 tiles with one workgroup to a compute unit), and

@@ -50,6 +50,53 @@ void set_tiles(Layout& L, int64_t m, int64_t n, int s, bool small, bool one_laun
     L.tiles_n = (int)((n + cols - 1) / cols);
 }
 
+// How many workgroups share a tile of C, each with a part of k. With fewer tiles than compute units most of the chip
+// idles while a tile's walk takes its time; integer sums add up exactly in any order, so the walk can be shared, at the
+// price of the parts' INT32 sums going through memory and of a kernel that adds and folds them. The line is drawn where
+// the estimate says so: a step of a walk takes what its MFMAs take (64 cycles per pair and wavefront of a SIMD at 2.4 GHz) and what
+// they cannot cover of its loads (with one wavefront per SIMD 66 cycles behind each, twice s of them), and no less than 0.45 us; the
+// second launch takes 4 us, the sums 4.5 TB/s; more workgroups than compute units take 1.7 times as long where two share one, else 2.1 times. The
+// constants are fitted to 500 products of 8 to 230 tiles, 12 to 120 steps and 2 to 16 slices, each timed with one to 32 parts: on
+// average the choice costs 0.6 % more than the best one. Measured (product and fold, one part against the parts chosen): 80 tiles of
+// 60 steps 41 -> 31 us at five slices, 48 of 30 at six 30 -> 25, 100 of 30 at eleven 133 -> 106; the call 1273 x 153 x 8000 at six 96 -> 50.
+// (Where one band holds more than eight diagonals its step takes what is charged for two all the same: with one wavefront to a SIMD it has less to cover
+// its loads with. Without the charge fewer parts are chosen: complex 261 x 197 x 704 at fourteen 58 -> 68 us, double-double 288 x 473 x 535 at twelve 36 -> 42.)
+struct Split {
+    int splits;
+    int slabs;      // of a part (even)
+    size_t bytes;   // of their sums
+    double us;      // the estimate of the product's time (a round of tiles at most)
+};
+Split choose_split(const Layout& L, int s, size_t available) {
+    const int64_t tiles = (int64_t)L.tiles_m * L.tiles_n, slabs = L.k_pad / kSlab, steps = (slabs + 1) / 2;
+    const size_t part = (size_t)tiles * s * L.tile_rows * L.tile_cols * sizeof(int32_t);
+    const bool wide_tiles = L.tile_cols == 128;
+    const int pairs = s <= kBand ? s * (s + 1) / 2 : s * (s + 1) / 2 + s - kBand;   // (a second band costs about its slices more)
+    const double step_us = std::max(0.45, pairs * (wide_tiles ? 128.0 : 64.0) / 2400.0 + s * (wide_tiles ? 0.0825 : 0.055));
+    const double alone_us = steps * step_us + 3.0;
+    Split best{1, (int)slabs, 0, alone_us};
+    if (tiles == 0 || tiles >= kComputeUnits || steps < 8) return best;
+    const double twice = !wide_tiles && s <= 9 ? 1.7 : 2.1;
+    double best_us = std::min(0.95 * alone_us, alone_us - 2.0);
+    for (int64_t n = 2; n <= 64 && n * 2 <= steps; ++n) {
+        const int64_t chunk = (steps + n - 1) / n, parts = (steps + chunk - 1) / chunk;
+        if (2 * chunk * kSlab * s > OZIMMU_INT32_BLOCK || part * parts > available || tiles * parts > 2 * kComputeUnits) continue;
+        const double us = chunk * step_us * (tiles * parts > kComputeUnits ? twice : 1.0) + 7.0 + 2.0 * part * parts / 4.5e6;
+        if (us < best_us) {
+            best_us = us;
+            best = Split{(int)parts, (int)(2 * chunk), part * (size_t)parts, us};
+        }
+    }
+    return best;
+}
+// Room for those sums behind a workspace of `total` bytes. They are used where the caller's workspace has it, but are not
+// asked for: smaller ones are accepted as well, and a product that fits the built-in scratch of ozimmu_dgemm_static fits
+// it with what is reported here.
+size_t split_available(size_t total) {
+    const size_t limit = OZIMMU_STATIC_SCRATCH_BYTES;
+    return total <= limit ? limit - total : SIZE_MAX;
+}
+
 Layout make_layout(int64_t m, int64_t n, int64_t k, int s, bool cplx) {
     Layout L{};
     L.m_pad = round_up(m, kRowAlign);
@@ -78,52 +125,16 @@ Layout make_layout(int64_t m, int64_t n, int64_t k, int s, bool cplx) {
     L.off_scan = off;   // the counters of splitters that count for the slice-count check: first operand, then second
     off = align_up(off + 2 * scan_slots_bytes(planes));
     L.total = off;
+    // Eleven slices to thirteen: small tiles were chosen by rounds, but where larger ones leave compute units idle several workgroups share each, and more of
+    // those may fit a round than two of the smaller ones (410 x 1174 x 3391 at thirteen slices, 70 tiles three ways or 133: 198 us per call, 220).
+    if (s > 10 && s <= 13 && L.tile_cols == 64 && k > 0 && (int64_t)L.tiles_m * L.tiles_n <= kComputeUnits) {
+        Layout large = L;
+        set_tiles(large, m, n, s, false, one_launch);
+        if (choose_split(large, s, split_available(L.total)).us < 0.95 * choose_split(L, s, split_available(L.total)).us) L = large;
+    }
     return L;
 }
 
-// How many workgroups share a tile of C, each with a part of k. With fewer tiles than compute units most of the chip
-// idles while a tile's walk takes its time; integer sums add up exactly in any order, so the walk can be shared, at the
-// price of the parts' INT32 sums going through memory and of a kernel that adds and folds them. The line is drawn where
-// the estimate says so: a step of a walk takes what its MFMAs take (64 cycles per pair and wavefront of a SIMD at 2.4 GHz) and what
-// they cannot cover of its loads (with one wavefront per SIMD 66 cycles behind each, twice s of them), and no less than 0.45 us; the
-// second launch takes 4 us, the sums 4.5 TB/s; more workgroups than compute units take 1.7 times as long where two share one, else 2.1 times. The
-// constants are fitted to 500 products of 8 to 230 tiles, 12 to 120 steps and 2 to 16 slices, each timed with one to 32 parts: on
-// average the choice costs 0.6 % more than the best one. Measured (product and fold, one part against the parts chosen): 80 tiles of
-// 60 steps 41 -> 31 us at five slices, 48 of 30 at six 30 -> 25, 100 of 30 at eleven 133 -> 106; the call 1273 x 153 x 8000 at six 96 -> 50.
-struct Split {
-    int splits;
-    int slabs;      // of a part (even)
-    size_t bytes;   // of their sums
-};
-Split choose_split(const Layout& L, int s, size_t available) {
-    const int64_t tiles = (int64_t)L.tiles_m * L.tiles_n, slabs = L.k_pad / kSlab, steps = (slabs + 1) / 2;
-    const size_t part = (size_t)tiles * s * L.tile_rows * L.tile_cols * sizeof(int32_t);
-    Split best{1, (int)slabs, 0};
-    if (tiles == 0 || tiles >= kComputeUnits || steps < 8) return best;
-    const int pairs = s <= kBand ? s * (s + 1) / 2 : s * (s + 1) / 2 + s - kBand;   // (a second band costs about its slices more)
-    const bool wide_tiles = L.tile_cols == 128;
-    const double step_us = std::max(0.45, pairs * (wide_tiles ? 128.0 : 64.0) / 2400.0 + s * (wide_tiles ? 0.0825 : 0.055));
-    const double twice = !wide_tiles && s <= 9 ? 1.7 : 2.1;
-    const double alone_us = steps * step_us + 3.0;
-    double best_us = std::min(0.95 * alone_us, alone_us - 2.0);
-    for (int64_t n = 2; n <= 64 && n * 2 <= steps; ++n) {
-        const int64_t chunk = (steps + n - 1) / n, parts = (steps + chunk - 1) / chunk;
-        if (2 * chunk * kSlab * s > OZIMMU_INT32_BLOCK || part * parts > available || tiles * parts > 2 * kComputeUnits) continue;
-        const double us = chunk * step_us * (tiles * parts > kComputeUnits ? twice : 1.0) + 7.0 + 2.0 * part * parts / 4.5e6;
-        if (us < best_us) {
-            best_us = us;
-            best = Split{(int)parts, (int)(2 * chunk), part * (size_t)parts};
-        }
-    }
-    return best;
-}
-// Room for those sums behind a workspace of `total` bytes. They are used where the caller's workspace has it, but are not
-// asked for: smaller ones are accepted as well, and a product that fits the built-in scratch of ozimmu_dgemm_static fits
-// it with what is reported here.
-size_t split_available(size_t total) {
-    const size_t limit = OZIMMU_STATIC_SCRATCH_BYTES;
-    return total <= limit ? limit - total : SIZE_MAX;
-}
 size_t split_room(const Layout& L, int s, size_t total) { return choose_split(L, s, split_available(total)).bytes; }
 
 ozimmu_status_t hip_status(hipError_t e) { return e == hipSuccess ? OZIMMU_OK : OZIMMU_ERR_HIP; }

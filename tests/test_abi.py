@@ -119,6 +119,17 @@ def test_argument_errors_are_reported_before_any_launch():
     assert L.ozimmu_dgemm_stage(3, 4, 4, 4, fake, 4, fake, 4, fake, 4, 3, fake, 1 << 30, None) == 1
 
 
+@pytest.mark.parametrize("m,n,k,s,cols,parts", [(410, 1174, 3391, 13, 128, 3), (298, 1891, 4479, 11, 128, 3), (410, 1174, 512, 13, 64, 1), (410, 1174, 3391, 14, 64, 3),
+                                               (1024, 1024, 3391, 13, 64, 1), (300, 300, 5000, 12, 64, 4)])
+def test_larger_tiles_that_more_workgroups_share_are_kept(m, n, k, s, cols, parts):
+    """Eleven to thirteen slices: 64 x 64 tiles of which a round has room for one workgroup each, or fewer of 64 x 128 with several on each."""
+    plan = ozimmu.launch_plan(m, n, k, s)
+    tiles = -(-m // 64) * -(-n // cols)
+    assert plan["tile_cols"] == cols and plan["workgroups"] == parts * tiles
+    # room for the sums of the parts is reported
+    assert ozimmu.workspace_bytes(m, n, k, s) >= (parts > 1) * plan["workgroups"] * s * 4 * 64 * cols
+
+
 def test_launch_plan_host_logic():
     # the headline shape: 64 x 128 tiles, 8192 workgroups = 32 full rounds of the 256 CUs, one band, no k-blocking
     assert ozimmu.launch_plan(8192, 8192, 8192, 8) == {"tile_rows": 64, "tile_cols": 128, "workgroups": 8192,

@@ -35,6 +35,29 @@ def test_real_products_across_the_estimate(m, n, k, s, cols):
     assert np.array_equal(bits(C[rows].cpu().numpy()), bits(want))
 
 
+# few of the larger tiles with three workgroups on each, ahead of the smaller ones with one; double-double and complex products on the same
+@pytest.mark.parametrize("m,n,k,s", [(410, 1174, 3391, 13), (298, 1891, 4479, 11)])
+def test_shared_larger_tiles(m, n, k, s):
+    plan = ozimmu.launch_plan(m, n, k, s)
+    assert plan["tile_cols"] == 128 and plan["workgroups"] > -(-m // 64) * -(-n // 128)
+    A, B = wl.phi_matrix_device(m, k, 1.0, 11), wl.phi_matrix_device(k, n, 1.0, 12)
+    hi, lo = (torch.full((m, n), float("nan"), dtype=torch.float64, device="cuda") for _ in range(2))
+    ws = ozimmu.alloc_workspace(m, n, k, s)
+    rows = sampled(m)[::2]
+    a, b = A[rows].cpu().numpy(), B.cpu().numpy()
+    ozimmu.dgemm(A, B, hi, s, ws)
+    assert not torch.isnan(hi).any() and np.array_equal(bits(hi[rows].cpu().numpy()), bits(oracle.dgemm(a, b, s)))
+    ozimmu.dgemm_dd(A, B, hi, lo, s, ws)
+    want_hi, want_lo = oracle.dgemm_dd(a, b, s)
+    assert np.array_equal(bits(hi[rows].cpu().numpy()), bits(want_hi)) and np.array_equal(bits(lo[rows].cpu().numpy()), bits(want_lo))
+    # (a complex element is two real rows and columns)
+    Z, W = wl.gaussian_complex_device(m // 2, k, 13), wl.gaussian_complex_device(k, n // 2, 14)
+    C = torch.full((m // 2, n // 2), float("nan"), dtype=torch.complex128, device="cuda")
+    ozimmu.zgemm(Z, W, C, s, ozimmu.alloc_workspace(m // 2, n // 2, k, s, True))
+    rows = sampled(m // 2)[::2]
+    assert not torch.isnan(C.real).any() and np.array_equal(bits(C[rows].cpu().numpy()), bits(oracle.zgemm(Z[rows].cpu().numpy(), W.cpu().numpy(), s)))
+
+
 # complex: 64 x 64 tiles hold 32 x 32 complex elements; more than 256 of the larger tiles each, so that k and the slice count decide
 @pytest.mark.parametrize("m,n,k,s", [(520, 1030, 33, 1), (520, 1030, 100, 7), (511, 1057, 512, 9), (530, 1000, 700, 8), (515, 1030, 1600, 5), (520, 1030, 64, 10)])
 def test_complex_products_on_small_and_large_tiles(m, n, k, s):
