@@ -125,7 +125,7 @@ def test_tile_counts_that_do_not_fill_the_chip_sampled_rows_bit_exact(size, s):
 
 @pytest.mark.parametrize("s", range(1, 10))
 def test_large_tile_kernels_up_to_nine_slices_sampled_rows_bit_exact(s):
-    """Small shapes take 64 x 64 tiles up to nine slices; this one has 256 tiles of 64 x 128 and k > 512, so it
+    """Small shapes take 64 x 64 tiles up to nine slices (or one kernel on 32 x 32 tiles); this one has 256 tiles of 64 x 128 and k > 512, so it
     runs the 64 x 128 kernels that the small parity cases no longer reach."""
     m, n, k = 1024, 2048, 544
     assert ozimmu.launch_plan(m, n, k, s)["tile_cols"] == 128
@@ -145,15 +145,15 @@ def test_small_tiles_are_chosen_for_short_k_and_for_grids_that_underfill_the_chi
     assert ozimmu.launch_plan(4096, 4096, 256, 7)["tile_cols"] == 64      # short inner dimension
     assert ozimmu.launch_plan(1024, 1024, 1024, 8)["tile_cols"] == 64     # 128 tiles of 64 x 128 for 256 compute units
     assert ozimmu.launch_plan(4096, 4096, 4096, 8)["tile_cols"] == 128
-    assert ozimmu.launch_plan(1024, 1024, 1024, 10)["tile_cols"] == 128   # no small kernels beyond nine slices
+    assert ozimmu.launch_plan(1024, 1024, 1024, 10)["tile_cols"] == 128   # ten slices keep the large tiles
     assert ozimmu.launch_plan(64, 64, 200000, 2)["tile_cols"] == 128      # k-blocking keeps the large tiles
 
 
 @pytest.mark.parametrize("m,n,k,s,cols", [(1024, 2048, 512, 8, 64), (960, 2048, 600, 5, 64), (1024, 2048, 600, 9, 128),
                                           (1000, 1000, 1000, 9, 64), (1000, 1000, 1000, 10, 128)])
 def test_both_sides_of_the_tile_choice_sampled_rows_bit_exact(m, n, k, s, cols):
-    """Shapes just on either side of the rule that picks 64 x 64 tiles (k <= 512, or fewer than 256 tiles of
-    64 x 128, up to nine slices), with ragged edges."""
+    """Shapes just on either side of where up to nine slices always take 64 x 64 tiles (k <= 512, or fewer than 256 tiles of
+    64 x 128; beyond, an estimate decides, test_gpu_tile_choice.py), and ten, which never do; with ragged edges."""
     assert ozimmu.launch_plan(m, n, k, s)["tile_cols"] == cols
     A = wl.phi_matrix_device(m, k, 1.0, 1008)
     B = wl.phi_matrix_device(k, n, 1.0, 2008)

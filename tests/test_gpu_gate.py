@@ -1,6 +1,7 @@
 """GPU parity of the one-kernel complex product for a small gate on a tall state (Section 4.4: a d-qubit gate on an
 N-qubit state vector is the complex product 2^(N-d) x 2^d x 2^d). ozimmu_zgemm takes that path when k and n are
-at most 128 (256 with up to eight slices); the state is then split inside the product kernel (tiles of 32 rows; one
+at most 128 (256 with up to eight slices) and there are more than 256 tiles of 32 x 32 or k is beyond 64 (128 up to eight slices); smaller products are
+one kernel's (test_gpu_small_product.py), and the shapes of few rows here run that one. The gate kernel splits the state inside the product kernel (tiles of 32 rows; one
 step of 64 positions and eight fragments of the gate while k and n are at most 64, two steps and sixteen fragments up to
 128, four steps, 32 fragments and sixteen wavefronts up to 256; four wavefronts per SIMD up to eight slices, two beyond). Compared bit for bit with the oracle, which splits first and multiplies afterwards."""
 import numpy as np
@@ -185,10 +186,12 @@ def test_gate_on_a_long_state_sampled_rows():
     assert_same(C[idx].cpu().numpy(), want)
 
 
-def test_gate_call_captured_in_a_graph_replays_correctly():
-    """The gate path only enqueues two kernels on the caller's stream, so a call can be captured and replayed: each
+@pytest.mark.parametrize("m", [3000, 8300])   # the kernel for small products, and the gate kernel
+def test_gate_call_captured_in_a_graph_replays_correctly(m):
+    """Either path only enqueues kernels on the caller's stream (one, two), so a call can be captured and replayed: each
     replay runs on new data written into the captured buffers, with eager work and synchronisations in between."""
-    m, k, s = 3000, 64, 8
+    k, s = 64, 8
+    rows = np.r_[0:100, m // 2:m // 2 + 50, m - 100:m]
     A = torch.empty((m, k), dtype=torch.complex128, device=DEV)
     U = torch.empty((k, k), dtype=torch.complex128, device=DEV)
     C = torch.empty((m, k), dtype=torch.complex128, device=DEV)
@@ -210,7 +213,9 @@ def test_gate_call_captured_in_a_graph_replays_correctly():
         torch.cuda.synchronize()
         graph.replay()
         torch.cuda.synchronize()
-        assert_same(C.cpu().numpy(), oracle.zgemm(Ah, Uh, s))
+        got = C.cpu().numpy()
+        assert not np.isnan(got).any()
+        assert_same(got[rows], oracle.zgemm(Ah[rows], Uh, s))
 
 
 def test_gate_seeded_random_shapes_and_values():
@@ -288,3 +293,64 @@ def test_gate_largest_integer_sums(k, s, signs):
     A = plane(m, k) + 1j * plane(m, k)
     B = plane(k, n) + 1j * plane(k, n)
     assert_same(gpu_zgemm(A, B, s), oracle.zgemm(A, B, s))
+
+
+# ------------------------------------------------------------------ states of more tiles than the kernel for small products takes
+def sampled_rows(m):
+    """The first tiles, rows over the whole state, and the ragged end."""
+    return np.unique(np.r_[0:70, np.arange(70, m, 397), m - 40:m])
+
+
+# the smallest class (four and eight wavefronts to a tile, one and several fragments, both row fragments of a tile to a wavefront or one), two steps, four
+LONG = [(8225, 64, 64, 8), (8225, 40, 50, 7), (8225, 9, 33, 11), (8225, 7, 13, 5), (4200, 64, 64, 8), (4200, 33, 40, 12), (8192, 16, 16, 13), (300, 5, 16, 16),
+        (4200, 113, 127, 6), (4200, 81, 100, 10), (4200, 65, 64, 7), (8225, 128, 1, 2), (600, 200, 129, 5)]
+
+
+@pytest.mark.parametrize("m,n,k,s", LONG)
+def test_long_states_with_leading_dimensions(m, n, k, s):
+    A, B = wl.gaussian_complex(m, k, seed=m + k), wl.unit_column_complex(k, n, seed=n + k + 1)
+    rows = sampled_rows(m)
+    got = gpu_zgemm(A, B, s, lda_extra=5, ldb_extra=3, ldc_extra=9)
+    assert not np.isnan(got).any()
+    assert_same(got[rows], oracle.zgemm(A[rows], B, s))
+
+
+def adversarial_state(m, k, seed):
+    """The adversarial rows at the start, in a tile of the middle and in the last, ragged one."""
+    A = wl.gaussian_complex(m, k, seed=seed)
+    few = wl.adversarial_matrix(12, k, seed=seed + 1) + 1j * wl.adversarial_matrix(12, k, seed=seed + 2)
+    for at in (0, m // 2 // 32 * 32 + 10, m - 12):
+        A[at:at + 12] = few
+    return A, np.unique(np.r_[0:40, m // 2 // 32 * 32:m // 2 // 32 * 32 + 32, m - 40:m])
+
+
+@pytest.mark.parametrize("m,n,k,s", LONG)
+def test_long_states_adversarial_values(m, n, k, s):
+    A, rows = adversarial_state(m, k, 5)
+    B = wl.adversarial_matrix(k, n, seed=7) + 1j * wl.adversarial_matrix(k, n, seed=8)
+    # (rows and columns near the top of the range: infinities, and their differences, are among the results)
+    assert_same(gpu_zgemm(A, B, s)[rows], oracle.zgemm(A[rows], B, s))
+
+
+@pytest.mark.parametrize("m,n,k", [(8225, 64, 64), (8225, 7, 16), (4200, 64, 40), (4200, 128, 65)])
+def test_long_states_purely_real_and_purely_imaginary_operands(m, n, k):
+    A, B, rows = wl.gaussian_complex(m, k, seed=9), wl.unit_column_complex(k, n, seed=10), sampled_rows(m)
+    for Ax, Bx in ((A.real + 0j, B.real + 0j), (1j * A.imag, 1j * B.imag), (A.real + 0j, 1j * B.imag), (1j * A.imag, B.real + 0j)):
+        Ax, Bx = np.ascontiguousarray(Ax), np.ascontiguousarray(Bx)
+        assert_same(gpu_zgemm(Ax, Bx, 6)[rows], oracle.zgemm(Ax[rows], Bx, 6))
+
+
+@pytest.mark.parametrize("m,n,k", [(8225, 40, 64), (8225, 7, 16), (4200, 64, 33), (4200, 100, 65)])
+@pytest.mark.parametrize("threshold", [0.0, 2.0, 30.0])
+def test_long_states_counted_with_adversarial_rows(m, n, k, threshold):
+    """Zero and subnormal rows, rows near the ends of the range in the counters of the gate kernel."""
+    A, rows = adversarial_state(m, k, 51)
+    B = wl.unit_column_complex(k, n, seed=53)
+    s_want, _ = oracle.auto_num_slices(A, B, threshold)
+    want = oracle.zgemm(A[rows], B, s_want)
+    dA, dB = torch.from_numpy(A).to(DEV), torch.from_numpy(B).to(DEV)
+    for guess in sorted({s_want, max(1, s_want - 1), min(16, s_want + 1), 7}):
+        C = torch.full((m, n), complex(float("nan"), float("nan")), dtype=torch.complex128, device=DEV)
+        s_got, confirmed = ozimmu.zgemm_auto(dA, dB, C, threshold, guess=guess)
+        assert s_got == s_want and confirmed == (guess == s_want), (guess, s_got, s_want)
+        assert_same(C.cpu().numpy()[rows], want)

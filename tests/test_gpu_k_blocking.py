@@ -42,9 +42,10 @@ def assert_blocked(k, s):
     assert s * ozimmu.slice_geometry(1, k)[1] > ozimmu.INT32_BLOCK
 
 
-# one band and two, both tile shapes, even and odd numbers of slabs of 32 positions
+# one band (up to eight slices, fourteen and fifteen) and two, both tile shapes, even and odd numbers of slabs of 32 positions
 @pytest.mark.parametrize("m,n,k,s", [(40, 50, 70000, 2), (40, 50, 69970, 2), (129, 65, 20000, 8), (65, 130, 14000, 10), (70, 140, 13001, 13),
-                                     (70, 66, 9000, 16), (70, 66, 9025, 15)])
+                                     (70, 66, 9000, 16), (70, 66, 9025, 15),
+                                     (66, 70, 9450, 14), (66, 70, 9500, 14)])
 def test_dgemm(m, n, k, s):
     assert_blocked(k, s)
     A, B = wl.phi_pair(m, n, k, 2.0, seed=k)
@@ -71,7 +72,8 @@ def test_saturating_slices_across_the_block(s):
     assert np.array_equal(bits(C.cpu().numpy()), bits(oracle.dgemm(A, B, s)))
 
 
-@pytest.mark.parametrize("m,n,k,s", [(40, 50, 70000, 3), (50, 70, 69970, 3), (64, 120, 14000, 12), (66, 70, 9000, 16)])
+@pytest.mark.parametrize("m,n,k,s", [(40, 50, 70000, 3), (50, 70, 69970, 3), (64, 120, 14000, 12), (66, 70, 9000, 16),
+                                     (64, 70, 9450, 14), (66, 70, 9500, 14), (66, 70, 8830, 15), (50, 60, 8800, 15)])
 def test_double_double(m, n, k, s):
     assert_blocked(k, s)
     A, B = wl.phi_pair(m, n, k, 1.0, seed=9)

@@ -123,12 +123,13 @@ def test_split_of_random_bit_patterns(s):
     check_split(Eg, Sg, Eo, So, 70, 333)
 
 
-def test_dgemm_of_random_bit_patterns_bit_exact():
+@pytest.mark.parametrize("k", [200, 300])   # the kernel for small products, and the general path
+def test_dgemm_of_random_bit_patterns_bit_exact(k):
     """Exponent fields spread over 600 binades (the result stays finite), and over all binades (the scale
     2^(EA+EB) overflows for part of the outputs: both sides must then give the same infinities, never NaN)."""
     for lo, hi, seed in ((723, 1323, 7), (0, 2046, 8)):
-        A = random_bit_patterns((130, 200), seed, lo, hi)
-        B = random_bit_patterns((200, 90), seed + 100, lo, hi)
+        A = random_bit_patterns((130, k), seed, lo, hi)
+        B = random_bit_patterns((k, 90), seed + 100, lo, hi)
         got, want = gpu_dgemm(A, B, 8), oracle.dgemm(A, B, 8)
         assert not np.isnan(want).any() and np.array_equal(bits(got), bits(want))
     assert np.isinf(want).any()
@@ -300,12 +301,14 @@ def test_dgemm_integer_matrices_equal_plain_matmul():
     assert np.array_equal(C, (A.astype(np.int64) @ B.astype(np.int64)).astype(np.float64))
 
 
-def test_dgemm_subnormal_and_overflowing_scale():
-    A = np.array([[1.2345678901234567e-160, -3.3e-161, 2e-162]])
-    B = np.array([[7.7e-160], [1.1e-159], [5e-158]])
+@pytest.mark.parametrize("zeros", [0, 300])   # behind k: the kernel for small products, and the general path
+def test_dgemm_subnormal_and_overflowing_scale(zeros):
+    def longer(A, B):
+        return np.pad(A, ((0, 0), (0, zeros))), np.pad(B, ((0, zeros), (0, 0)))
+
+    A, B = longer(np.array([[1.2345678901234567e-160, -3.3e-161, 2e-162]]), np.array([[7.7e-160], [1.1e-159], [5e-158]]))
     assert np.array_equal(bits(gpu_dgemm(A, B, 10)), bits(oracle.dgemm(A, B, 10)))
-    A = np.array([[1.5e200, 1.0e200]])
-    B = np.array([[1.5e200], [1.0e200]])
+    A, B = longer(np.array([[1.5e200, 1.0e200]]), np.array([[1.5e200], [1.0e200]]))
     got, want = gpu_dgemm(A, B, 6), oracle.dgemm(A, B, 6)
     assert np.isinf(want[0, 0]) and np.array_equal(bits(got), bits(want))
 

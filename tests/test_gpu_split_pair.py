@@ -1,5 +1,6 @@
 """The launch that splits both operands of a product (short vectors): every way the operands can be stored, at the edges of the
-register tiling and beyond them, against the oracle bit for bit; the counts it takes on the way for the slice-count check."""
+register tiling and beyond them, against the oracle bit for bit; the counts it takes on the way for the slice-count check. (Products of few tiles
+with short vectors are one kernel's, test_gpu_small_product.py: with the smallest shapes here that one runs.)"""
 import numpy as np
 import pytest
 import torch
@@ -39,6 +40,43 @@ def test_real_operands_bit_exact(ta, tb, m, n, k, s):
                           dB, dB.stride(0) if dB.shape[0] > 1 else max(dB.shape[1], 1), 0.0, C, m, s, ozimmu.alloc_workspace(n, m, k, s))
         torch.cuda.synchronize()
         assert np.array_equal(bits(C.cpu().numpy().T), bits(oracle.dgemm(A, B, s))), (pad, odd)
+
+
+# the shortest vectors, with more tiles than the kernel for small products takes
+@pytest.mark.parametrize("ta", [False, True])
+@pytest.mark.parametrize("tb", [False, True])
+@pytest.mark.parametrize("m,n,k,s", [(1030, 1060, 1, 3), (1060, 1030, 33, 7), (1030, 1060, 64, 9), (1030, 1060, 65, 10), (9, 33000, 40, 6), (520, 1040, 130, 5)])
+def test_short_vectors_of_many_tiles(ta, tb, m, n, k, s):
+    A, B = wl.phi_pair(m, n, k, 1.0, seed=k)
+    A[0, :] = 0.0
+    A[m - 1, k - 1] = 3.0e-310
+    rows = np.r_[0:9] if m < 20 else np.r_[0:9, m // 2 - 2:m // 2 + 3, m - 9:m]
+    want = oracle.dgemm(A[rows], B, s)
+    for pad, odd in ((0, 0), (3, 1)):
+        dA, dB = stored(A if ta else A.T, pad, odd), stored(B if tb else B.T, pad, odd)
+        C = torch.full((n, m), float("nan"), dtype=torch.float64, device="cuda")
+        ozimmu.dgemm_blas("T" if ta else "N", "T" if tb else "N", m, n, k, 1.0, dA, dA.stride(0) if dA.shape[0] > 1 else dA.shape[1],
+                          dB, dB.stride(0) if dB.shape[0] > 1 else dB.shape[1], 0.0, C, m, s, ozimmu.alloc_workspace(n, m, k, s))
+        torch.cuda.synchronize()
+        got = C.cpu().numpy().T
+        assert np.array_equal(bits(got[rows]), bits(want)) and not np.isnan(got).any(), (pad, odd)
+
+
+@pytest.mark.parametrize("m,n,k", [(1030, 1060, 33), (520, 700, 200), (1060, 1030, 1)])
+def test_guess_is_checked_from_the_counts_of_many_tiles(m, n, k):
+    A, B = wl.phi_pair(m, n, k, 1.0, seed=4)
+    A[3] = 0.0
+    dA, dB = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+    rows = np.r_[0:9, m - 9:m]
+    for T in (0.0, 1.0):
+        right, _ = oracle.auto_num_slices(A, B, T)
+        want = oracle.dgemm(A[rows], B, right)
+        for guess in (right - 1, right, min(16, right + 1), 16):
+            C = torch.empty((m, n), dtype=torch.float64, device="cuda")
+            got, confirmed = ozimmu.dgemm_auto(dA, dB, C, T, guess=guess)
+            torch.cuda.synchronize()
+            assert got == right and confirmed == (guess == right)
+            assert np.array_equal(bits(C.cpu().numpy()[rows]), bits(want))
 
 
 @pytest.mark.parametrize("ta", ["N", "C"])
