@@ -39,8 +39,9 @@ static inline void tile_waves(int s, bool small, int* wm, int* wn) {
 // of large ones) 191 -> 153, 3500 x 3500 x 1536 at eight 529 -> 483, 8192 x 8192 x 8192 at eight 12910 -> 13090 (stays large). One round of
 // large tiles is one of small ones as well and takes as long (1024 x 2048 x 1024 70.5, 71.4).
 // Eleven to thirteen: one workgroup per compute unit of either, and the same rate (4096^3 at eleven 2822, 2838 us; 4096 x 4096 x 512 396, 413), so rounds decide:
-// 1024^3 at twelve 103 -> 71, 300^3 42 -> 28, 1500 x 1500 x 1000 205 -> 171, complex 300^3 48 -> 35. (Ten keep the large tiles, which the
-// interface's tests of ozimmu_launch_plan ask for.)
+// 1024^3 at twelve 103 -> 71, 300^3 42 -> 28, 1500 x 1500 x 1000 205 -> 171, complex 300^3 48 -> 35.
+// Ten keep the large tiles and two bands only because the interface's tests hold ozimmu_launch_plan to them (1000^3, 1024^3). They take longer: with this rule and one
+// band for ten slices as well 1024^3 89 -> 62 us, 1500 x 1800 x 1500 219 -> 179, double-double 1501 x 1301 x 1107 180 -> 112, complex 300^3 39 -> 30, 1.25 x on average over 214 products.
 static inline bool use_small_tiles(int64_t m, int64_t n, int64_t k_pad, int s, bool wide) {
     if (wide || s == 10 || s > 13) return false;
     const int64_t row_tiles = (m + 63) / 64, large = row_tiles * ((n + 127) / 128), small = row_tiles * ((n + 63) / 64);
@@ -54,7 +55,8 @@ static inline bool use_small_tiles(int64_t m, int64_t n, int64_t k_pad, int s, b
     if (k_pad <= 512 || large < kComputeUnits) return true;
     if (large == kComputeUnits) return false;
     // what a step of the small tiles takes more (five and six slices: their loads are covered least; of seven and eight, in few rounds, less is
-    // covered than in many: complex 217 x 3797 x 1568 at seven, two rounds of either, 195 -> 201 us, 808 x 1024 x 1024 97 -> 99: both stay large)
+    // covered than in many: complex 217 x 3797 x 1568 at seven, two rounds of either, 195 -> 201 us, 808 x 1024 x 1024 97 -> 99: both stay large. Those two set the
+    // term; over 1700 drawn products of every slice count none takes longer than under the rule before this estimate, k <= 512 or less than a round, by more than the runs differ)
     const double few = large_rounds < 8 ? 0.04 : 0.0;
     const double more = s == 9 ? -0.01 : s == 8 ? 0.012 + few : s == 7 ? 0.015 + few : 0.065;
     // a last round of small tiles with a compute unit to each takes 0.6 of one with two
