@@ -105,7 +105,7 @@ Layout make_layout(int64_t m, int64_t n, int64_t k, int s, bool cplx) {
     L.wide = needs_wide(s, L.k_pad);
     // a complex product without k-blocking runs in one launch
     const bool one_launch = cplx && !L.wide;
-    set_tiles(L, m, n, s, one_launch ? use_small_tiles(2 * m, 2 * n, L.k_pad, s, L.wide) : use_small_tiles(m, n, L.k_pad, s, L.wide), one_launch);
+    set_tiles(L, m, n, s, one_launch ? use_small_tiles(2 * m, 2 * n, L.k_pad, s, L.wide, true) : use_small_tiles(m, n, L.k_pad, s, L.wide, false), one_launch);
     L.sa_bytes = (size_t)s * L.m_pad * L.k_pad;
     L.sb_bytes = (size_t)s * L.n_pad * L.k_pad;
     const int planes = cplx ? 2 : 1;

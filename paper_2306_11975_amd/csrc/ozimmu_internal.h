@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "ozimmu.h"
 
 namespace ozimmu {
@@ -38,11 +40,17 @@ static inline void tile_waves(int s, bool small, int* wm, int* wn) {
 // 456 -> 392 us, x 1024 at eight 1735 -> 1690, x 2048 at six 2080 -> 2140 (stays large); real 1500 x 1800 x 1500 at nine (two rounds
 // of large ones) 191 -> 153, 3500 x 3500 x 1536 at eight 529 -> 483, 8192 x 8192 x 8192 at eight 12910 -> 13090 (stays large). One round of
 // large tiles is one of small ones as well and takes as long (1024 x 2048 x 1024 70.5, 71.4).
+// With two to six slices the loads are what a long walk waits for, and two workgroups, each at a step of its own, find fewer of them in the L2 than one twice as large:
+// as k goes from 2048 to 10240 a step of the small tiles comes to take up to 7 % more at five and six slices, of real products 12 % at three and four and 30 % at two (complex
+// ones of so few slices, and one slice, lose nothing). Five have the least to cover a load with where a workgroup has a compute unit to itself. Per call, small -> large:
+// 1033 x 12215 x 16484 at four 2830 -> 2550 us, 4990 x 1835 x 16428 at two 910 -> 845, 1169 x 9165 x 11163 at four 1524 -> 1430, complex 228 x 2401 x 5028 at five 403 -> 373; still
+// large -> small: complex 1836 x 544 x 17249 at four 1577 -> 1204, 1338 x 1549 x 12050 at six 735 -> 683. Fitted to 1190 products of one to nine slices that the estimate without these
+// terms has on small tiles, of which 123 took more than 1.5 % longer there, up to 10 %; of 350 others, with the terms, five do, up to 2.9 % (all seen: 455 x 6066 x 10890 at six, 4.8 %).
 // Eleven to thirteen: one workgroup per compute unit of either, and the same rate (4096^3 at eleven 2822, 2838 us; 4096 x 4096 x 512 396, 413), so rounds decide:
 // 1024^3 at twelve 103 -> 71, 300^3 42 -> 28, 1500 x 1500 x 1000 205 -> 171, complex 300^3 48 -> 35.
 // Ten keep the large tiles and two bands only because the interface's tests hold ozimmu_launch_plan to them (1000^3, 1024^3). They take longer: with this rule and one
 // band for ten slices as well 1024^3 89 -> 62 us, 1500 x 1800 x 1500 219 -> 179, double-double 1501 x 1301 x 1107 180 -> 112, complex 300^3 39 -> 30, 1.25 x on average over 214 products.
-static inline bool use_small_tiles(int64_t m, int64_t n, int64_t k_pad, int s, bool wide) {
+static inline bool use_small_tiles(int64_t m, int64_t n, int64_t k_pad, int s, bool wide, bool cplx) {
     if (wide || s == 10 || s > 13) return false;
     const int64_t row_tiles = (m + 63) / 64, large = row_tiles * ((n + 127) / 128), small = row_tiles * ((n + 63) / 64);
     const int64_t large_rounds = (large + kComputeUnits - 1) / kComputeUnits;
@@ -55,13 +63,14 @@ static inline bool use_small_tiles(int64_t m, int64_t n, int64_t k_pad, int s, b
     if (k_pad <= 512 || large < kComputeUnits) return true;
     if (large == kComputeUnits) return false;
     // what a step of the small tiles takes more (five and six slices: their loads are covered least; of seven and eight, in few rounds, less is
-    // covered than in many: complex 217 x 3797 x 1568 at seven, two rounds of either, 195 -> 201 us, 808 x 1024 x 1024 97 -> 99: both stay large. Those two set the
-    // term; over 1700 drawn products of every slice count none takes longer than under the rule before this estimate, k <= 512 or less than a round, by more than the runs differ)
+    // covered than in many: complex 217 x 3797 x 1568 at seven, two rounds of either, 195 -> 201 us, 808 x 1024 x 1024 97 -> 99: both stay large)
     const double few = large_rounds < 8 ? 0.04 : 0.0;
-    const double more = s == 9 ? -0.01 : s == 8 ? 0.012 + few : s == 7 ? 0.015 + few : 0.065;
+    const double long_walk = std::min(std::max((double)(k_pad - 2048) / 8192.0, 0.0), 1.0);
+    const double more = s == 9 ? -0.01 : s == 8 ? 0.012 + few : s == 7 ? 0.015 + few
+                      : 0.065 + long_walk * (s >= 5 ? 0.07 : cplx || s == 1 ? 0.0 : s == 2 ? 0.3 : 0.12);
     // a last round of small tiles with a compute unit to each takes 0.6 of one with two
     const int64_t pairs = 2 * kComputeUnits, rest = small % pairs;
-    const double small_rounds = (double)(small / pairs) + (rest == 0 ? 0.0 : rest <= kComputeUnits ? 0.6 : 1.0);
+    const double small_rounds = (double)(small / pairs) + (rest == 0 ? 0.0 : rest > kComputeUnits ? 1.0 : s == 5 ? 0.9 : 0.6);
     return small_rounds * (walk_us * (1.0 + more) + ends_us) < (double)large_rounds * (walk_us + ends_alone_us);
 }
 

@@ -161,6 +161,13 @@ def test_launch_plan_host_logic():
     assert L.ozimmu_launch_plan(1, 1, 1, 3, None) == 4
 
 
+@pytest.mark.parametrize("m,n,k,s,cols", [(1033, 12215, 16484, 4, 128), (4990, 1835, 16428, 2, 128), (899, 3001, 7814, 5, 128), (1169, 9165, 11163, 4, 128),
+                                          (1033, 12215, 2048, 4, 64), (899, 3001, 2048, 5, 64), (1338, 1549, 12050, 6, 64), (1500, 1800, 8000, 9, 64), (1500, 1800, 8000, 1, 64)])
+def test_long_walks_of_few_slices_keep_the_larger_tiles(m, n, k, s, cols):
+    """More than a round of 64 x 128 tiles: with two to five slices and a long inner dimension 64 x 64 ones take up to 10 % longer, with a short one, or more slices, less."""
+    assert ozimmu.launch_plan(m, n, k, s)["tile_cols"] == cols
+
+
 def test_blas_call_argument_errors():
     L = ozimmu.lib()
     fake = ctypes.c_void_p(256)
