@@ -181,7 +181,8 @@ struct Stored {
 };
 // Slices and exponents of both operands: `a` into the layout's A, `b` into its B. sums_a, sums_b (both or neither;
 // [planes][16], device or mapped host memory): the splitters also count for the check of s as the automatic slice count
-// (Section 4.4), and the bits the planes lose with s and with s - 1 slices arrive there.
+// (Section 4.4), and the bits the planes lose with s and with s - 1 slices arrive there. to_host (optional): as for launch_split_pair. Where its
+// `blocks` is set on return, nothing arrives in sums_a and sums_b before add_pair_counts.
 hipError_t split_operands(const Layout& L, bool cplx, const Stored& a, const Stored& b, int64_t k, int s, unsigned char* ws,
                           hipStream_t st, unsigned long long* sums_a = nullptr, unsigned long long* sums_b = nullptr, PairCounts* to_host = nullptr) {
     const int planes = cplx ? 2 : 1;
@@ -499,8 +500,8 @@ ozimmu_status_t gemm_auto(bool cplx, int64_t m, int64_t n, int64_t k, const doub
             return OZIMMU_OK;
         }
     } else if (host) {
-        // Any other shape: the splitters of the general path count while they split, two small kernels leave the
-        // sums for `guess` and `guess - 1` in the mapped buffer, and the product follows at once; one wait at the end.
+        // Any other shape: the splitters of the general path count while they split, and the product follows at once; one wait at the end. The
+        // sums for `guess` and `guess - 1` are left in the mapped buffer by a small kernel, or by the host from the counters of one launch for both operands.
         L = make_layout(m, n, k, guess, cplx);
         unsigned char* ws = static_cast<unsigned char*>(workspace);
         unsigned long long* const host_b = host + (cplx ? 2 : 1) * OZIMMU_MAX_SLICES;

@@ -193,7 +193,7 @@ struct SplitOperand {
 bool split_pair_applies(const SplitOperand& a, const SplitOperand& b, int planes, int64_t k_pad, int s, bool counting);
 // to_host (optional; its words: kPairCountWords of mapped host memory): where they fit, the counters of its workgroups go there instead and no launch adds
 // them up (its blocks is then set); add_pair_counts does, once the stream has been waited for. (Automatic mode, per call: 376 x 2594 x 67 at threshold
-// 1 45.9 -> 39.9 us, 508 x 2683 x 390 65.4 -> 60.4, 2048^3 at twelve slices 486 -> 480. More words than that: the launch that adds them up takes less than the host.)
+// 1 45.9 -> 39.9 us, 508 x 2683 x 390 65.4 -> 60.4; of longer calls, 2048^3 at twelve slices, it is lost in the runs' differences. More words than that: the launch that adds them up takes less than the host.)
 constexpr int kPairCountWords = 8192;
 struct PairCounts {
     unsigned* words;
