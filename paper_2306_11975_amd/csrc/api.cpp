@@ -35,6 +35,7 @@ struct Layout {
     size_t off_ea[2], off_eb[2];
     size_t off_colmax, off_d, off_z, off_gate;
     size_t total;
+    bool large_if_shared;   // the larger tiles are taken for their shared walks, which need room behind the layout (in_room)
 };
 
 // Tile shape and count (the byte offsets of a layout do not depend on them: D exists only with k-blocking,
@@ -97,6 +98,12 @@ size_t split_available(size_t total) {
     return total <= limit ? limit - total : SIZE_MAX;
 }
 
+// Eleven slices to thirteen: small tiles were chosen by rounds, but where larger ones leave compute units idle several workgroups share each, and more of
+// those may fit a round than two of the smaller ones (410 x 1174 x 3391 at thirteen slices, 70 tiles three ways or 133: 198 us per call, 220).
+bool large_shared_ahead(const Layout& large, const Layout& small, int s, size_t available) {
+    return choose_split(large, s, available).us < 0.95 * choose_split(small, s, available).us;
+}
+
 Layout make_layout(int64_t m, int64_t n, int64_t k, int s, bool cplx) {
     Layout L{};
     L.m_pad = round_up(m, kRowAlign);
@@ -125,12 +132,11 @@ Layout make_layout(int64_t m, int64_t n, int64_t k, int s, bool cplx) {
     L.off_scan = off;   // the counters of splitters that count for the slice-count check: first operand, then second
     off = align_up(off + 2 * scan_slots_bytes(planes));
     L.total = off;
-    // Eleven slices to thirteen: small tiles were chosen by rounds, but where larger ones leave compute units idle several workgroups share each, and more of
-    // those may fit a round than two of the smaller ones (410 x 1174 x 3391 at thirteen slices, 70 tiles three ways or 133: 198 us per call, 220).
     if (s > 10 && s <= 13 && L.tile_cols == 64 && k > 0 && (int64_t)L.tiles_m * L.tiles_n <= kComputeUnits) {
         Layout large = L;
         set_tiles(large, m, n, s, false, one_launch);
-        if (choose_split(large, s, split_available(L.total)).us < 0.95 * choose_split(L, s, split_available(L.total)).us) L = large;
+        large.large_if_shared = true;
+        if (large_shared_ahead(large, L, s, split_available(L.total))) L = large;
     }
     return L;
 }
@@ -231,6 +237,16 @@ Room room_behind(unsigned char* ws, size_t used, size_t workspace_bytes) {
     used = align_up(used);
     return workspace_bytes > used ? Room{ws + used, workspace_bytes - used} : Room{nullptr, 0};
 }
+// The layout with the tiles for the room there is: with less than is reported, larger ones whose walks it does not let workgroups share take longer than
+// small ones (410 x 1174 x 3391 at thirteen slices with the least workspace 355 us per call, on small tiles 217).
+Layout in_room(Layout L, int64_t m, int64_t n, int s, bool one_launch, const Room& room) {
+    if (L.large_if_shared) {
+        Layout small = L;
+        set_tiles(small, m, n, s, true, one_launch);
+        if (!large_shared_ahead(L, small, s, room.bytes)) L = small;
+    }
+    return L;
+}
 void set_split(GemmArgs& g, const Layout& L, int s, const Room& room) {
     const Split sp = choose_split(L, s, room.bytes);
     g.splits = sp.splits;
@@ -241,9 +257,10 @@ void set_split(GemmArgs& g, const Layout& L, int s, const Room& room) {
 
 // One real Ozaki product from already split planes: G = sum over diagonals, combined into C as
 // c_mode says (C_lo != nullptr: double-double sum into C, C_lo).
-hipError_t run_product(const Layout& L, int64_t m, int64_t n, int s, unsigned char* ws, int plane_a, int plane_b,
+hipError_t run_product(const Layout& layout, int64_t m, int64_t n, int s, unsigned char* ws, int plane_a, int plane_b,
                        double* C, int64_t ldc, int c_mode, hipStream_t st, const Room& room, double alpha = 1.0, double beta = 0.0,
                        double* C_lo = nullptr, double* Zr = nullptr, double* Cz = nullptr, int64_t ldcz = 0) {
+    const Layout L = in_room(layout, m, n, s, false, room);
     GemmArgs g{};
     g.SA = reinterpret_cast<const int8_t*>(ws + L.off_sa[plane_a]);
     g.SB = reinterpret_cast<const int8_t*>(ws + L.off_sb[plane_b]);
@@ -280,8 +297,9 @@ hipError_t run_product(const Layout& L, int64_t m, int64_t n, int s, unsigned ch
 // the workspace (contiguous FP64: every update there is a full-line access), the second product of
 // each part combined with the first by one rounded FP64 operation in the kernel's epilogue; the
 // epilogue of the last product writes C, once, as (re, im) pairs.
-hipError_t run_complex_products(const Layout& L, int64_t m, int64_t n, int s, unsigned char* ws, double* C,
+hipError_t run_complex_products(const Layout& layout, int64_t m, int64_t n, int s, unsigned char* ws, double* C,
                                 int64_t ldc, hipStream_t st, const Room& room) {
+    const Layout L = in_room(layout, m, n, s, true, room);
     double* Pr = reinterpret_cast<double*>(ws + L.off_z);
     double* Pi = Pr + (size_t)m * n;
     if (!L.wide) {
