@@ -32,8 +32,11 @@ __global__ __launch_bounds__(kSmallThreads) void small_complex_kernel(const Smal
             small_patch<S, KS, false>(lds + pa * PLANE + pi * kFragBytes, lds + OPERAND + pb * PLANE + pj * kFragBytes, sum, lo);
             // The sums are formed here: put off to the stores behind the other products (the compiler's choice where nothing else needs them), they
             // would keep every product's diagonals, more than the registers hold: 156 spilled at sixteen slices, 1024 x 64 x 64 28.0 us per call, now 15.4 (with two launches 21.3).
+            // Where they do fit, the compiler's choice is the faster one (300 x 200 x 40 at five slices 8.45 us, formed here 8.71; 338 x 183 x 95 at six 12.4, 12.8).
+            if constexpr (KS == 1 ? S >= 6 : S >= (COUNT ? 5 : 7)) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) asm volatile("" : "+v"(sum[u])::"memory");
+                for (int u = 0; u < 4; ++u) asm volatile("" : "+v"(sum[u])::"memory");
+            }
             const int eb = ex[1][pb][16 * pj + (lane & 15)];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
