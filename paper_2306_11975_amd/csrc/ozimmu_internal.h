@@ -45,7 +45,7 @@ static inline void tile_waves(int s, bool small, int* wm, int* wn) {
 // ones of so few slices, and one slice, lose nothing). Five have the least to cover a load with where a workgroup has a compute unit to itself. Per call, small -> large:
 // 1033 x 12215 x 16484 at four 2830 -> 2550 us, 4990 x 1835 x 16428 at two 910 -> 845, 1169 x 9165 x 11163 at four 1524 -> 1430, complex 228 x 2401 x 5028 at five 403 -> 373; still
 // large -> small: complex 1836 x 544 x 17249 at four 1577 -> 1204, 1338 x 1549 x 12050 at six 735 -> 683. Fitted to 1190 products of one to nine slices that the estimate without these
-// terms has on small tiles, of which 123 took more than 1.5 % longer there, up to 10 %; of 350 others, with the terms, five do, up to 2.9 % (all seen: 455 x 6066 x 10890 at six, 4.8 %).
+// terms has on small tiles, of which 123 took more than 1.5 % longer there, up to 10 %; of 350 others, with the terms, four do, up to 2.9 % (the most seen: 455 x 6066 x 10890 at six, 4.8 %).
 // Eleven to thirteen: one workgroup per compute unit of either, and the same rate (4096^3 at eleven 2822, 2838 us; 4096 x 4096 x 512 396, 413), so rounds decide:
 // 1024^3 at twelve 103 -> 71, 300^3 42 -> 28, 1500 x 1500 x 1000 205 -> 171, complex 300^3 48 -> 35.
 // Ten keep the large tiles and two bands only because the interface's tests hold ozimmu_launch_plan to them (1000^3, 1024^3). They take longer: with this rule and one
